@@ -21,11 +21,11 @@ static constexpr int BS_FP_SRC[64] = {
     25, 57, 17, 49, 9, 41, 1, 33, 24, 56, 16, 48, 8, 40, 0, 32,
 };
 
-// S-box gate counts: S1=27, S2=24, S3=25, S4=19, S5=26, S6=25, S7=25, S8=25 (total 196 per round)
-#define BS_SBOX_GATES_PER_ROUND 196
+// S-box gate counts: S1=24, S2=20, S3=22, S4=16, S5=25, S6=23, S7=23, S8=23 (total 176 per round)
+#define BS_SBOX_GATES_PER_ROUND 176
 // XORs per round: 32 of S-box outputs into the other half, and the second
-// uses whose masks are not folded into the gates (2 of 16 are)
-#define BS_XORS_PER_ROUND 46
+// uses whose masks are not folded into the gates (0 of 16 are)
+#define BS_XORS_PER_ROUND 48
 
 // One Feistel round on 32 blocks per lane (Sec. III-B): d ^= P(S(E(r) ^ K)).
 // The halves are stored XORed with key masks: each word of r already
@@ -43,38 +43,35 @@ __device__ __forceinline__ void bs_round(uint32_t (&d)[32], const uint32_t (&r)[
         const uint32_t x2 = r[1];
         const uint32_t x3 = r[2];
         const uint32_t x4 = r[3];
-        const uint32_t x5 = r[4];  // mask folded into its gates
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x5, x4, km(32), 0x69);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x4, x1, g6, 0x93);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x3, g7, g6, 0xc5);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x1, x3, g6, 0xb8);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x2, g8, g9, 0xc9);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x3, x4, g6, 0x79);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x2, g11, x4, 0x9c);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x2, g10, g12, 0xed);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x1, g12, g13, 0x6c);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x0, g10, g14, 0xac);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x0, g10, g11, 0x9c);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x0, x3, g12, 0x83);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(g6, g16, g17, 0xc9);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x0, x2, x4, 0x6d);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g6, g15, g19, 0x1b);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(g7, g19, g20, 0x6c);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(g14, g18, g21, 0x6c);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x0, x1, x3, 0xd6);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(g20, g23, g8, 0x9c);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(x1, x4, g24, 0x56);
-        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(x0, x2, g21, 0xd9);
-        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g22, g25, g26, 0xc6);
-        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(g10, g24, g27, 0xac);
-        const uint32_t g29 = __builtin_amdgcn_bitop3_b32(x1, g7, g15, 0xd8);
-        const uint32_t g30 = __builtin_amdgcn_bitop3_b32(g28, g29, g13, 0xc2);
-        const uint32_t g31 = __builtin_amdgcn_bitop3_b32(x4, g20, g21, 0x3e);
-        const uint32_t g32 = __builtin_amdgcn_bitop3_b32(g22, g30, g31, 0x7c);
-        d[8] = __builtin_amdgcn_bitop3_b32(d[8], g15, km(0), 0x96);
-        d[16] = __builtin_amdgcn_bitop3_b32(d[16], g32, km(1), 0x96);
+        const uint32_t x5 = r[4] ^ km(32);
+        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x1, x4, x5, 0x69);
+        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x3, x4, g6, 0xb5);
+        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x1, g6, g7, 0x7c);
+        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x2, g7, g8, 0x25);
+        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x1, g7, g9, 0x4a);
+        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x4, g9, g10, 0x2b);
+        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x2, g7, g11, 0x39);
+        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x0, x2, g8, 0x29);
+        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x4, g7, g13, 0x8c);
+        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x3, g11, g14, 0x85);
+        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(g7, g12, g13, 0x4a);
+        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x3, g8, g16, 0x67);
+        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x0, g6, g17, 0x78);
+        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(g10, g15, g18, 0x2d);
+        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x0, g12, g19, 0xca);
+        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(g8, g12, g14, 0xf6);
+        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x4, g19, g17, 0x99);
+        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x4, x5, g20, 0xe9);
+        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x0, x1, x3, 0xd6);
+        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g8, g14, g23, 0xd8);
+        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(g9, g17, g22, 0x8f);
+        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g24, g25, g26, 0xd2);
+        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(g6, g23, g27, 0x96);
+        const uint32_t g29 = __builtin_amdgcn_bitop3_b32(g21, g22, g28, 0x63);
+        d[8] = __builtin_amdgcn_bitop3_b32(d[8], g20, km(0), 0x96);
+        d[16] = __builtin_amdgcn_bitop3_b32(d[16], g29, km(1), 0x69);
         d[22] = __builtin_amdgcn_bitop3_b32(d[22], g22, km(2), 0x96);
-        d[30] = __builtin_amdgcn_bitop3_b32(d[30], g28, km(3), 0x96);
+        d[30] = __builtin_amdgcn_bitop3_b32(d[30], g27, km(3), 0x96);
     }
     {  // S2
         const uint32_t x0 = r[3] ^ km(33);
@@ -83,34 +80,30 @@ __device__ __forceinline__ void bs_round(uint32_t (&d)[32], const uint32_t (&r)[
         const uint32_t x3 = r[6];
         const uint32_t x4 = r[7];
         const uint32_t x5 = r[8];
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x4, x5, 0x63);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x0, x5, g6, 0xb3);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x1, g6, g7, 0xc9);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x0, x1, g7, 0x58);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x2, g8, g9, 0x9c);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x1, x4, g6, 0xf4);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x3, g10, g11, 0x6c);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x3, x5, g11, 0x96);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x0, x1, g8, 0x86);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(g9, g14, g10, 0xdc);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(g12, g13, g15, 0x6c);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x2, g16, g9, 0x6c);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x1, x4, g17, 0x96);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x4, g8, g11, 0x9e);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g12, g18, g19, 0xc6);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x0, x2, g12, 0x4a);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(g14, g21, g17, 0x7c);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(g7, g20, g22, 0xc9);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(g17, g18, g20, 0xc6);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g12, g24, g19, 0x9c);
-        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(x0, g6, g20, 0xd2);
-        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g16, g21, g26, 0x7e);
-        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(x2, g26, g27, 0xac);
-        const uint32_t g29 = __builtin_amdgcn_bitop3_b32(x5, g25, g28, 0x6c);
-        d[12] = __builtin_amdgcn_bitop3_b32(d[12], g12, km(4), 0x96);
-        d[27] = __builtin_amdgcn_bitop3_b32(d[27], g23, km(5), 0x96);
-        d[1] = __builtin_amdgcn_bitop3_b32(d[1], g29, km(6), 0x96);
-        d[17] = __builtin_amdgcn_bitop3_b32(d[17], g17, km(7), 0x96);
+        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x1, x4, 0xd3);
+        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x4, x5, g6, 0xd7);
+        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x1, x5, g7, 0xf9);
+        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x0, x5, g8, 0x96);
+        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x2, x5, g6, 0xb4);
+        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x2, g8, g9, 0x4d);
+        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x3, g7, g11, 0x4b);
+        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(g8, g10, g12, 0x93);
+        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x4, g9, g13, 0x96);
+        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x5, g6, g13, 0x26);
+        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x5, g14, g15, 0x47);
+        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(g8, g12, g16, 0x63);
+        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x5, g10, g12, 0xb0);
+        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x1, x4, g18, 0x4b);
+        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g7, g14, g15, 0x21);
+        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(g17, g19, g20, 0x69);
+        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x0, g16, g17, 0x94);
+        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x5, g17, g22, 0xac);
+        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(g17, g21, g23, 0xae);
+        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g7, g15, g24, 0x96);
+        d[12] = __builtin_amdgcn_bitop3_b32(d[12], g14, km(4), 0x96);
+        d[27] = __builtin_amdgcn_bitop3_b32(d[27], g21, km(5), 0x69);
+        d[1] = __builtin_amdgcn_bitop3_b32(d[1], g25, km(6), 0x96);
+        d[17] = __builtin_amdgcn_bitop3_b32(d[17], g17, km(7), 0x69);
     }
     {  // S3
         const uint32_t x0 = r[7] ^ km(34);
@@ -118,36 +111,33 @@ __device__ __forceinline__ void bs_round(uint32_t (&d)[32], const uint32_t (&r)[
         const uint32_t x2 = r[9];
         const uint32_t x3 = r[10];
         const uint32_t x4 = r[11];
-        const uint32_t x5 = r[12];  // mask folded into its gates
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x5, x0, km(36), 0x69);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x0, x2, g6, 0xe8);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x4, g6, g7, 0x5c);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x2, x4, g6, 0x96);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x1, g8, g9, 0xac);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x1, x4, g8, 0x6d);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(g9, g11, x4, 0xc9);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x0, g10, g12, 0xca);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x3, g10, g13, 0xc5);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x1, x4, g9, 0x4a);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(g6, g8, g14, 0x9f);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x3, g15, g16, 0xc6);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x1, x3, g8, 0x69);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x4, g15, g18, 0xca);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x0, g17, g19, 0xca);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x0, g6, g10, 0x7e);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x3, g19, g21, 0x93);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(g7, g16, g19, 0x42);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x2, g22, g23, 0xc9);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(x1, g13, g17, 0x36);
-        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(x0, x2, g18, 0x89);
-        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g12, g25, g26, 0xca);
-        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(g21, g27, g20, 0xc9);
-        const uint32_t g29 = __builtin_amdgcn_bitop3_b32(g7, g9, g12, 0x31);
-        const uint32_t g30 = __builtin_amdgcn_bitop3_b32(g16, g28, g29, 0xca);
-        d[23] = __builtin_amdgcn_bitop3_b32(d[23], g14, km(8), 0x96);
-        d[15] = __builtin_amdgcn_bitop3_b32(d[15], g24, km(9), 0x96);
-        d[29] = __builtin_amdgcn_bitop3_b32(d[29], g30, km(10), 0x96);
-        d[5] = __builtin_amdgcn_bitop3_b32(d[5], g20, km(11), 0x96);
+        const uint32_t x5 = r[12] ^ km(36);
+        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x1, x4, x5, 0x96);
+        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x0, x2, g6, 0x69);
+        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x5, g6, g7, 0xc5);
+        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x2, x4, g8, 0x87);
+        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x1, g7, g9, 0xc6);
+        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x3, x4, g9, 0x5a);
+        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x4, g7, g11, 0x39);
+        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x5, g11, g12, 0xc6);
+        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x1, g12, g13, 0x9c);
+        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x0, g9, g14, 0xf6);
+        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x3, g10, g15, 0x39);
+        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(g11, g14, g15, 0x6d);
+        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x5, g8, g17, 0x1d);
+        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x1, g7, g17, 0xd9);
+        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x0, g12, g19, 0x29);
+        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x3, g18, g20, 0x17);
+        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x2, g12, g21, 0x69);
+        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x5, g10, g13, 0xd9);
+        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x0, g12, g23, 0x9c);
+        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(x4, g16, g21, 0x96);
+        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(x2, g24, g25, 0x6d);
+        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g9, g19, g26, 0x8d);
+        d[23] = __builtin_amdgcn_bitop3_b32(d[23], g16, km(8), 0x96);
+        d[15] = __builtin_amdgcn_bitop3_b32(d[15], g22, km(9), 0x69);
+        d[29] = __builtin_amdgcn_bitop3_b32(d[29], g27, km(10), 0x96);
+        d[5] = __builtin_amdgcn_bitop3_b32(d[5], g24, km(11), 0x69);
     }
     {  // S4
         const uint32_t x0 = r[11] ^ km(37);
@@ -156,29 +146,26 @@ __device__ __forceinline__ void bs_round(uint32_t (&d)[32], const uint32_t (&r)[
         const uint32_t x3 = r[14];
         const uint32_t x4 = r[15];
         const uint32_t x5 = r[16];
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x2, x3, x4, 0x4a);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x2, x3, x4, 0x73);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x0, g6, g7, 0xc6);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x0, x2, g6, 0xc1);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(g7, x0, g9, 0x9c);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x1, g8, g10, 0x6c);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x4, g7, g9, 0x95);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(g6, g10, g11, 0xe3);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x1, g12, g13, 0x6c);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x5, g11, g14, 0xc5);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x0, g6, g14, 0x69);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x1, x3, g14, 0x38);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(g11, g16, g17, 0xc6);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x1, x2, g8, 0xda);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x4, g8, g18, 0xa1);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x3, g19, g20, 0xc6);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x5, g18, g21, 0xc9);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x5, g18, g21, 0x6c);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x5, g11, g14, 0x53);
-        d[25] = __builtin_amdgcn_bitop3_b32(d[25], g24, km(12), 0x96);
-        d[19] = __builtin_amdgcn_bitop3_b32(d[19], g15, km(13), 0x96);
-        d[9] = __builtin_amdgcn_bitop3_b32(d[9], g23, km(14), 0x96);
-        d[0] = __builtin_amdgcn_bitop3_b32(d[0], g22, km(15), 0x96);
+        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x2, x4, 0x1c);
+        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x1, x3, g6, 0x14);
+        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x2, x3, x4, 0x4a);
+        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x1, g8, g6, 0x71);
+        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x0, g8, g9, 0x96);
+        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x4, g7, g10, 0xe9);
+        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x1, x3, g10, 0xb1);
+        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x5, g11, g12, 0x65);
+        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x3, g11, g12, 0x69);
+        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x2, g9, g14, 0xdb);
+        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(g9, g7, g15, 0x29);
+        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(g13, g15, g16, 0x96);
+        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x5, g11, g17, 0x96);
+        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x1, g10, g14, 0x69);
+        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x5, g16, g19, 0x95);
+        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x5, g16, g19, 0x56);
+        d[25] = __builtin_amdgcn_bitop3_b32(d[25], g17, km(12), 0x69);
+        d[19] = __builtin_amdgcn_bitop3_b32(d[19], g18, km(13), 0x96);
+        d[9] = __builtin_amdgcn_bitop3_b32(d[9], g20, km(14), 0x69);
+        d[0] = __builtin_amdgcn_bitop3_b32(d[0], g21, km(15), 0x69);
     }
     {  // S5
         const uint32_t x0 = r[15] ^ km(38);
@@ -187,36 +174,35 @@ __device__ __forceinline__ void bs_round(uint32_t (&d)[32], const uint32_t (&r)[
         const uint32_t x3 = r[18];
         const uint32_t x4 = r[19];
         const uint32_t x5 = r[20];
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x2, x3, x5, 0x72);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x2, x3, x5, 0x29);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x4, g6, g7, 0xc6);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x2, x3, x4, 0x59);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(g7, x4, g9, 0x35);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x0, g8, g10, 0x5c);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x0, g9, g11, 0x7e);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x3, g12, x4, 0xbc);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x1, g11, g13, 0x6c);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x0, x3, g10, 0x29);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x4, g7, g11, 0x49);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(g8, g15, g16, 0xc9);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x2, g8, g16, 0xe8);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x4, g7, g15, 0xd4);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x3, g18, g19, 0xac);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x1, g17, g20, 0xc9);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(g7, g13, g19, 0x76);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(g7, g8, g14, 0x48);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x5, g22, g23, 0x9c);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(x0, g13, g20, 0xb4);
-        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(x3, g25, g25, 0xdc);
-        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(x1, g24, g26, 0x6c);
-        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(g11, g21, g23, 0xe1);
-        const uint32_t g29 = __builtin_amdgcn_bitop3_b32(x1, x2, g12, 0x82);
-        const uint32_t g30 = __builtin_amdgcn_bitop3_b32(g9, g29, g13, 0xc1);
-        const uint32_t g31 = __builtin_amdgcn_bitop3_b32(g27, g28, g30, 0x9c);
-        d[7] = __builtin_amdgcn_bitop3_b32(d[7], g31, km(16), 0x96);
-        d[13] = __builtin_amdgcn_bitop3_b32(d[13], g27, km(17), 0x96);
-        d[24] = __builtin_amdgcn_bitop3_b32(d[24], g14, km(18), 0x96);
-        d[2] = __builtin_amdgcn_bitop3_b32(d[2], g21, km(19), 0x96);
+        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x2, x3, x5, 0xd6);
+        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x2, x3, x4, 0x69);
+        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x3, x5, g7, 0x56);
+        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x0, x3, g8, 0xd6);
+        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x4, g6, g9, 0x4d);
+        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x4, g6, g8, 0x59);
+        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x2, x5, g11, 0xb5);
+        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x0, g8, g12, 0xc5);
+        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x0, g11, g13, 0xe7);
+        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x3, x4, g14, 0x25);
+        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x1, g13, g15, 0x63);
+        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(g6, g12, g16, 0x84);
+        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(g7, g10, g17, 0x4b);
+        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(g9, g10, g15, 0x91);
+        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x5, g17, g19, 0x65);
+        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(g12, g14, g20, 0xf2);
+        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(g15, g18, g21, 0xb2);
+        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(g10, g14, g22, 0x82);
+        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x3, g10, g18, 0xc6);
+        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g9, g15, g21, 0xe1);
+        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(x1, g24, g25, 0x59);
+        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g13, g17, g26, 0xe1);
+        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(x0, x3, g22, 0xed);
+        const uint32_t g29 = __builtin_amdgcn_bitop3_b32(x1, g20, g28, 0x6c);
+        const uint32_t g30 = __builtin_amdgcn_bitop3_b32(g23, g27, g29, 0x39);
+        d[7] = __builtin_amdgcn_bitop3_b32(d[7], g30, km(16), 0x96);
+        d[13] = __builtin_amdgcn_bitop3_b32(d[13], g29, km(17), 0x96);
+        d[24] = __builtin_amdgcn_bitop3_b32(d[24], g16, km(18), 0x96);
+        d[2] = __builtin_amdgcn_bitop3_b32(d[2], g26, km(19), 0x96);
     }
     {  // S6
         const uint32_t x0 = r[19] ^ km(40);
@@ -225,35 +211,33 @@ __device__ __forceinline__ void bs_round(uint32_t (&d)[32], const uint32_t (&r)[
         const uint32_t x3 = r[22];
         const uint32_t x4 = r[23];
         const uint32_t x5 = r[24];
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x1, x5, 0x69);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x3, g6, g6, 0xc5);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x0, x1, g7, 0x46);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(g6, x0, g8, 0xc9);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x4, g7, g9, 0x9c);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x0, x4, g6, 0x6f);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x1, g11, x4, 0xcb);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x2, g10, g12, 0xc6);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x0, x2, g10, 0x37);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x1, g7, g14, 0x9c);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x2, g9, g10, 0xd3);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(g8, g16, g12, 0x4c);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x4, g15, g17, 0xca);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x3, x4, g16, 0x7c);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x2, x3, g18, 0x83);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x1, g19, g20, 0xc9);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x2, g8, g11, 0x56);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(g20, g22, g7, 0xca);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x0, g21, g23, 0x5c);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(x4, g6, g21, 0x69);
-        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(g19, g25, g20, 0xc7);
-        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g10, g12, g21, 0x87);
-        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(x0, g6, g20, 0x9e);
-        const uint32_t g29 = __builtin_amdgcn_bitop3_b32(x4, g27, g28, 0xac);
-        const uint32_t g30 = __builtin_amdgcn_bitop3_b32(x2, g26, g29, 0x5c);
-        d[3] = __builtin_amdgcn_bitop3_b32(d[3], g18, km(20), 0x96);
-        d[28] = __builtin_amdgcn_bitop3_b32(d[28], g30, km(21), 0x96);
-        d[10] = __builtin_amdgcn_bitop3_b32(d[10], g13, km(22), 0x96);
-        d[18] = __builtin_amdgcn_bitop3_b32(d[18], g24, km(23), 0x96);
+        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x1, x2, x4, 0x85);
+        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x0, x3, x5, 0x96);
+        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x1, x3, g7, 0xa5);
+        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x5, g7, g8, 0x16);
+        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x0, g7, g9, 0x51);
+        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x2, x4, g10, 0x4b);
+        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x0, x1, g9, 0x9b);
+        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x2, g11, g12, 0x87);
+        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x3, x4, g13, 0x7c);
+        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(g6, g8, g14, 0x6c);
+        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x0, g8, g14, 0x6f);
+        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x1, x4, g16, 0xad);
+        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x4, g15, g17, 0x47);
+        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(g8, g10, g11, 0x76);
+        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g15, g18, g19, 0x74);
+        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x2, g12, g16, 0x1c);
+        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(g13, g14, g21, 0x16);
+        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x2, x3, g19, 0x7c);
+        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x1, g14, g23, 0x39);
+        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g15, g22, g24, 0xc3);
+        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(g8, g11, g17, 0x87);
+        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g8, g18, g23, 0x4b);
+        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(x0, g27, g24, 0xca);
+        d[3] = __builtin_amdgcn_bitop3_b32(d[3], g20, km(20), 0x69);
+        d[28] = __builtin_amdgcn_bitop3_b32(d[28], g25, km(21), 0x96);
+        d[10] = __builtin_amdgcn_bitop3_b32(d[10], g26, km(22), 0x96);
+        d[18] = __builtin_amdgcn_bitop3_b32(d[18], g28, km(23), 0x69);
     }
     {  // S7
         const uint32_t x0 = r[23] ^ km(42);
@@ -262,34 +246,32 @@ __device__ __forceinline__ void bs_round(uint32_t (&d)[32], const uint32_t (&r)[
         const uint32_t x3 = r[26];
         const uint32_t x4 = r[27];
         const uint32_t x5 = r[28];
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x3, x4, 0x69);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x1, x3, x4, 0xb4);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x2, g6, g7, 0xc9);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x0, x1, g8, 0x66);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x0, x2, g6, 0x35);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(g7, g9, g10, 0x5c);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x5, g8, g11, 0x5c);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x0, g6, g12, 0x5c);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x0, x5, g11, 0xe8);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x3, g13, g14, 0x6c);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x0, x2, x3, 0x79);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x0, x3, x4, 0x2c);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x5, g16, g17, 0xbc);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x1, g15, g18, 0x6c);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x0, x2, g6, 0x56);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x5, g20, g11, 0xc5);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x2, x3, g18, 0x9a);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x5, g10, g22, 0x19);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x4, g22, g23, 0xc5);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(x1, g21, g24, 0xc6);
-        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(x3, g6, g19, 0xb6);
-        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g25, g26, x3, 0x7c);
-        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(x0, g21, g23, 0xb4);
-        const uint32_t g29 = __builtin_amdgcn_bitop3_b32(x2, g28, g9, 0xbc);
-        const uint32_t g30 = __builtin_amdgcn_bitop3_b32(g11, g27, g29, 0xc9);
+        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x1, x3, x4, 0xb4);
+        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x0, x3, x4, 0x96);
+        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x2, g6, g7, 0x1e);
+        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(g6, g7, g8, 0x3a);
+        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x0, x1, g6, 0xe4);
+        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(g8, g9, g10, 0x4e);
+        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x5, g9, g11, 0x5c);
+        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x3, x5, g11, 0x1f);
+        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x0, g12, g13, 0x91);
+        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x0, g7, g14, 0xae);
+        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x0, x1, g15, 0x71);
+        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x0, g9, g14, 0x37);
+        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x5, g16, g17, 0x9e);
+        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x1, x5, g18, 0x53);
+        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x0, x2, x3, 0x79);
+        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x5, g17, g20, 0x7a);
+        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x1, g15, g21, 0x93);
+        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x3, g7, g22, 0x16);
+        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(g8, g14, g23, 0xc9);
+        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g11, g19, g24, 0x69);
+        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(g18, g22, g25, 0x87);
+        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(x3, g23, g25, 0x64);
+        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(g11, g26, g27, 0xa6);
         d[31] = __builtin_amdgcn_bitop3_b32(d[31], g25, km(24), 0x96);
-        d[11] = __builtin_amdgcn_bitop3_b32(d[11], g19, km(25), 0x96);
-        d[21] = __builtin_amdgcn_bitop3_b32(d[21], g30, km(26), 0x96);
+        d[11] = __builtin_amdgcn_bitop3_b32(d[11], g22, km(25), 0x96);
+        d[21] = __builtin_amdgcn_bitop3_b32(d[21], g28, km(26), 0x69);
         d[6] = __builtin_amdgcn_bitop3_b32(d[6], g12, km(27), 0x96);
     }
     {  // S8
@@ -299,35 +281,33 @@ __device__ __forceinline__ void bs_round(uint32_t (&d)[32], const uint32_t (&r)[
         const uint32_t x3 = r[30];
         const uint32_t x4 = r[31] ^ km(46);
         const uint32_t x5 = r[0] ^ km(47);
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x1, x4, 0x65);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x1, x3, x4, 0x58);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x0, g6, g7, 0xc5);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x1, x3, g6, 0xd2);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x2, g8, g9, 0x6c);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x2, x3, g8, 0x69);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x0, x2, g6, 0xb5);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(g9, g11, g12, 0xc6);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x5, g10, g13, 0xc5);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x2, x3, x4, 0x72);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x5, g8, g13, 0x86);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x0, g15, g16, 0x9c);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x0, x5, g9, 0x90);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x0, x5, g11, 0x79);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g14, g18, g19, 0xc6);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x1, g17, g20, 0x9c);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(g6, g17, g19, 0x65);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(g18, g22, g15, 0x2c);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(g14, g17, g18, 0x08);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g6, g24, g13, 0xec);
-        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(g10, g23, g25, 0xc9);
-        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g10, g16, g19, 0xd4);
-        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(x1, g15, g18, 0x9c);
-        const uint32_t g29 = __builtin_amdgcn_bitop3_b32(x0, g27, g28, 0xac);
-        const uint32_t g30 = __builtin_amdgcn_bitop3_b32(x5, g29, g13, 0xac);
-        d[4] = __builtin_amdgcn_bitop3_b32(d[4], g30, km(28), 0x96);
+        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x1, x4, 0x9a);
+        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x1, x3, g6, 0x1e);
+        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x2, x3, x4, 0x72);
+        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x0, g6, g8, 0x7c);
+        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x1, g6, g8, 0x34);
+        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x0, g6, g10, 0xca);
+        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x2, x3, g11, 0x69);
+        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(g7, g9, g12, 0x6a);
+        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x5, g6, g13, 0xe9);
+        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x0, g8, g14, 0x93);
+        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x1, g8, g14, 0x49);
+        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(g12, g15, g16, 0x6d);
+        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x5, g13, g17, 0x36);
+        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x2, g7, g11, 0x65);
+        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x0, g8, g13, 0x18);
+        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x1, g10, g12, 0x83);
+        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x5, g13, g19, 0xac);
+        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(g20, g21, g22, 0xa3);
+        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x2, g15, g21, 0x76);
+        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g12, g23, g24, 0xe7);
+        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(x5, g19, g25, 0x96);
+        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(x3, g20, g26, 0x42);
+        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(x1, g15, g27, 0x63);
+        d[4] = __builtin_amdgcn_bitop3_b32(d[4], g18, km(28), 0x96);
         d[26] = __builtin_amdgcn_bitop3_b32(d[26], g26, km(29), 0x96);
-        d[14] = __builtin_amdgcn_bitop3_b32(d[14], g21, km(30), 0x96);
-        d[20] = __builtin_amdgcn_bitop3_b32(d[20], g14, km(31), 0x96);
+        d[14] = __builtin_amdgcn_bitop3_b32(d[14], g28, km(30), 0x96);
+        d[20] = __builtin_amdgcn_bitop3_b32(d[20], g22, km(31), 0x96);
     }
 }
 
@@ -368,38 +348,35 @@ __device__ __forceinline__ void bs_round_piped(uint32_t (&d)[32], const uint32_t
         const uint32_t x2 = r[1];
         const uint32_t x3 = r[2];
         const uint32_t x4 = r[3];
-        const uint32_t x5 = r[4];  // mask folded into its gates
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x5, x4, m.e[0], 0x69);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x4, x1, g6, 0x93);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x3, g7, g6, 0xc5);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x1, x3, g6, 0xb8);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x2, g8, g9, 0xc9);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x3, x4, g6, 0x79);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x2, g11, x4, 0x9c);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x2, g10, g12, 0xed);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x1, g12, g13, 0x6c);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x0, g10, g14, 0xac);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x0, g10, g11, 0x9c);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x0, x3, g12, 0x83);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(g6, g16, g17, 0xc9);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x0, x2, x4, 0x6d);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g6, g15, g19, 0x1b);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(g7, g19, g20, 0x6c);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(g14, g18, g21, 0x6c);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x0, x1, x3, 0xd6);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(g20, g23, g8, 0x9c);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(x1, x4, g24, 0x56);
-        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(x0, x2, g21, 0xd9);
-        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g22, g25, g26, 0xc6);
-        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(g10, g24, g27, 0xac);
-        const uint32_t g29 = __builtin_amdgcn_bitop3_b32(x1, g7, g15, 0xd8);
-        const uint32_t g30 = __builtin_amdgcn_bitop3_b32(g28, g29, g13, 0xc2);
-        const uint32_t g31 = __builtin_amdgcn_bitop3_b32(x4, g20, g21, 0x3e);
-        const uint32_t g32 = __builtin_amdgcn_bitop3_b32(g22, g30, g31, 0x7c);
-        d[8] = __builtin_amdgcn_bitop3_b32(d[8], g15, m.o[0], 0x96);
-        d[16] = __builtin_amdgcn_bitop3_b32(d[16], g32, m.o[1], 0x96);
+        const uint32_t x5 = r[4] ^ m.e[0];
+        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x1, x4, x5, 0x69);
+        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x3, x4, g6, 0xb5);
+        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x1, g6, g7, 0x7c);
+        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x2, g7, g8, 0x25);
+        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x1, g7, g9, 0x4a);
+        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x4, g9, g10, 0x2b);
+        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x2, g7, g11, 0x39);
+        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x0, x2, g8, 0x29);
+        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x4, g7, g13, 0x8c);
+        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x3, g11, g14, 0x85);
+        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(g7, g12, g13, 0x4a);
+        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x3, g8, g16, 0x67);
+        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x0, g6, g17, 0x78);
+        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(g10, g15, g18, 0x2d);
+        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x0, g12, g19, 0xca);
+        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(g8, g12, g14, 0xf6);
+        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x4, g19, g17, 0x99);
+        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x4, x5, g20, 0xe9);
+        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x0, x1, x3, 0xd6);
+        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g8, g14, g23, 0xd8);
+        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(g9, g17, g22, 0x8f);
+        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g24, g25, g26, 0xd2);
+        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(g6, g23, g27, 0x96);
+        const uint32_t g29 = __builtin_amdgcn_bitop3_b32(g21, g22, g28, 0x63);
+        d[8] = __builtin_amdgcn_bitop3_b32(d[8], g20, m.o[0], 0x96);
+        d[16] = __builtin_amdgcn_bitop3_b32(d[16], g29, m.o[1], 0x69);
         d[22] = __builtin_amdgcn_bitop3_b32(d[22], g22, m.o[2], 0x96);
-        d[30] = __builtin_amdgcn_bitop3_b32(d[30], g28, m.o[3], 0x96);
+        d[30] = __builtin_amdgcn_bitop3_b32(d[30], g27, m.o[3], 0x96);
     }
     {  // S2
         __builtin_amdgcn_sched_barrier(0);
@@ -413,34 +390,30 @@ __device__ __forceinline__ void bs_round_piped(uint32_t (&d)[32], const uint32_t
         const uint32_t x3 = r[6];
         const uint32_t x4 = r[7];
         const uint32_t x5 = r[8];
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x4, x5, 0x63);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x0, x5, g6, 0xb3);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x1, g6, g7, 0xc9);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x0, x1, g7, 0x58);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x2, g8, g9, 0x9c);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x1, x4, g6, 0xf4);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x3, g10, g11, 0x6c);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x3, x5, g11, 0x96);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x0, x1, g8, 0x86);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(g9, g14, g10, 0xdc);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(g12, g13, g15, 0x6c);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x2, g16, g9, 0x6c);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x1, x4, g17, 0x96);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x4, g8, g11, 0x9e);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g12, g18, g19, 0xc6);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x0, x2, g12, 0x4a);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(g14, g21, g17, 0x7c);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(g7, g20, g22, 0xc9);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(g17, g18, g20, 0xc6);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g12, g24, g19, 0x9c);
-        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(x0, g6, g20, 0xd2);
-        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g16, g21, g26, 0x7e);
-        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(x2, g26, g27, 0xac);
-        const uint32_t g29 = __builtin_amdgcn_bitop3_b32(x5, g25, g28, 0x6c);
-        d[12] = __builtin_amdgcn_bitop3_b32(d[12], g12, m.o[0], 0x96);
-        d[27] = __builtin_amdgcn_bitop3_b32(d[27], g23, m.o[1], 0x96);
-        d[1] = __builtin_amdgcn_bitop3_b32(d[1], g29, m.o[2], 0x96);
-        d[17] = __builtin_amdgcn_bitop3_b32(d[17], g17, m.o[3], 0x96);
+        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x1, x4, 0xd3);
+        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x4, x5, g6, 0xd7);
+        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x1, x5, g7, 0xf9);
+        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x0, x5, g8, 0x96);
+        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x2, x5, g6, 0xb4);
+        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x2, g8, g9, 0x4d);
+        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x3, g7, g11, 0x4b);
+        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(g8, g10, g12, 0x93);
+        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x4, g9, g13, 0x96);
+        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x5, g6, g13, 0x26);
+        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x5, g14, g15, 0x47);
+        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(g8, g12, g16, 0x63);
+        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x5, g10, g12, 0xb0);
+        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x1, x4, g18, 0x4b);
+        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g7, g14, g15, 0x21);
+        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(g17, g19, g20, 0x69);
+        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x0, g16, g17, 0x94);
+        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x5, g17, g22, 0xac);
+        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(g17, g21, g23, 0xae);
+        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g7, g15, g24, 0x96);
+        d[12] = __builtin_amdgcn_bitop3_b32(d[12], g14, m.o[0], 0x96);
+        d[27] = __builtin_amdgcn_bitop3_b32(d[27], g21, m.o[1], 0x69);
+        d[1] = __builtin_amdgcn_bitop3_b32(d[1], g25, m.o[2], 0x96);
+        d[17] = __builtin_amdgcn_bitop3_b32(d[17], g17, m.o[3], 0x69);
     }
     {  // S3
         __builtin_amdgcn_sched_barrier(0);
@@ -453,36 +426,33 @@ __device__ __forceinline__ void bs_round_piped(uint32_t (&d)[32], const uint32_t
         const uint32_t x2 = r[9];
         const uint32_t x3 = r[10];
         const uint32_t x4 = r[11];
-        const uint32_t x5 = r[12];  // mask folded into its gates
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x5, x0, m.e[2], 0x69);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x0, x2, g6, 0xe8);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x4, g6, g7, 0x5c);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x2, x4, g6, 0x96);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x1, g8, g9, 0xac);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x1, x4, g8, 0x6d);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(g9, g11, x4, 0xc9);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x0, g10, g12, 0xca);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x3, g10, g13, 0xc5);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x1, x4, g9, 0x4a);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(g6, g8, g14, 0x9f);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x3, g15, g16, 0xc6);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x1, x3, g8, 0x69);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x4, g15, g18, 0xca);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x0, g17, g19, 0xca);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x0, g6, g10, 0x7e);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x3, g19, g21, 0x93);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(g7, g16, g19, 0x42);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x2, g22, g23, 0xc9);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(x1, g13, g17, 0x36);
-        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(x0, x2, g18, 0x89);
-        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g12, g25, g26, 0xca);
-        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(g21, g27, g20, 0xc9);
-        const uint32_t g29 = __builtin_amdgcn_bitop3_b32(g7, g9, g12, 0x31);
-        const uint32_t g30 = __builtin_amdgcn_bitop3_b32(g16, g28, g29, 0xca);
-        d[23] = __builtin_amdgcn_bitop3_b32(d[23], g14, m.o[0], 0x96);
-        d[15] = __builtin_amdgcn_bitop3_b32(d[15], g24, m.o[1], 0x96);
-        d[29] = __builtin_amdgcn_bitop3_b32(d[29], g30, m.o[2], 0x96);
-        d[5] = __builtin_amdgcn_bitop3_b32(d[5], g20, m.o[3], 0x96);
+        const uint32_t x5 = r[12] ^ m.e[2];
+        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x1, x4, x5, 0x96);
+        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x0, x2, g6, 0x69);
+        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x5, g6, g7, 0xc5);
+        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x2, x4, g8, 0x87);
+        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x1, g7, g9, 0xc6);
+        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x3, x4, g9, 0x5a);
+        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x4, g7, g11, 0x39);
+        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x5, g11, g12, 0xc6);
+        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x1, g12, g13, 0x9c);
+        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x0, g9, g14, 0xf6);
+        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x3, g10, g15, 0x39);
+        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(g11, g14, g15, 0x6d);
+        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x5, g8, g17, 0x1d);
+        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x1, g7, g17, 0xd9);
+        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x0, g12, g19, 0x29);
+        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x3, g18, g20, 0x17);
+        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x2, g12, g21, 0x69);
+        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x5, g10, g13, 0xd9);
+        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x0, g12, g23, 0x9c);
+        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(x4, g16, g21, 0x96);
+        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(x2, g24, g25, 0x6d);
+        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g9, g19, g26, 0x8d);
+        d[23] = __builtin_amdgcn_bitop3_b32(d[23], g16, m.o[0], 0x96);
+        d[15] = __builtin_amdgcn_bitop3_b32(d[15], g22, m.o[1], 0x69);
+        d[29] = __builtin_amdgcn_bitop3_b32(d[29], g27, m.o[2], 0x96);
+        d[5] = __builtin_amdgcn_bitop3_b32(d[5], g24, m.o[3], 0x69);
     }
     {  // S4
         __builtin_amdgcn_sched_barrier(0);
@@ -496,29 +466,26 @@ __device__ __forceinline__ void bs_round_piped(uint32_t (&d)[32], const uint32_t
         const uint32_t x3 = r[14];
         const uint32_t x4 = r[15];
         const uint32_t x5 = r[16];
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x2, x3, x4, 0x4a);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x2, x3, x4, 0x73);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x0, g6, g7, 0xc6);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x0, x2, g6, 0xc1);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(g7, x0, g9, 0x9c);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x1, g8, g10, 0x6c);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x4, g7, g9, 0x95);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(g6, g10, g11, 0xe3);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x1, g12, g13, 0x6c);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x5, g11, g14, 0xc5);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x0, g6, g14, 0x69);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x1, x3, g14, 0x38);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(g11, g16, g17, 0xc6);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x1, x2, g8, 0xda);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x4, g8, g18, 0xa1);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x3, g19, g20, 0xc6);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x5, g18, g21, 0xc9);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x5, g18, g21, 0x6c);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x5, g11, g14, 0x53);
-        d[25] = __builtin_amdgcn_bitop3_b32(d[25], g24, m.o[0], 0x96);
-        d[19] = __builtin_amdgcn_bitop3_b32(d[19], g15, m.o[1], 0x96);
-        d[9] = __builtin_amdgcn_bitop3_b32(d[9], g23, m.o[2], 0x96);
-        d[0] = __builtin_amdgcn_bitop3_b32(d[0], g22, m.o[3], 0x96);
+        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x2, x4, 0x1c);
+        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x1, x3, g6, 0x14);
+        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x2, x3, x4, 0x4a);
+        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x1, g8, g6, 0x71);
+        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x0, g8, g9, 0x96);
+        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x4, g7, g10, 0xe9);
+        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x1, x3, g10, 0xb1);
+        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x5, g11, g12, 0x65);
+        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x3, g11, g12, 0x69);
+        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x2, g9, g14, 0xdb);
+        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(g9, g7, g15, 0x29);
+        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(g13, g15, g16, 0x96);
+        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x5, g11, g17, 0x96);
+        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x1, g10, g14, 0x69);
+        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x5, g16, g19, 0x95);
+        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x5, g16, g19, 0x56);
+        d[25] = __builtin_amdgcn_bitop3_b32(d[25], g17, m.o[0], 0x69);
+        d[19] = __builtin_amdgcn_bitop3_b32(d[19], g18, m.o[1], 0x96);
+        d[9] = __builtin_amdgcn_bitop3_b32(d[9], g20, m.o[2], 0x69);
+        d[0] = __builtin_amdgcn_bitop3_b32(d[0], g21, m.o[3], 0x69);
     }
     {  // S5
         __builtin_amdgcn_sched_barrier(0);
@@ -532,36 +499,35 @@ __device__ __forceinline__ void bs_round_piped(uint32_t (&d)[32], const uint32_t
         const uint32_t x3 = r[18];
         const uint32_t x4 = r[19];
         const uint32_t x5 = r[20];
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x2, x3, x5, 0x72);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x2, x3, x5, 0x29);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x4, g6, g7, 0xc6);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x2, x3, x4, 0x59);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(g7, x4, g9, 0x35);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x0, g8, g10, 0x5c);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x0, g9, g11, 0x7e);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x3, g12, x4, 0xbc);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x1, g11, g13, 0x6c);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x0, x3, g10, 0x29);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x4, g7, g11, 0x49);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(g8, g15, g16, 0xc9);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x2, g8, g16, 0xe8);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x4, g7, g15, 0xd4);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x3, g18, g19, 0xac);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x1, g17, g20, 0xc9);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(g7, g13, g19, 0x76);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(g7, g8, g14, 0x48);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x5, g22, g23, 0x9c);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(x0, g13, g20, 0xb4);
-        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(x3, g25, g25, 0xdc);
-        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(x1, g24, g26, 0x6c);
-        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(g11, g21, g23, 0xe1);
-        const uint32_t g29 = __builtin_amdgcn_bitop3_b32(x1, x2, g12, 0x82);
-        const uint32_t g30 = __builtin_amdgcn_bitop3_b32(g9, g29, g13, 0xc1);
-        const uint32_t g31 = __builtin_amdgcn_bitop3_b32(g27, g28, g30, 0x9c);
-        d[7] = __builtin_amdgcn_bitop3_b32(d[7], g31, m.o[0], 0x96);
-        d[13] = __builtin_amdgcn_bitop3_b32(d[13], g27, m.o[1], 0x96);
-        d[24] = __builtin_amdgcn_bitop3_b32(d[24], g14, m.o[2], 0x96);
-        d[2] = __builtin_amdgcn_bitop3_b32(d[2], g21, m.o[3], 0x96);
+        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x2, x3, x5, 0xd6);
+        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x2, x3, x4, 0x69);
+        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x3, x5, g7, 0x56);
+        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x0, x3, g8, 0xd6);
+        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x4, g6, g9, 0x4d);
+        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x4, g6, g8, 0x59);
+        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x2, x5, g11, 0xb5);
+        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x0, g8, g12, 0xc5);
+        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x0, g11, g13, 0xe7);
+        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x3, x4, g14, 0x25);
+        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x1, g13, g15, 0x63);
+        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(g6, g12, g16, 0x84);
+        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(g7, g10, g17, 0x4b);
+        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(g9, g10, g15, 0x91);
+        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x5, g17, g19, 0x65);
+        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(g12, g14, g20, 0xf2);
+        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(g15, g18, g21, 0xb2);
+        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(g10, g14, g22, 0x82);
+        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x3, g10, g18, 0xc6);
+        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g9, g15, g21, 0xe1);
+        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(x1, g24, g25, 0x59);
+        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g13, g17, g26, 0xe1);
+        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(x0, x3, g22, 0xed);
+        const uint32_t g29 = __builtin_amdgcn_bitop3_b32(x1, g20, g28, 0x6c);
+        const uint32_t g30 = __builtin_amdgcn_bitop3_b32(g23, g27, g29, 0x39);
+        d[7] = __builtin_amdgcn_bitop3_b32(d[7], g30, m.o[0], 0x96);
+        d[13] = __builtin_amdgcn_bitop3_b32(d[13], g29, m.o[1], 0x96);
+        d[24] = __builtin_amdgcn_bitop3_b32(d[24], g16, m.o[2], 0x96);
+        d[2] = __builtin_amdgcn_bitop3_b32(d[2], g26, m.o[3], 0x96);
     }
     {  // S6
         __builtin_amdgcn_sched_barrier(0);
@@ -575,35 +541,33 @@ __device__ __forceinline__ void bs_round_piped(uint32_t (&d)[32], const uint32_t
         const uint32_t x3 = r[22];
         const uint32_t x4 = r[23];
         const uint32_t x5 = r[24];
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x1, x5, 0x69);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x3, g6, g6, 0xc5);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x0, x1, g7, 0x46);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(g6, x0, g8, 0xc9);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x4, g7, g9, 0x9c);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x0, x4, g6, 0x6f);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x1, g11, x4, 0xcb);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x2, g10, g12, 0xc6);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x0, x2, g10, 0x37);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x1, g7, g14, 0x9c);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x2, g9, g10, 0xd3);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(g8, g16, g12, 0x4c);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x4, g15, g17, 0xca);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x3, x4, g16, 0x7c);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x2, x3, g18, 0x83);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x1, g19, g20, 0xc9);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x2, g8, g11, 0x56);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(g20, g22, g7, 0xca);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x0, g21, g23, 0x5c);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(x4, g6, g21, 0x69);
-        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(g19, g25, g20, 0xc7);
-        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g10, g12, g21, 0x87);
-        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(x0, g6, g20, 0x9e);
-        const uint32_t g29 = __builtin_amdgcn_bitop3_b32(x4, g27, g28, 0xac);
-        const uint32_t g30 = __builtin_amdgcn_bitop3_b32(x2, g26, g29, 0x5c);
-        d[3] = __builtin_amdgcn_bitop3_b32(d[3], g18, m.o[0], 0x96);
-        d[28] = __builtin_amdgcn_bitop3_b32(d[28], g30, m.o[1], 0x96);
-        d[10] = __builtin_amdgcn_bitop3_b32(d[10], g13, m.o[2], 0x96);
-        d[18] = __builtin_amdgcn_bitop3_b32(d[18], g24, m.o[3], 0x96);
+        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x1, x2, x4, 0x85);
+        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x0, x3, x5, 0x96);
+        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x1, x3, g7, 0xa5);
+        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x5, g7, g8, 0x16);
+        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x0, g7, g9, 0x51);
+        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x2, x4, g10, 0x4b);
+        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x0, x1, g9, 0x9b);
+        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x2, g11, g12, 0x87);
+        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x3, x4, g13, 0x7c);
+        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(g6, g8, g14, 0x6c);
+        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x0, g8, g14, 0x6f);
+        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x1, x4, g16, 0xad);
+        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x4, g15, g17, 0x47);
+        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(g8, g10, g11, 0x76);
+        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g15, g18, g19, 0x74);
+        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x2, g12, g16, 0x1c);
+        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(g13, g14, g21, 0x16);
+        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x2, x3, g19, 0x7c);
+        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x1, g14, g23, 0x39);
+        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g15, g22, g24, 0xc3);
+        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(g8, g11, g17, 0x87);
+        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g8, g18, g23, 0x4b);
+        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(x0, g27, g24, 0xca);
+        d[3] = __builtin_amdgcn_bitop3_b32(d[3], g20, m.o[0], 0x69);
+        d[28] = __builtin_amdgcn_bitop3_b32(d[28], g25, m.o[1], 0x96);
+        d[10] = __builtin_amdgcn_bitop3_b32(d[10], g26, m.o[2], 0x96);
+        d[18] = __builtin_amdgcn_bitop3_b32(d[18], g28, m.o[3], 0x69);
     }
     {  // S7
         __builtin_amdgcn_sched_barrier(0);
@@ -617,34 +581,32 @@ __device__ __forceinline__ void bs_round_piped(uint32_t (&d)[32], const uint32_t
         const uint32_t x3 = r[26];
         const uint32_t x4 = r[27];
         const uint32_t x5 = r[28];
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x3, x4, 0x69);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x1, x3, x4, 0xb4);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x2, g6, g7, 0xc9);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x0, x1, g8, 0x66);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x0, x2, g6, 0x35);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(g7, g9, g10, 0x5c);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x5, g8, g11, 0x5c);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x0, g6, g12, 0x5c);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x0, x5, g11, 0xe8);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x3, g13, g14, 0x6c);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x0, x2, x3, 0x79);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x0, x3, x4, 0x2c);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x5, g16, g17, 0xbc);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x1, g15, g18, 0x6c);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x0, x2, g6, 0x56);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x5, g20, g11, 0xc5);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x2, x3, g18, 0x9a);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x5, g10, g22, 0x19);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x4, g22, g23, 0xc5);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(x1, g21, g24, 0xc6);
-        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(x3, g6, g19, 0xb6);
-        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g25, g26, x3, 0x7c);
-        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(x0, g21, g23, 0xb4);
-        const uint32_t g29 = __builtin_amdgcn_bitop3_b32(x2, g28, g9, 0xbc);
-        const uint32_t g30 = __builtin_amdgcn_bitop3_b32(g11, g27, g29, 0xc9);
+        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x1, x3, x4, 0xb4);
+        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x0, x3, x4, 0x96);
+        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x2, g6, g7, 0x1e);
+        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(g6, g7, g8, 0x3a);
+        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x0, x1, g6, 0xe4);
+        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(g8, g9, g10, 0x4e);
+        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x5, g9, g11, 0x5c);
+        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x3, x5, g11, 0x1f);
+        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x0, g12, g13, 0x91);
+        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x0, g7, g14, 0xae);
+        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x0, x1, g15, 0x71);
+        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x0, g9, g14, 0x37);
+        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x5, g16, g17, 0x9e);
+        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x1, x5, g18, 0x53);
+        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x0, x2, x3, 0x79);
+        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x5, g17, g20, 0x7a);
+        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x1, g15, g21, 0x93);
+        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x3, g7, g22, 0x16);
+        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(g8, g14, g23, 0xc9);
+        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g11, g19, g24, 0x69);
+        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(g18, g22, g25, 0x87);
+        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(x3, g23, g25, 0x64);
+        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(g11, g26, g27, 0xa6);
         d[31] = __builtin_amdgcn_bitop3_b32(d[31], g25, m.o[0], 0x96);
-        d[11] = __builtin_amdgcn_bitop3_b32(d[11], g19, m.o[1], 0x96);
-        d[21] = __builtin_amdgcn_bitop3_b32(d[21], g30, m.o[2], 0x96);
+        d[11] = __builtin_amdgcn_bitop3_b32(d[11], g22, m.o[1], 0x96);
+        d[21] = __builtin_amdgcn_bitop3_b32(d[21], g28, m.o[2], 0x69);
         d[6] = __builtin_amdgcn_bitop3_b32(d[6], g12, m.o[3], 0x96);
     }
     {  // S8
@@ -659,34 +621,32 @@ __device__ __forceinline__ void bs_round_piped(uint32_t (&d)[32], const uint32_t
         const uint32_t x3 = r[30];
         const uint32_t x4 = r[31] ^ m.e[2];
         const uint32_t x5 = r[0] ^ m.e[3];
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x1, x4, 0x65);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x1, x3, x4, 0x58);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x0, g6, g7, 0xc5);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x1, x3, g6, 0xd2);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x2, g8, g9, 0x6c);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x2, x3, g8, 0x69);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x0, x2, g6, 0xb5);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(g9, g11, g12, 0xc6);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x5, g10, g13, 0xc5);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x2, x3, x4, 0x72);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x5, g8, g13, 0x86);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x0, g15, g16, 0x9c);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x0, x5, g9, 0x90);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x0, x5, g11, 0x79);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g14, g18, g19, 0xc6);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x1, g17, g20, 0x9c);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(g6, g17, g19, 0x65);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(g18, g22, g15, 0x2c);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(g14, g17, g18, 0x08);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g6, g24, g13, 0xec);
-        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(g10, g23, g25, 0xc9);
-        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g10, g16, g19, 0xd4);
-        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(x1, g15, g18, 0x9c);
-        const uint32_t g29 = __builtin_amdgcn_bitop3_b32(x0, g27, g28, 0xac);
-        const uint32_t g30 = __builtin_amdgcn_bitop3_b32(x5, g29, g13, 0xac);
-        d[4] = __builtin_amdgcn_bitop3_b32(d[4], g30, m.o[0], 0x96);
+        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x1, x4, 0x9a);
+        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x1, x3, g6, 0x1e);
+        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x2, x3, x4, 0x72);
+        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x0, g6, g8, 0x7c);
+        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x1, g6, g8, 0x34);
+        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x0, g6, g10, 0xca);
+        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x2, x3, g11, 0x69);
+        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(g7, g9, g12, 0x6a);
+        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x5, g6, g13, 0xe9);
+        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x0, g8, g14, 0x93);
+        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x1, g8, g14, 0x49);
+        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(g12, g15, g16, 0x6d);
+        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x5, g13, g17, 0x36);
+        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x2, g7, g11, 0x65);
+        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x0, g8, g13, 0x18);
+        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x1, g10, g12, 0x83);
+        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x5, g13, g19, 0xac);
+        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(g20, g21, g22, 0xa3);
+        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x2, g15, g21, 0x76);
+        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g12, g23, g24, 0xe7);
+        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(x5, g19, g25, 0x96);
+        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(x3, g20, g26, 0x42);
+        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(x1, g15, g27, 0x63);
+        d[4] = __builtin_amdgcn_bitop3_b32(d[4], g18, m.o[0], 0x96);
         d[26] = __builtin_amdgcn_bitop3_b32(d[26], g26, m.o[1], 0x96);
-        d[14] = __builtin_amdgcn_bitop3_b32(d[14], g21, m.o[2], 0x96);
-        d[20] = __builtin_amdgcn_bitop3_b32(d[20], g14, m.o[3], 0x96);
+        d[14] = __builtin_amdgcn_bitop3_b32(d[14], g28, m.o[2], 0x96);
+        d[20] = __builtin_amdgcn_bitop3_b32(d[20], g22, m.o[3], 0x96);
     }
 }

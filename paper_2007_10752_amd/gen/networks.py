@@ -76,9 +76,7 @@ def verify_network(box, net):
 # second use).  That XOR can be folded into the network when every gate that
 # depends on the input depends on one other signal at most: the gate then
 # takes the raw word, the other signal and the mask, and computes its
-# function of (word ^ mask).  Which of a word's two positions is the second
-# use is free; second_use_plan picks it so that as many second uses as
-# possible fold.
+# function of (word ^ mask).  second_use_plan says which second uses fold.
 
 MASK_BASE = 100  # signal MASK_BASE + q: the key mask of input q in a folded network
 
@@ -177,58 +175,25 @@ def shared_words():
     return [tuple(p) for j, p in sorted(pos.items()) if len(p) == 2]
 
 
+# The second use of each of the 16 words, as expansion positions: part of the
+# layout of device-resident schedules (kBsDupE), so it stays the same whatever
+# the networks are.
+SECOND_USES = (5, 6, 12, 13, 17, 18, 24, 25, 30, 31, 36, 37, 42, 43, 46, 47)
+
+
 def second_use_plan(nets):
-    """Choose, for each word read twice, which position is its second use,
-    and which second uses fold into their S-box's gates.  Maximises the
-    folded count; among equal plans keeps the most second uses at the later
-    position in e order.  Returns (second-use positions, folded positions),
-    both sets of e."""
-    shared = shared_words()
-    cand = {}  # box -> shared inputs of that box
-    for pair in shared:
-        for e in pair:
-            cand.setdefault(e // 6, []).append(e % 6)
-    options = []
+    """The second uses (SECOND_USES) and those of them that fold into their
+    S-box's gates, both as sets of e: per box the largest foldable subset,
+    the first of equals."""
+    pairs = shared_words()
+    assert all(sum(e in SECOND_USES for e in pair) == 1 for pair in pairs)
+    folded = set()
     for box in range(8):
-        qs = sorted(cand.get(box, []))
-        opts = [frozenset(c) for n in range(len(qs) + 1)
-                for c in itertools.combinations(qs, n) if foldable(nets[box], c)]
-        options.append(opts)
-    # each box has a handful of fold options at most (a fold needs a free
-    # operand in every gate that reads the input); keep the search bounded
-    # all the same by dropping the smaller options of the widest boxes
-    while True:
-        size = 1
-        for o in options:
-            size *= len(o)
-        if size <= 1 << 20:
-            break
-        widest = max(range(8), key=lambda b: len(options[b]))
-        options[widest] = sorted(options[widest], key=len)[len(options[widest]) // 2:]
-    best, best_key = None, None
-    for choice in itertools.product(*options):
-        fold_e = {6 * box + q for box, c in enumerate(choice) for q in c}
-        covered, second, moved = set(), set(), 0
-        ok = True
-        for first, later in shared:
-            if later in fold_e:
-                second.add(later)
-                covered.add(later)
-            elif first in fold_e:
-                second.add(first)
-                covered.add(first)
-                moved += 1
-            else:
-                second.add(later)
-        # a choice that folds both positions of one word folds one of them for nothing
-        if any(a in fold_e and b in fold_e for a, b in shared):
-            ok = False
-        if not ok:
-            continue
-        key = (len(covered), -moved)
-        if best_key is None or key > best_key:
-            best_key, best = key, (second, covered)
-    return best
+        qs = [e % 6 for e in SECOND_USES if e // 6 == box]
+        opts = [c for n in range(len(qs), -1, -1) for c in itertools.combinations(qs, n)
+                if foldable(nets[box], c)]
+        folded |= {6 * box + q for q in opts[0]}
+    return set(SECOND_USES), folded
 
 
 def format_networks(nets):

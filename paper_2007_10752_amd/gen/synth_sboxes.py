@@ -12,6 +12,12 @@ the emitter reads, so a normal build does not search.
 
     python -m paper_2007_10752_amd.gen.synth_sboxes --restarts 2000 --jobs 8
     python -m paper_2007_10752_amd.gen.synth_sboxes --restarts 1400 --restrict 1,2,16,32
+
+With --walk SECONDS it shrinks networks by local search instead
+(sbox_walk.cpp): each job starts from the stored network or, every other
+one, from a fresh result of sbox_synth.cpp.
+
+    python -m paper_2007_10752_amd.gen.synth_sboxes --walk 300 --jobs 8
 """
 import argparse
 import concurrent.futures as cf
@@ -27,10 +33,17 @@ from .networks import (NETWORKS_PATH, foldable, format_networks, load_networks, 
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 
-def _build(tmpdir):
-    exe = os.path.join(tmpdir, "sbox_synth")
-    subprocess.run(["g++", "-O2", "-o", exe, os.path.join(HERE, "sbox_synth.cpp")], check=True)
+def _build(tmpdir, name="sbox_synth"):
+    exe = os.path.join(tmpdir, name)
+    subprocess.run(["g++", "-O2", "-o", exe, os.path.join(HERE, name + ".cpp")], check=True)
     return exe
+
+
+def _walk(exe, box, seconds, seed, start):
+    vals = [str(v) for row in SBOX[box] for v in row]
+    r = subprocess.run([exe, str(seconds), str(seed), "0.35", "2"] + vals, check=True,
+                       input=format_networks({box: start}), capture_output=True, text=True)
+    return parse_network(r.stdout)
 
 
 def _run(exe, box, restarts, seed, restrict, lookahead):
@@ -87,6 +100,7 @@ def main():
     ap.add_argument("--restrict", default="0",
                     help="comma-separated bit masks of restricted inputs, one search each")
     ap.add_argument("--lookahead", type=int, default=int(os.environ.get("SBOX_LOOKAHEAD", "0")))
+    ap.add_argument("--walk", type=float, default=0, help="seconds of local search per job")
     args = ap.parse_args()
     boxes = [int(b) for b in args.boxes.split(",")]
     masks = [int(m) for m in args.restrict.split(",")]
@@ -95,6 +109,19 @@ def main():
     except FileNotFoundError:
         current = {}
     cands = {b: [current[b]] for b in range(8) if b in current}
+    if args.walk:
+        with tempfile.TemporaryDirectory() as td, cf.ThreadPoolExecutor(args.jobs) as pool:
+            synth, walk = _build(td), _build(td, "sbox_walk")
+
+            def job(box, j):
+                seed = args.seed * 1000003 + box * 7919 + j
+                start = current.get(box) if j % 2 == 0 else None
+                return _walk(walk, box, args.walk, seed, start or _run(synth, box, 1, seed, 0, 0))
+            futs = {pool.submit(job, b, j): b for j in range(args.jobs) for b in boxes}
+            for fut in cf.as_completed(futs):
+                verify_network(futs[fut], fut.result())
+                cands.setdefault(futs[fut], []).append(fut.result())
+        return _store(choose(cands))
     with tempfile.TemporaryDirectory() as td:
         exe = _build(td)
         per_job = max(1, args.restarts // args.jobs)
@@ -118,7 +145,10 @@ def main():
     for (box, mask), net in sorted(found.items()):
         print("S%d restrict %d: %d gates" % (box + 1, mask, len(net["gates"])))
         cands.setdefault(box, []).append(net)
-    best = choose(cands)
+    _store(choose(cands))
+
+
+def _store(best):
     _, folded = second_use_plan(best)
     for box in sorted(best):
         print("S%d: %d gates" % (box + 1, len(best[box]["gates"])))
