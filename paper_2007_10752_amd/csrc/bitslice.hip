@@ -28,6 +28,11 @@
 // out; nothing is loaded before the rounds.  CBC decryption decrypts the
 // loaded blocks, then XORs each with the ciphertext block before it (the
 // IV before the first), re-read after the rounds.
+//
+// Bound by VALU issue: 92 % of the SIMDs' issue slots are busy on 1 GiB, with
+// 0.875 of the instructions issued in pairs, at ~1.93 GHz under load.  With 224
+// operations a round (176 S-box gates) 1 GiB takes 1,028 us (1,044 GB/s);
+// with 242 (196 gates) it took 1,083 us.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -305,6 +310,10 @@ template <int MODE>
 hipError_t launch_mode(const BitsliceKeys &k, const ModeArgs &m, const uint8_t *in, uint8_t *out,
                        size_t nbytes, hipStream_t stream) {
     const size_t chunks = (nbytes + kChunk - 1) / kChunk;
+    // Up to five chunks a CU every SIMD here would hold one wave, some two, and
+    // the split kernel is the faster (20 MiB on 256 CUs: 33.5 against 35.4 us;
+    // 24 MiB: 38.5 against 37.7).
+    if (chunks <= 5 * device_cus()) return launch_bitslice_split<MODE>(k, m, in, out, nbytes, stream);
     const size_t blocks = (chunks + kWavesPerBlock - 1) / kWavesPerBlock;
     if (blocks > 0x7fffffffu) return hipErrorInvalidValue;
     const bool vec16 = ((((uintptr_t)in) | ((uintptr_t)out)) & 15u) == 0;

@@ -61,6 +61,9 @@ void round_sequence(const tdes_schedule &ks, int dir, RoundSequence *seq);
 void bitslice_keys(const tdes_schedule &ks, int dir, BitsliceKeys *out);
 void spbox_keys(const RoundSequence &seq, SpboxKeys *out);
 
+// Compute units of the current device.
+size_t device_cus();
+
 // Launchers: enqueue on `stream`; return the HIP launch status.
 hipError_t launch_bitslice(const BitsliceKeys &k, const uint8_t *in, uint8_t *out,
                            size_t nbytes, hipStream_t stream);
@@ -72,6 +75,11 @@ hipError_t launch_bitslice_ctr(const BitsliceKeys &k, uint64_t ctr, const uint8_
 hipError_t launch_bitslice_cbc_dec(const BitsliceKeys &k, uint32_t iv0, uint32_t iv1,
                                    const uint8_t *in, uint8_t *out, size_t nbytes,
                                    hipStream_t stream);
+// A mode (kModeEcb, kModeCtr, kModeCbcDec; keys and buffers as above) with
+// every chunk's S-boxes split over several waves (bitslice_split.hip).
+template <int MODE>
+hipError_t launch_bitslice_split(const BitsliceKeys &k, const ModeArgs &m, const uint8_t *in,
+                                 uint8_t *out, size_t nbytes, hipStream_t stream);
 size_t batch_workspace_bytes(size_t n_msgs);
 
 // Configuration of the batched cipher: the compiled variant (kmax messages

@@ -197,30 +197,29 @@ __global__ __launch_bounds__(kThreads) void tdes_spbox_multi_kernel(const SpboxM
                   (threadIdx.x % kCopies) * 4u, in_vgpr(kIndexMask), rk);
 }
 
-// Workgroups that fit on the current device at once, cached per device
-// (atomics: first calls from several threads may race; they all store the
-// same value).
-constexpr int kMaxDevices = 64;
-std::atomic<int> g_resident[kMaxDevices];
-
-int resident_workgroups() {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) dev = 0;
-    int n = g_resident[dev].load();
-    if (n == 0) {
-        int cus = 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            cus <= 0)
-            cus = 256;
-        n = 2 * cus;  // 64 KiB of tables per workgroup: two fit in 160 KiB of LDS
-        g_resident[dev].store(n);
-    }
-    return n;
-}
+// Workgroups that fit on the current device at once: 64 KiB of tables per
+// workgroup, two in a CU's 160 KiB of LDS.
+size_t resident_workgroups() { return 2 * device_cus(); }
 
 }  // namespace
 
-size_t spbox_one_pass_bytes() { return (size_t)resident_workgroups() * kThreads * 8; }
+// Cached per device (atomics: first calls from several threads may race;
+// they all store the same value).
+size_t device_cus() {
+    constexpr int kMaxDevices = 64;
+    static std::atomic<int> cache[kMaxDevices];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) dev = 0;
+    int n = cache[dev].load();
+    if (n == 0) {
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
+            n = 256;
+        cache[dev].store(n);
+    }
+    return (size_t)n;
+}
+
+size_t spbox_one_pass_bytes() { return resident_workgroups() * kThreads * 8; }
 
 hipError_t launch_spbox(const SpboxKeys &k, const uint8_t *in, uint8_t *out, size_t nbytes,
                         hipStream_t stream) {
@@ -229,13 +228,13 @@ hipError_t launch_spbox(const SpboxKeys &k, const uint8_t *in, uint8_t *out, siz
     // that the blocks spread over as many CUs as there are (one workgroup
     // each) rather than crowding a few CUs' LDS: the smallest per in 64,
     // 128, .. 1024 whose workgroups fit the CUs once.
-    const size_t cus = (size_t)resident_workgroups() / 2;
+    const size_t cus = device_cus();
     uint32_t per = 64;
     while (per < (uint32_t)kThreads && (nblocks + per - 1) / per > cus) per *= 2;
     size_t grid = (nblocks + per - 1) / per;
     // Two workgroups per resident slot: the second wave of workgroups fills
     // the slots of those that finish early.
-    const size_t cap = 2 * (size_t)resident_workgroups();
+    const size_t cap = 2 * resident_workgroups();
     if (grid > cap) grid = cap;
     hipLaunchKernelGGL(tdes_spbox_kernel, dim3((unsigned)grid), dim3(kThreads), 0, stream, in,
                        out, nblocks, per, k);
@@ -243,7 +242,7 @@ hipError_t launch_spbox(const SpboxKeys &k, const uint8_t *in, uint8_t *out, siz
 }
 
 uint32_t spbox_multi_lanes(const uint64_t *nblocks, size_t n) {
-    const uint64_t cus = (uint64_t)resident_workgroups() / 2;
+    const uint64_t cus = device_cus();
     uint32_t per = 64;
     for (; per < (uint32_t)kThreads; per *= 2) {
         uint64_t wgs = 0;

@@ -7,6 +7,7 @@ Outputs
   des_tables_gen.h   PC-1 / PC-2 / rotation tables for the host key schedule
   bitslice_gen.h     bitsliced kernel: IP and FP as plane renaming, one
                      Feistel round (E and P as renaming, S-boxes as gates)
+  bitslice_boxes_gen.h  the S-boxes one by one, for the split bitsliced kernel
   bitslice_keys_gen.h  host tables for the bitsliced kernel's key masks
   spbox_gen.h        table kernel: the 8 combined S-box+P tables and IP/FP as
                      delta swaps on a block held in two 32-bit words
@@ -282,6 +283,43 @@ def emit_round_piped(nets):
     return "".join(s)
 
 
+def emit_bitslice_boxes(nets):
+    """The S-boxes as separate functions, for kernels in which a wave runs
+    some of them only: bs_box<J>(x, d, m) reads the box's six right-half
+    words x (raw, in input order), XORs its outputs and their re-masks
+    m.o[q] into the four words d[q] of the other half that they land in, and
+    takes the second-use masks m.e[i] as bs_round_piped does."""
+    _, _, dup_of_e, _ = e_structure(nets)
+    s = [BANNER, "#pragma once\n#include <stdint.h>\n\n#include \"bitslice_gen.h\"\n\n",
+         "// One S-box on 32 blocks per lane: d[q] ^= output q ^ m.o[q], x the box's six\n"
+         "// inputs as right-half words, m.e[i] the mask of its i-th second-use input.\n"
+         "template <int J>\n"
+         "__device__ __forceinline__ void bs_box(const uint32_t *x, uint32_t *d, const BsBoxMasks &m);\n"]
+    for box in range(8):
+        net = box_network(nets, box)
+        s.append("\ntemplate <>\n__device__ __forceinline__ void bs_box<%d>(const uint32_t *x, uint32_t *d,\n"
+                 "                                           const BsBoxMasks &m) {  // S%d\n" % (box, box + 1))
+        names, di = {}, 0
+        for q in range(6):
+            names[q] = "x%d" % q
+            masked = dup_of_e[6 * box + q] >= 0
+            if masked and q in net["folded"]:
+                names[MASK_BASE + q] = "m.e[%d]" % di
+            s.append("    const uint32_t x%d = x[%d]%s;\n"
+                     % (q, q, " ^ m.e[%d]" % di if masked and q not in net["folded"] else ""))
+            di += masked
+        for i, (a, b, c, imm) in enumerate(net["gates"]):
+            nm = "g%d" % (6 + i)
+            s.append("    const uint32_t %s = __builtin_amdgcn_bitop3_b32(%s, %s, %s, 0x%02x);\n"
+                     % (nm, names[a], names[b], names[c], imm))
+            names[6 + i] = nm
+        for q, (sig, neg) in enumerate(net["outs"]):
+            s.append("    d[%d] = __builtin_amdgcn_bitop3_b32(d[%d], %s, m.o[%d], 0x%02x);\n"
+                     % (q, q, names[sig], q, 0x69 if neg else 0x96))
+        s.append("}\n")
+    return "".join(s)
+
+
 def emit_bitslice_keys():
     """Host-side tables for building the bitsliced kernel's key masks."""
     src, primary, dup_of_e, dup_e = e_structure()
@@ -506,6 +544,7 @@ def main():
     os.makedirs(OUT_DIR, exist_ok=True)
     for name, text in (("des_tables_gen.h", emit_tables()),
                        ("bitslice_gen.h", emit_bitslice(nets)),
+                       ("bitslice_boxes_gen.h", emit_bitslice_boxes(nets)),
                        ("bitslice_keys_gen.h", emit_bitslice_keys()),
                        ("spbox_gen.h", emit_spbox()),
                        ("replica_tables_gen.h", emit_replica_tables())):
