@@ -79,25 +79,31 @@ tdes_status tdes::set_last_error(tdes_status st, const char *msg) {
 }
 
 int tdes::auto_kernel(size_t nbytes) {
-    // one and a half passes: up to there the table kernel's launch is the
-    // shorter (measured: 28.6 against 35.1 us at 6 MiB on 256 CUs, 35.6
-    // against 35.2 at 6.5 MiB)
+    // one and a half passes: up to there the table kernel's launch is shorter
+    // than the plain bitsliced kernel's (launch_auto has a third choice)
     return nbytes <= spbox_one_pass_bytes() / 2 * 3 ? TDES_KERNEL_SPBOX : TDES_KERNEL_BITSLICE;
 }
 
-hipError_t tdes::launch_ecb_auto(const tdes_schedule &ks, int dir, const uint8_t *in,
-                                 uint8_t *out, size_t nbytes, hipStream_t stream) {
-    if (auto_kernel(nbytes) == TDES_KERNEL_SPBOX) {
+template <int MODE>
+hipError_t tdes::launch_auto(const tdes_schedule &ks, int dir, const ModeArgs &m, const uint8_t *in,
+                             uint8_t *out, size_t nbytes, hipStream_t stream) {
+    // The table kernel as long as its workgroups have a CU each (2 MiB on 256
+    // CUs): one lane's 48 rounds on one block, 6-11 us a launch against 15 for
+    // the bitsliced kernel with its S-boxes split over waves.  Two workgroups
+    // share a CU's LDS beyond: 17.8 against 15.4 us at 3 MiB.
+    if (nbytes <= spbox_one_pass_bytes() / 2) {
         RoundSequence seq;
         round_sequence(ks, dir, &seq);
         SpboxKeys k;
         spbox_keys(seq, &k);
-        return launch_spbox(k, in, out, nbytes, stream);
+        return launch_spbox<MODE>(k, m, in, out, nbytes, stream);
     }
     BitsliceKeys k;
     bitslice_keys(ks, dir, &k);
-    return launch_bitslice(k, in, out, nbytes, stream);
+    return launch_bitslice_mode<MODE>(k, m, in, out, nbytes, stream);
 }
+template hipError_t tdes::launch_auto<tdes::kModeEcb>(const tdes_schedule &, int, const ModeArgs &,
+                                                      const uint8_t *, uint8_t *, size_t, hipStream_t);
 
 extern "C" {
 
@@ -134,7 +140,7 @@ tdes_status tdes_ecb_crypt(const tdes_schedule *ks, int dir, int kernel, const v
         tdes::round_sequence(*ks, dir, &seq);
         tdes::SpboxKeys k;
         tdes::spbox_keys(seq, &k);
-        e = tdes::launch_spbox(k, in, out, nbytes, s);
+        e = tdes::launch_spbox<tdes::kModeEcb>(k, tdes::ModeArgs{}, in, out, nbytes, s);
     } else if (kernel == TDES_KERNEL_BITSLICE) {
         tdes::BitsliceKeys k;
         tdes::bitslice_keys(*ks, dir, &k);
@@ -154,11 +160,9 @@ tdes_status tdes_ctr_crypt(const tdes_schedule *ks, const uint8_t iv[8], const v
     if (st != TDES_OK || nbytes == 0) return st;
     uint64_t ctr = 0;
     for (int i = 0; i < 8; i++) ctr = ctr << 8 | iv[i];  // big-endian counter value
-    tdes::BitsliceKeys k;
-    tdes::bitslice_keys(*ks, TDES_ENCRYPT, &k);
-    hipError_t e = tdes::launch_bitslice_ctr(k, ctr, static_cast<const uint8_t *>(d_in),
-                                             static_cast<uint8_t *>(d_out), nbytes,
-                                             static_cast<hipStream_t>(stream));
+    hipError_t e = tdes::launch_auto<tdes::kModeCtr>(
+        *ks, TDES_ENCRYPT, tdes::ModeArgs{ctr, 0, 0}, static_cast<const uint8_t *>(d_in),
+        static_cast<uint8_t *>(d_out), nbytes, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail(TDES_ERR_DEVICE, "kernel launch failed: %s", hipGetErrorString(e));
     return TDES_OK;
 }
@@ -173,11 +177,9 @@ tdes_status tdes_cbc_decrypt(const tdes_schedule *ks, const uint8_t iv[8], const
         return fail(TDES_ERR_OVERLAP, "CBC decryption re-reads the ciphertext: no in-place");
     const uint32_t iv0 = iv[0] | iv[1] << 8 | iv[2] << 16 | (uint32_t)iv[3] << 24;
     const uint32_t iv1 = iv[4] | iv[5] << 8 | iv[6] << 16 | (uint32_t)iv[7] << 24;
-    tdes::BitsliceKeys k;
-    tdes::bitslice_keys(*ks, TDES_DECRYPT, &k);
-    hipError_t e = tdes::launch_bitslice_cbc_dec(k, iv0, iv1, static_cast<const uint8_t *>(d_in),
-                                                 static_cast<uint8_t *>(d_out), nbytes,
-                                                 static_cast<hipStream_t>(stream));
+    hipError_t e = tdes::launch_auto<tdes::kModeCbcDec>(
+        *ks, TDES_DECRYPT, tdes::ModeArgs{0, iv0, iv1}, static_cast<const uint8_t *>(d_in),
+        static_cast<uint8_t *>(d_out), nbytes, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail(TDES_ERR_DEVICE, "kernel launch failed: %s", hipGetErrorString(e));
     return TDES_OK;
 }

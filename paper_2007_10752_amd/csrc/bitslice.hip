@@ -306,9 +306,11 @@ void tdes_bitslice_kernel(const uint8_t *in, uint8_t *out, size_t nbytes, Bitsli
     }
 }
 
+}  // namespace
+
 template <int MODE>
-hipError_t launch_mode(const BitsliceKeys &k, const ModeArgs &m, const uint8_t *in, uint8_t *out,
-                       size_t nbytes, hipStream_t stream) {
+hipError_t launch_bitslice_mode(const BitsliceKeys &k, const ModeArgs &m, const uint8_t *in,
+                                uint8_t *out, size_t nbytes, hipStream_t stream) {
     const size_t chunks = (nbytes + kChunk - 1) / kChunk;
     // Up to five chunks a CU every SIMD here would hold one wave, some two, and
     // the split kernel is the faster (20 MiB on 256 CUs: 33.5 against 35.4 us;
@@ -326,22 +328,15 @@ hipError_t launch_mode(const BitsliceKeys &k, const ModeArgs &m, const uint8_t *
     return hipGetLastError();
 }
 
-}  // namespace
+template hipError_t launch_bitslice_mode<kModeCtr>(const BitsliceKeys &, const ModeArgs &,
+                                                   const uint8_t *, uint8_t *, size_t, hipStream_t);
+template hipError_t launch_bitslice_mode<kModeCbcDec>(const BitsliceKeys &, const ModeArgs &,
+                                                      const uint8_t *, uint8_t *, size_t,
+                                                      hipStream_t);
 
 hipError_t launch_bitslice(const BitsliceKeys &k, const uint8_t *in, uint8_t *out,
                            size_t nbytes, hipStream_t stream) {
-    return launch_mode<kModeEcb>(k, ModeArgs{}, in, out, nbytes, stream);
-}
-
-hipError_t launch_bitslice_ctr(const BitsliceKeys &k, uint64_t ctr, const uint8_t *in,
-                               uint8_t *out, size_t nbytes, hipStream_t stream) {
-    return launch_mode<kModeCtr>(k, ModeArgs{ctr, 0, 0}, in, out, nbytes, stream);
-}
-
-hipError_t launch_bitslice_cbc_dec(const BitsliceKeys &k, uint32_t iv0, uint32_t iv1,
-                                   const uint8_t *in, uint8_t *out, size_t nbytes,
-                                   hipStream_t stream) {
-    return launch_mode<kModeCbcDec>(k, ModeArgs{0, iv0, iv1}, in, out, nbytes, stream);
+    return launch_bitslice_mode<kModeEcb>(k, ModeArgs{}, in, out, nbytes, stream);
 }
 
 }  // namespace tdes

@@ -67,14 +67,13 @@ size_t device_cus();
 // Launchers: enqueue on `stream`; return the HIP launch status.
 hipError_t launch_bitslice(const BitsliceKeys &k, const uint8_t *in, uint8_t *out,
                            size_t nbytes, hipStream_t stream);
-// CTR mode: out = in XOR E(counter blocks ctr, ctr + 1, ...), k = encryption keys.
-hipError_t launch_bitslice_ctr(const BitsliceKeys &k, uint64_t ctr, const uint8_t *in,
-                               uint8_t *out, size_t nbytes, hipStream_t stream);
-// CBC decryption: out block i = D(in block i) XOR in block i - 1 (the IV for
-// i = 0), k = decryption keys; in and out must not overlap.
-hipError_t launch_bitslice_cbc_dec(const BitsliceKeys &k, uint32_t iv0, uint32_t iv1,
-                                   const uint8_t *in, uint8_t *out, size_t nbytes,
-                                   hipStream_t stream);
+// The same in a mode.  kModeCtr: out = in XOR E(counter blocks ctr, ctr + 1,
+// ...), k = encryption keys.  kModeCbcDec: out block i = D(in block i) XOR in
+// block i - 1 (the IV for i = 0), k = decryption keys; in and out must not
+// overlap.
+template <int MODE>
+hipError_t launch_bitslice_mode(const BitsliceKeys &k, const ModeArgs &m, const uint8_t *in,
+                                uint8_t *out, size_t nbytes, hipStream_t stream);
 // A mode (kModeEcb, kModeCtr, kModeCbcDec; keys and buffers as above) with
 // every chunk's S-boxes split over several waves (bitslice_split.hip).
 template <int MODE>
@@ -146,22 +145,25 @@ hipError_t batch_autotune(const tdes_msg *msgs, size_t n_msgs, const uint32_t *s
                           const TuneLane *lanes, int n_lanes, uint64_t out_bytes, int reps,
                           BatchConfig *best, float *best_us);
 // Bytes the table kernel covers with one block per lane in one wave of
-// resident workgroups on the current device (4 MiB on 256 CUs).  Up to 1.5
-// times this size it has the lower latency: its lanes each run one or two
-// blocks through the rounds, while a bitsliced lane runs 32 (one launch of
-// either kernel measured 8-29 us against 33-35 us); above it the bitsliced
-// kernel's throughput wins.
+// resident workgroups on the current device (4 MiB on 256 CUs).
 size_t spbox_one_pass_bytes();
 
-// tdes_ecb_crypt's TDES_KERNEL_AUTO: the table kernel up to one and a half
-// times spbox_one_pass_bytes(), the bitsliced kernel above (auto_kernel says which,
-// as a tdes_kernel value).
+// tdes_ecb_auto_kernel's answer, as a tdes_kernel value.
 int auto_kernel(size_t nbytes);
-hipError_t launch_ecb_auto(const tdes_schedule &ks, int dir, const uint8_t *in, uint8_t *out,
-                           size_t nbytes, hipStream_t stream);
+// What TDES_KERNEL_AUTO and the other modes run for a size: the table kernel
+// or the bitsliced ones (see api.cpp).
+template <int MODE>
+hipError_t launch_auto(const tdes_schedule &ks, int dir, const ModeArgs &m, const uint8_t *in,
+                       uint8_t *out, size_t nbytes, hipStream_t stream);
+inline hipError_t launch_ecb_auto(const tdes_schedule &ks, int dir, const uint8_t *in, uint8_t *out,
+                                  size_t nbytes, hipStream_t stream) {
+    return launch_auto<kModeEcb>(ks, dir, ModeArgs{}, in, out, nbytes, stream);
+}
 
-hipError_t launch_spbox(const SpboxKeys &k, const uint8_t *in, uint8_t *out, size_t nbytes,
-                        hipStream_t stream);
+// The table kernel in a mode (as for launch_bitslice_mode).
+template <int MODE>
+hipError_t launch_spbox(const SpboxKeys &k, const ModeArgs &m, const uint8_t *in, uint8_t *out,
+                        size_t nbytes, hipStream_t stream);
 
 // The table kernel over several messages in one launch, each with its own
 // keys (the request server's small batches).  Message i's blocks go to

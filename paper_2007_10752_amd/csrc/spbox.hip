@@ -28,6 +28,11 @@
 //
 // IP and FP run once per block as delta swaps; the three DES passes are
 // fused as in the bitsliced kernel (FP then IP cancel between passes).
+//
+// The modes are those of bitslice.hip.  Small inputs are bound by one lane's
+// chain of rounds (203 clocks each; the table fill takes ~2,100), large ones
+// by LDS and VALU issue together.  CTR and CBC decryption of 64 KiB run 6.5 us
+// a launch here, 14.7 on the split bitsliced kernel, 31 on the plain one.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -80,19 +85,36 @@ __device__ __forceinline__ uint32_t round_step(uint32_t L, uint32_t R, const uin
     return xor3(xor3(v0, v1, v2), xor3(v3, v4, v5), xor3(v6, v7, L));
 }
 
-// The 48 rounds and FP/IP of N blocks at once (in + 8 b, stride blocks
-// apart), interleaved so that one block's LDS reads wait while the others
-// compute.
+// What block b of a mode puts through the cipher (ECB and CBC: input block b;
+// CTR: its counter), and what is XORed into the result (CTR: input block b;
+// CBC: the block before, the IV for the first), as little-endian words.
+__device__ __forceinline__ uint2 load_block(const uint8_t *in, size_t b) {
+    return *reinterpret_cast<const uint2 *>(in + 8 * b);
+}
+template <int MODE>
+__device__ __forceinline__ uint2 cipher_input(const uint8_t *in, const ModeArgs &m, size_t b) {
+    if (MODE != kModeCtr) return load_block(in, b);
+    const uint64_t c = m.ctr + b;
+    return make_uint2(__builtin_bswap32((uint32_t)(c >> 32)), __builtin_bswap32((uint32_t)c));
+}
+template <int MODE>
+__device__ __forceinline__ uint2 xor_input(const uint8_t *in, const ModeArgs &m, size_t b) {
+    if (MODE == kModeCtr) return load_block(in, b);
+    if (MODE == kModeCbcDec) {
+        const uint2 w = load_block(in, b == 0 ? 0 : b - 1);
+        return b == 0 ? make_uint2(m.iv0, m.iv1) : w;
+    }
+    return make_uint2(0, 0);
+}
+
+// IP, the 48 rounds and FP of N blocks at once, in place, interleaved so that
+// one block's LDS reads wait while the others compute.
 template <int N>
-__device__ __forceinline__ void blocks(const uint8_t *in, uint8_t *out, size_t b, size_t stride,
-                                       const uint8_t *sp, uint32_t lane, uint32_t mask,
-                                       const uint4 *rk) {
+__device__ __forceinline__ void cipher_blocks(uint2 (&w)[N], const uint8_t *sp, uint32_t lane,
+                                              uint32_t mask, const uint4 *rk) {
     uint32_t X[N], Y[N];
 #pragma unroll
-    for (int i = 0; i < N; i++) {
-        const uint2 w = *reinterpret_cast<const uint2 *>(in + 8 * (b + i * stride));
-        SP_IP(w.x, w.y, X[i], Y[i]);
-    }
+    for (int i = 0; i < N; i++) SP_IP(w[i].x, w[i].y, X[i], Y[i]);
     // Pass 1: L = X, R = Y.
 #pragma unroll 2
     for (int r = 0; r < 16; r += 2) {
@@ -121,17 +143,28 @@ __device__ __forceinline__ void blocks(const uint8_t *in, uint8_t *out, size_t b
     for (int i = 0; i < N; i++) {
         uint32_t o0, o1;
         SP_FP(X[i], Y[i], o0, o1);  // preoutput R16 || L16 = Y || X
-        *reinterpret_cast<uint2 *>(out + 8 * (b + i * stride)) = make_uint2(o0, o1);
+        w[i] = make_uint2(o0, o1);
     }
 }
 
-// `per`: lanes of each workgroup that take blocks (a multiple of 64, at most
-// kThreads); all kThreads lanes fill the tables, then the others exit.
-__global__ __launch_bounds__(kThreads) void tdes_spbox_kernel(const uint8_t *in, uint8_t *out,
-                                                             size_t nblocks, uint32_t per,
-                                                             SpboxKeys keys) {
-    __shared__ __align__(16) uint32_t table[kTableWords];
-    __shared__ uint4 rk[48];
+// N blocks, stride blocks apart.
+template <int N, int MODE>
+__device__ __forceinline__ void blocks(const uint8_t *in, uint8_t *out, const ModeArgs &m, size_t b,
+                                       size_t stride, const uint8_t *sp, uint32_t lane,
+                                       uint32_t mask, const uint4 *rk) {
+    uint2 w[N];
+#pragma unroll
+    for (int i = 0; i < N; i++) w[i] = cipher_input<MODE>(in, m, b + i * stride);
+    cipher_blocks<N>(w, sp, lane, mask, rk);
+#pragma unroll
+    for (int i = 0; i < N; i++) {
+        const uint2 x = xor_input<MODE>(in, m, b + i * stride);
+        *reinterpret_cast<uint2 *>(out + 8 * (b + i * stride)) = make_uint2(w[i].x ^ x.x, w[i].y ^ x.y);
+    }
+}
+
+// The workgroup's tables and round keys; ends with a barrier.
+__device__ __forceinline__ void fill_tables(uint32_t *table, uint4 *rk, const SpboxKeys &keys) {
     // the 512 entries x 32 copies as 16-byte chunks (8 per entry), lane i
     // writing chunks i, i + 1024, ...: each store of a wave covers 1 KiB in a
     // row, free of bank conflicts
@@ -147,6 +180,19 @@ __global__ __launch_bounds__(kThreads) void tdes_spbox_kernel(const uint8_t *in,
         rk[r] = make_uint4(keys.w[r][0], keys.w[r][1], keys.w[r][2], keys.w[r][3]);
     }
     __syncthreads();
+}
+
+// `per`: lanes of each workgroup that take blocks (a multiple of 64, at most
+// kThreads); all kThreads lanes fill the tables, then the others exit.
+// (Requesting a lane's first block before the fill measured no faster:
+// 6.1-6.6 us for 64 KiB either way.)
+template <int MODE>
+__global__ __launch_bounds__(kThreads) void tdes_spbox_kernel(const uint8_t *in, uint8_t *out,
+                                                             size_t nblocks, uint32_t per,
+                                                             SpboxKeys keys, ModeArgs mode) {
+    __shared__ __align__(16) uint32_t table[kTableWords];
+    __shared__ uint4 rk[48];
+    fill_tables(table, rk, keys);
     if (threadIdx.x >= per) return;  // whole waves: per is a multiple of 64
     const uint8_t *sp = reinterpret_cast<const uint8_t *>(table);
     const uint32_t lane = (threadIdx.x % kCopies) * 4u;
@@ -156,9 +202,11 @@ __global__ __launch_bounds__(kThreads) void tdes_spbox_kernel(const uint8_t *in,
     // then two, then one.
     const size_t stride = (size_t)gridDim.x * per;
     size_t b = (size_t)blockIdx.x * per + threadIdx.x;
-    for (; b + 3 * stride < nblocks; b += 4 * stride) blocks<4>(in, out, b, stride, sp, lane, mask, rk);
-    for (; b + stride < nblocks; b += 2 * stride) blocks<2>(in, out, b, stride, sp, lane, mask, rk);
-    if (b < nblocks) blocks<1>(in, out, b, stride, sp, lane, mask, rk);
+    for (; b + 3 * stride < nblocks; b += 4 * stride)
+        blocks<4, MODE>(in, out, mode, b, stride, sp, lane, mask, rk);
+    for (; b + stride < nblocks; b += 2 * stride)
+        blocks<2, MODE>(in, out, mode, b, stride, sp, lane, mask, rk);
+    if (b < nblocks) blocks<1, MODE>(in, out, mode, b, stride, sp, lane, mask, rk);
 }
 
 // Several messages, each with its own keys: workgroup g takes up to `per`
@@ -180,21 +228,13 @@ __global__ __launch_bounds__(kThreads) void tdes_spbox_multi_kernel(const SpboxM
     const bool le = l64 < n && msgs[l64].first_wg <= g;
     const uint32_t k = (uint32_t)__popcll(__ballot(le));
     const uint32_t m = k > 0 ? k - 1 : 0;  // (k is at least 1 when message 0 starts at 0)
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-        const int c = threadIdx.x + j * kThreads;
-        const uint32_t v = SP_TABLE[c >> 3];
-        reinterpret_cast<uint4 *>(table)[c] = make_uint4(v, v, v, v);
-    }
-    if (threadIdx.x < 48)
-        rk[threadIdx.x] = *reinterpret_cast<const uint4 *>(keys[m].w[threadIdx.x]);
-    __syncthreads();
+    fill_tables(table, rk, keys[m]);
     if (threadIdx.x >= per) return;  // whole waves: per is a multiple of 64
     const SpboxMsg d = msgs[m];
     const uint64_t b = (uint64_t)(g - d.first_wg) * per + threadIdx.x;
     if (g >= d.first_wg && b < d.nblocks)
-        blocks<1>(d.in, d.out, b, 0, reinterpret_cast<const uint8_t *>(table),
-                  (threadIdx.x % kCopies) * 4u, in_vgpr(kIndexMask), rk);
+        blocks<1, kModeEcb>(d.in, d.out, ModeArgs{}, b, 0, reinterpret_cast<const uint8_t *>(table),
+                            (threadIdx.x % kCopies) * 4u, in_vgpr(kIndexMask), rk);
 }
 
 // Workgroups that fit on the current device at once: 64 KiB of tables per
@@ -221,8 +261,9 @@ size_t device_cus() {
 
 size_t spbox_one_pass_bytes() { return resident_workgroups() * kThreads * 8; }
 
-hipError_t launch_spbox(const SpboxKeys &k, const uint8_t *in, uint8_t *out, size_t nbytes,
-                        hipStream_t stream) {
+template <int MODE>
+hipError_t launch_spbox(const SpboxKeys &k, const ModeArgs &m, const uint8_t *in, uint8_t *out,
+                        size_t nbytes, hipStream_t stream) {
     const size_t nblocks = nbytes / 8;
     // Few blocks: fewer working lanes per workgroup and more workgroups, so
     // that the blocks spread over as many CUs as there are (one workgroup
@@ -236,10 +277,16 @@ hipError_t launch_spbox(const SpboxKeys &k, const uint8_t *in, uint8_t *out, siz
     // the slots of those that finish early.
     const size_t cap = 2 * resident_workgroups();
     if (grid > cap) grid = cap;
-    hipLaunchKernelGGL(tdes_spbox_kernel, dim3((unsigned)grid), dim3(kThreads), 0, stream, in,
-                       out, nblocks, per, k);
+    hipLaunchKernelGGL(tdes_spbox_kernel<MODE>, dim3((unsigned)grid), dim3(kThreads), 0, stream, in,
+                       out, nblocks, per, k, m);
     return hipGetLastError();
 }
+template hipError_t launch_spbox<kModeEcb>(const SpboxKeys &, const ModeArgs &, const uint8_t *,
+                                           uint8_t *, size_t, hipStream_t);
+template hipError_t launch_spbox<kModeCtr>(const SpboxKeys &, const ModeArgs &, const uint8_t *,
+                                           uint8_t *, size_t, hipStream_t);
+template hipError_t launch_spbox<kModeCbcDec>(const SpboxKeys &, const ModeArgs &, const uint8_t *,
+                                              uint8_t *, size_t, hipStream_t);
 
 uint32_t spbox_multi_lanes(const uint64_t *nblocks, size_t n) {
     const uint64_t cus = device_cus();
