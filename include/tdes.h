@@ -237,7 +237,7 @@ tdes_status tdes_batch_submit_noalloc(const tdes_msg *d_msgs, size_t n_msgs,
  *
  *   - Direct (d_work == NULL): h_in and h_out must be pinned host memory
  *     (hipHostMalloc), which is mapped into the device's address space.  The
- *     bitsliced kernel reads and writes them there, over PCIe in both
+ *     table kernel reads and writes them there, over PCIe in both
  *     directions at once; nothing is staged.  chunk_bytes and work_bytes
  *     are ignored.  Each range must lie within one pinned allocation
  *     (checked: TDES_ERR_ARG otherwise).
@@ -245,8 +245,8 @@ tdes_status tdes_batch_submit_noalloc(const tdes_msg *d_msgs, size_t n_msgs,
  *     chunks of chunk_bytes (the last one shorter).  Chunk i goes to slot
  *     i % n_slots of the device workspace d_work (n_slots =
  *     min(work_bytes / chunk_bytes, TDES_HOST_MAX_SLOTS)).  There it is
- *     copied in, encrypted or decrypted in place by the bitsliced kernel,
- *     and copied out, in order on that slot's stream.  The slots' streams
+ *     copied in, encrypted or decrypted in place by the size's kernel, and
+ *     copied out, in order on that slot's stream.  The slots' streams
  *     run side by side, so copies to the device, kernels and copies back of
  *     different chunks overlap.  The copies run asynchronously only if the
  *     host buffers are pinned; pageable memory gives the same result, more

@@ -84,14 +84,18 @@ int tdes::auto_kernel(size_t nbytes) {
     return nbytes <= spbox_one_pass_bytes() / 2 * 3 ? TDES_KERNEL_SPBOX : TDES_KERNEL_BITSLICE;
 }
 
-template <int MODE>
-hipError_t tdes::launch_auto(const tdes_schedule &ks, int dir, const ModeArgs &m, const uint8_t *in,
-                             uint8_t *out, size_t nbytes, hipStream_t stream) {
+bool tdes::auto_is_table(size_t nbytes) {
     // The table kernel as long as its workgroups have a CU each (2 MiB on 256
     // CUs): one lane's 48 rounds on one block, 6-11 us a launch against 15 for
     // the bitsliced kernel with its S-boxes split over waves.  Two workgroups
     // share a CU's LDS beyond: 17.8 against 15.4 us at 3 MiB.
-    if (nbytes <= spbox_one_pass_bytes() / 2) {
+    return nbytes <= spbox_one_pass_bytes() / 2;
+}
+
+template <int MODE>
+hipError_t tdes::launch_auto(const tdes_schedule &ks, int dir, const ModeArgs &m, const uint8_t *in,
+                             uint8_t *out, size_t nbytes, hipStream_t stream) {
+    if (auto_is_table(nbytes)) {
         RoundSequence seq;
         round_sequence(ks, dir, &seq);
         SpboxKeys k;
@@ -257,15 +261,17 @@ tdes_status tdes_ecb_host(const tdes_schedule *ks, int dir, const void *h_in, vo
     if (dir != TDES_ENCRYPT && dir != TDES_DECRYPT) return fail(TDES_ERR_ARG, "bad direction %d", dir);
     tdes_status st = check_buffers(h_in, h_out, nbytes);
     if (st != TDES_OK || nbytes == 0) return st;
-    tdes::BitsliceKeys k;
+    tdes::RoundSequence seq;
+    tdes::round_sequence(*ks, dir, &seq);
+    tdes::SpboxKeys kt;
+    tdes::spbox_keys(seq, &kt);
     if (d_work == nullptr) {  // direct: the kernel works on the mapped host buffers
         uint8_t *d_in = nullptr, *d_out = nullptr;
         hipError_t e = tdes::mapped_range(h_in, nbytes, &d_in);
         if (e == hipSuccess) e = tdes::mapped_range(h_out, nbytes, &d_out);
         if (e != hipSuccess)
             return fail(TDES_ERR_ARG, "direct mode needs pinned host buffers: %s", hipGetErrorString(e));
-        tdes::bitslice_keys(*ks, dir, &k);
-        e = tdes::run_host_direct(k, d_in, d_out, nbytes);
+        e = tdes::run_host_direct(kt, d_in, d_out, nbytes);
         if (e != hipSuccess) return fail(TDES_ERR_DEVICE, "direct host run failed: %s", hipGetErrorString(e));
         return TDES_OK;
     }
@@ -278,8 +284,9 @@ tdes_status tdes_ecb_host(const tdes_schedule *ks, int dir, const void *h_in, vo
                     chunk_bytes);
     size_t n_slots = work_bytes / chunk_bytes;
     if (n_slots > TDES_HOST_MAX_SLOTS) n_slots = TDES_HOST_MAX_SLOTS;
+    tdes::BitsliceKeys k;
     tdes::bitslice_keys(*ks, dir, &k);
-    hipError_t e = tdes::run_host_pipeline(k, static_cast<const uint8_t *>(h_in),
+    hipError_t e = tdes::run_host_pipeline(k, kt, static_cast<const uint8_t *>(h_in),
                                            static_cast<uint8_t *>(h_out), nbytes,
                                            static_cast<uint8_t *>(d_work), n_slots, chunk_bytes);
     if (e != hipSuccess) return fail(TDES_ERR_DEVICE, "host pipeline failed: %s", hipGetErrorString(e));

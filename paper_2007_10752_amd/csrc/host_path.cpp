@@ -1,9 +1,8 @@
 // Host-resident 3DES-ECB, two ways.
 //
 // Direct: the buffers are pinned host memory, mapped into the device's
-// address space, and the bitsliced kernel reads and writes them there over
-// PCIe; both directions of the link carry data at once and nothing is
-// staged.
+// address space, and the table kernel reads and writes them there over PCIe;
+// both directions of the link carry data at once and nothing is staged.
 //
 // Staged (any host memory): the buffer is processed in chunks staged
 // through device slots.  Each slot has its own stream, on which its chunks
@@ -53,8 +52,8 @@ hipError_t device_streams(hipStream_t (&out)[TDES_HOST_MAX_SLOTS]) {
 
 }  // namespace
 
-hipError_t run_host_pipeline(const BitsliceKeys &k, const uint8_t *h_in, uint8_t *h_out,
-                             size_t nbytes, uint8_t *d_work, size_t n_slots, size_t chunk) {
+hipError_t run_host_pipeline(const BitsliceKeys &kb, const SpboxKeys &ks, const uint8_t *h_in,
+                             uint8_t *h_out, size_t nbytes, uint8_t *d_work, size_t n_slots, size_t chunk) {
     std::lock_guard<std::mutex> lock(g_host_mutex);
     hipStream_t s[TDES_HOST_MAX_SLOTS];
     hipError_t first = device_streams(s);
@@ -69,7 +68,9 @@ hipError_t run_host_pipeline(const BitsliceKeys &k, const uint8_t *h_in, uint8_t
         const size_t len = nbytes - off < chunk ? nbytes - off : chunk;
         uint8_t *d = d_work + slot * chunk;
         hipError_t e = hipMemcpyAsync(d, h_in + off, len, hipMemcpyHostToDevice, s[slot]);
-        if (e == hipSuccess) e = launch_bitslice(k, d, d, len, s[slot]);
+        if (e == hipSuccess)
+            e = auto_is_table(len) ? launch_spbox<kModeEcb>(ks, ModeArgs{}, d, d, len, s[slot])
+                                   : launch_bitslice(kb, d, d, len, s[slot]);
         if (e == hipSuccess) e = hipMemcpyAsync(h_out + off, d, len, hipMemcpyDeviceToHost, s[slot]);
         first = e;
     }
@@ -107,13 +108,13 @@ hipError_t mapped_range(const void *h, size_t n, uint8_t **d) {
     return hipSuccess;
 }
 
-hipError_t run_host_direct(const BitsliceKeys &k, const uint8_t *d_in, uint8_t *d_out,
+hipError_t run_host_direct(const SpboxKeys &k, const uint8_t *d_in, uint8_t *d_out,
                            size_t nbytes) {
     std::lock_guard<std::mutex> lock(g_host_mutex);
     hipStream_t s[TDES_HOST_MAX_SLOTS];
     hipError_t e = device_streams(s);
     if (e != hipSuccess) return e;
-    e = launch_bitslice(k, d_in, d_out, nbytes, s[0]);
+    e = launch_spbox_host(k, d_in, d_out, nbytes, s[0]);
     const hipError_t w = hipStreamSynchronize(s[0]);
     return e != hipSuccess ? e : w;
 }

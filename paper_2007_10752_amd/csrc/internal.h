@@ -150,8 +150,9 @@ size_t spbox_one_pass_bytes();
 
 // tdes_ecb_auto_kernel's answer, as a tdes_kernel value.
 int auto_kernel(size_t nbytes);
-// What TDES_KERNEL_AUTO and the other modes run for a size: the table kernel
-// or the bitsliced ones (see api.cpp).
+// Whether TDES_KERNEL_AUTO and the other modes run the table kernel for a size
+// (the bitsliced ones otherwise), and the launch (see api.cpp).
+bool auto_is_table(size_t nbytes);
 template <int MODE>
 hipError_t launch_auto(const tdes_schedule &ks, int dir, const ModeArgs &m, const uint8_t *in,
                        uint8_t *out, size_t nbytes, hipStream_t stream);
@@ -164,6 +165,10 @@ inline hipError_t launch_ecb_auto(const tdes_schedule &ks, int dir, const uint8_
 template <int MODE>
 hipError_t launch_spbox(const SpboxKeys &k, const ModeArgs &m, const uint8_t *in, uint8_t *out,
                         size_t nbytes, hipStream_t stream);
+
+// The table kernel on device-mapped host memory (ECB).
+hipError_t launch_spbox_host(const SpboxKeys &k, const uint8_t *in, uint8_t *out, size_t nbytes,
+                             hipStream_t stream);
 
 // The table kernel over several messages in one launch, each with its own
 // keys (the request server's small batches).  Message i's blocks go to
@@ -190,17 +195,18 @@ hipError_t launch_spbox_multi(const SpboxMsg *d_msgs, uint32_t n, const SpboxKey
 hipError_t launch_replica_pass(const ReplicaKeyBits &k, const uint8_t *in, uint8_t *out,
                                size_t nbytes, hipStream_t stream);
 
-// Host-resident pipeline behind tdes_ecb_host (arguments already checked):
+// Host-resident pipeline behind tdes_ecb_host (arguments already checked; the
+// keys of both kernels, a chunk's size picks one):
 // chunks of `chunk` bytes through n_slots device slots at d_work; returns
 // once every chunk is back in h_out, or the first HIP error.
-hipError_t run_host_pipeline(const BitsliceKeys &k, const uint8_t *h_in, uint8_t *h_out,
+hipError_t run_host_pipeline(const BitsliceKeys &kb, const SpboxKeys &ks, const uint8_t *h_in, uint8_t *h_out,
                              size_t nbytes, uint8_t *d_work, size_t n_slots, size_t chunk);
 // Device address *d of the host range [h, h + n), n > 0: an error unless
 // the whole range lies in one pinned, device-mapped host allocation.
 hipError_t mapped_range(const void *h, size_t n, uint8_t **d);
-// The kernel run in place on device-mapped host memory (device addresses
-// from mapped_range); returns once it has finished, or the first HIP error.
-hipError_t run_host_direct(const BitsliceKeys &k, const uint8_t *d_in, uint8_t *d_out,
+// The table kernel on device-mapped host memory (device addresses from
+// mapped_range); returns once it has finished, or the first HIP error.
+hipError_t run_host_direct(const SpboxKeys &k, const uint8_t *d_in, uint8_t *d_out,
                            size_t nbytes);
 
 }  // namespace tdes

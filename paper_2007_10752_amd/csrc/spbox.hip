@@ -209,6 +209,32 @@ __global__ __launch_bounds__(kThreads) void tdes_spbox_kernel(const uint8_t *in,
     if (b < nblocks) blocks<1, MODE>(in, out, mode, b, stride, sp, lane, mask, rk);
 }
 
+// ECB over device-mapped host memory.  Bound by the PCIe link, which carries
+// both directions at once as long as reads and writes are spread evenly over
+// the launch: one block per lane and step, one workgroup a CU, and stores that
+// do not linger in L2 until the kernel ends (non-temporal).  16 MB in and out:
+// 377 us, 450 with plain stores, 549 on the bitsliced kernel, whose waves all
+// read, then all write (the copy engines take 337, both directions at once);
+// 256 MiB: 48.4 GB/s against 42.7.  Other shapes (256-1024 lanes, 128-512
+// workgroups, two adjacent blocks a lane, the next block requested early):
+// 368-430 us for 16 MB, none the faster at 256 MiB too.
+__global__ __launch_bounds__(kThreads) void tdes_spbox_host_kernel(const uint8_t *in, uint8_t *out,
+                                                                  size_t nblocks, uint32_t per,
+                                                                  SpboxKeys keys) {
+    __shared__ __align__(16) uint32_t table[kTableWords];
+    __shared__ uint4 rk[48];
+    fill_tables(table, rk, keys);
+    if (threadIdx.x >= per) return;
+    const uint32_t mask = in_vgpr(kIndexMask);
+    typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+    for (size_t b = (size_t)blockIdx.x * per + threadIdx.x; b < nblocks; b += (size_t)gridDim.x * per) {
+        uint2 w[1] = {load_block(in, b)};
+        cipher_blocks<1>(w, reinterpret_cast<const uint8_t *>(table), (threadIdx.x % kCopies) * 4u,
+                         mask, rk);
+        __builtin_nontemporal_store(v2u{w[0].x, w[0].y}, reinterpret_cast<v2u *>(out + 8 * b));
+    }
+}
+
 // Several messages, each with its own keys: workgroup g takes up to `per`
 // blocks of the message whose workgroup range holds g (one block per
 // working lane), after filling its tables and copying that message's round
@@ -261,17 +287,33 @@ size_t device_cus() {
 
 size_t spbox_one_pass_bytes() { return resident_workgroups() * kThreads * 8; }
 
+// Few blocks: fewer working lanes per workgroup and more workgroups, so that
+// the blocks spread over as many CUs as there are (one workgroup each) rather
+// than crowding a few CUs' LDS: the smallest of 64, 128, .. 1024 whose
+// workgroups fit the CUs once.
+static uint32_t working_lanes(size_t nblocks) {
+    const size_t cus = device_cus();
+    uint32_t per = 64;
+    while (per < (uint32_t)kThreads && (nblocks + per - 1) / per > cus) per *= 2;
+    return per;
+}
+
+hipError_t launch_spbox_host(const SpboxKeys &k, const uint8_t *in, uint8_t *out, size_t nbytes,
+                             hipStream_t stream) {
+    const size_t nblocks = nbytes / 8;
+    const uint32_t per = working_lanes(nblocks);
+    size_t grid = (nblocks + per - 1) / per;
+    if (grid > device_cus()) grid = device_cus();
+    hipLaunchKernelGGL(tdes_spbox_host_kernel, dim3((unsigned)grid), dim3(kThreads), 0, stream, in,
+                       out, nblocks, per, k);
+    return hipGetLastError();
+}
+
 template <int MODE>
 hipError_t launch_spbox(const SpboxKeys &k, const ModeArgs &m, const uint8_t *in, uint8_t *out,
                         size_t nbytes, hipStream_t stream) {
     const size_t nblocks = nbytes / 8;
-    // Few blocks: fewer working lanes per workgroup and more workgroups, so
-    // that the blocks spread over as many CUs as there are (one workgroup
-    // each) rather than crowding a few CUs' LDS: the smallest per in 64,
-    // 128, .. 1024 whose workgroups fit the CUs once.
-    const size_t cus = device_cus();
-    uint32_t per = 64;
-    while (per < (uint32_t)kThreads && (nblocks + per - 1) / per > cus) per *= 2;
+    const uint32_t per = working_lanes(nblocks);
     size_t grid = (nblocks + per - 1) / per;
     // Two workgroups per resident slot: the second wave of workgroups fills
     // the slots of those that finish early.
