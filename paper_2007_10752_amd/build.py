@@ -16,7 +16,7 @@ CSRC = os.path.join(PKG, "csrc")
 BUILD_DIR = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libtdes.so")
 SOURCES = ("api.cpp", "keysched.cpp", "serve.cpp", "host_path.cpp", "batch_tune.cpp",
-           "bitslice.hip", "bitslice_split.hip", "batch.hip",
+           "bitslice.hip", "bitslice_split.hip", "batch.hip", "batch_table.hip",
            "spbox.hip", "probe.hip", "replica.hip")
 ARCH = os.environ.get("TDES_OFFLOAD_ARCH", "gfx950")
 

@@ -22,6 +22,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "batch_core.h"
 #include "bitslice_core.h"
 #include "internal.h"
 #include "lds_masks.h"
@@ -37,42 +38,9 @@ namespace tdes {
 
 namespace {
 
-constexpr int kWave = 64;
 constexpr int kWavesPerBlock = 4;
 constexpr int kThreads = kWave * kWavesPerBlock;
-constexpr uint32_t kSlice = 256;  // bytes per lane
 constexpr int kScanThreads = 1024;
-
-// Workspace words: [0] total slices, [1] skipped messages,
-// [2 + i] first slice of message i (i = 0..n; entry n = total).
-constexpr int kWsHeader = 2;
-
-// Buffer sizes a batch's message ranges are checked against.
-struct BatchBounds {
-    uint64_t in_bytes, out_bytes;
-};
-
-__device__ __forceinline__ uint64_t slices_of(const tdes_msg &m, size_t n_sched, BatchBounds bb,
-                                              bool *bad) {
-    // bitwise, not short-circuit, so that no field is read under a branch;
-    // in_bytes - nbytes may wrap, but only where nbytes <= in_bytes fails
-    const bool ok = (((m.nbytes | m.in_off | m.out_off) % 8) == 0) & (m.sched_idx < n_sched) &
-                    (m.dir <= 1) & (m.nbytes <= bb.in_bytes) &
-                    (m.in_off <= bb.in_bytes - m.nbytes) & (m.nbytes <= bb.out_bytes) &
-                    (m.out_off <= bb.out_bytes - m.nbytes);
-    *bad = !ok;
-    return ok ? (m.nbytes + kSlice - 1) / kSlice : 0;
-}
-
-// Inclusive scan of v over the 64 lanes of a wave.
-__device__ __forceinline__ uint64_t wave_scan(uint64_t v, int lane) {
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const uint64_t u = __shfl_up(v, d, kWave);
-        if (lane >= d) v += u;
-    }
-    return v;
-}
 
 // The descriptor scan over many workgroups: each tile of kTile descriptors
 // is validated and scanned by its own workgroup (tile-local prefixes, the
@@ -98,7 +66,7 @@ __global__ __launch_bounds__(kScanThreads) void batch_tile_scan_kernel(const tde
     const bool live = i < n;
     const tdes_msg m = msgs[live ? i : n - 1];
     bool bad = false;
-    const uint64_t vi = slices_of(m, n_sched, bb, &bad);
+    const uint64_t vi = units_of(m, n_sched, bb, kSlice, &bad);
     const uint64_t v = live ? vi : 0;
     const uint64_t incl = wave_scan(v, lane);
     const uint32_t nbad = (uint32_t)__popcll(__ballot(live && bad));
@@ -392,23 +360,7 @@ void batch_bitslice_kernel(const tdes_msg *__restrict__ msgs, uint32_t n_msgs,
             __builtin_amdgcn_s_setprio(3);
             uint32_t lo, woff;
             {
-                // Message holding slice `base`: the largest m with first[m]
-                // <= base (first[] is non-decreasing, first[n_msgs] = total >
-                // base).  A 64-way search: each step every lane tests one
-                // evenly spaced entry and a ballot keeps the sub-range, so
-                // 16k messages take 3 steps.
-                lo = 0;
-                uint32_t hi = n_msgs;  // first[lo] <= base < first[hi]
-                while (hi - lo > 1) {
-                    const uint32_t step = (hi - lo + kWave - 1) / kWave;
-                    const uint64_t idx = lo + (uint64_t)(lane + 1) * step;
-                    const bool le = idx < hi && first[idx] <= base;
-                    const uint32_t k = (uint32_t)__popcll(__ballot(le));  // a prefix of lanes
-                    const uint64_t nhi = lo + (uint64_t)(k + 1) * step;
-                    lo = lo + k * step;
-                    hi = nhi < hi ? (uint32_t)nhi : hi;
-                }
-                lo = __builtin_amdgcn_readfirstlane(lo);
+                lo = find_message(first, n_msgs, base, lane);
                 // Each lane's message: m0 plus the number of the next 64
                 // message starts at or before its slice, found by a binary
                 // search over the starts held one per lane.  Past 63 of them
@@ -704,6 +656,43 @@ hipError_t launch_batch_prefixed(const tdes_msg *msgs, size_t n_msgs, const uint
     return launch_cipher(msgs, n_msgs, schedules, n_schedules, in, out, ws, need, stream);
 }
 
+namespace {
+
+// First-slice table, skipped count and total of a batch into ws.
+hipError_t launch_scan(const tdes_msg *msgs, size_t n_msgs, size_t n_schedules, BatchBounds bb,
+                       uint64_t *ws, uint64_t *skipped_out, hipStream_t stream) {
+    const size_t T = (n_msgs + kTile - 1) / kTile;  // n_msgs >= 1
+    if (T > 0x7fffffffu) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(batch_tile_scan_kernel, dim3((unsigned)T), dim3(kScanThreads), 0, stream,
+                       msgs, n_msgs, n_schedules, bb, ws);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (T <= kFusedTiles) {
+        hipLaunchKernelGGL(batch_tile_finish_kernel, dim3((unsigned)T), dim3(kScanThreads), 0,
+                           stream, n_msgs, ws, skipped_out);
+    } else {
+        hipLaunchKernelGGL(batch_tile_offsets_kernel, dim3(1), dim3(kScanThreads), 0, stream,
+                           n_msgs, ws, skipped_out);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(batch_tile_add_kernel, dim3((unsigned)T), dim3(kScanThreads), 0, stream,
+                           n_msgs, ws);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_bitslice(const tdes_msg *msgs, size_t n_msgs, const uint32_t *schedules,
+                                 size_t n_schedules, const uint8_t *in, uint64_t in_bytes,
+                                 uint8_t *out, uint64_t out_bytes, uint64_t *ws,
+                                 uint64_t *skipped_out, hipStream_t stream) {
+    const hipError_t e = launch_scan(msgs, n_msgs, n_schedules, BatchBounds{in_bytes, out_bytes},
+                                     ws, skipped_out, stream);
+    if (e != hipSuccess) return e;
+    return launch_cipher(msgs, n_msgs, schedules, n_schedules, in, out, ws, 0, stream);
+}
+
+}  // namespace
+
 hipError_t batch_autotune(const tdes_msg *msgs, size_t n_msgs, const uint32_t *schedules,
                           size_t n_schedules, const uint8_t *in, uint64_t in_bytes,
                           const TuneLane *lanes, int n_lanes, uint64_t out_bytes, int reps,
@@ -724,8 +713,8 @@ hipError_t batch_autotune(const tdes_msg *msgs, size_t n_msgs, const uint32_t *s
     float best_ms = 0;
     BatchConfig best = keep;
     auto run = [&](const TuneLane &l) {
-        return launch_batch(msgs, n_msgs, schedules, n_schedules, in, in_bytes, l.out, out_bytes,
-                            l.ws, nullptr, l.stream);
+        return launch_batch_bitslice(msgs, n_msgs, schedules, n_schedules, in, in_bytes, l.out,
+                                     out_bytes, l.ws, nullptr, l.stream);
     };
     const hipStream_t s0 = lanes[0].stream;
     for (int i = 0; i < n_cands && e == hipSuccess; i++) {
@@ -804,26 +793,15 @@ hipError_t launch_batch(const tdes_msg *msgs, size_t n_msgs, const uint32_t *sch
                         size_t n_schedules, const uint8_t *in, uint64_t in_bytes, uint8_t *out,
                         uint64_t out_bytes, uint64_t *ws, uint64_t *skipped_out,
                         hipStream_t stream) {
-    const size_t T = (n_msgs + kTile - 1) / kTile;  // n_msgs >= 1
-    if (T > 0x7fffffffu) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(batch_tile_scan_kernel, dim3((unsigned)T), dim3(kScanThreads), 0, stream,
-                       msgs, n_msgs, n_schedules, BatchBounds{in_bytes, out_bytes}, ws);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (T <= kFusedTiles) {
-        hipLaunchKernelGGL(batch_tile_finish_kernel, dim3((unsigned)T), dim3(kScanThreads), 0,
-                           stream, n_msgs, ws, skipped_out);
-    } else {
-        hipLaunchKernelGGL(batch_tile_offsets_kernel, dim3(1), dim3(kScanThreads), 0, stream,
-                           n_msgs, ws, skipped_out);
-        e = hipGetLastError();
+    const BatchBounds bb{in_bytes, out_bytes};
+    if (!batch_is_table(n_msgs, out_bytes))
+        return launch_batch_bitslice(msgs, n_msgs, schedules, n_schedules, in, in_bytes, out,
+                                     out_bytes, ws, skipped_out, stream);
+    if (n_msgs > kTableScanMax) {
+        const hipError_t e = launch_scan(msgs, n_msgs, n_schedules, bb, ws, skipped_out, stream);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(batch_tile_add_kernel, dim3((unsigned)T), dim3(kScanThreads), 0, stream,
-                           n_msgs, ws);
     }
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return launch_cipher(msgs, n_msgs, schedules, n_schedules, in, out, ws, 0, stream);
+    return launch_batch_table(msgs, n_msgs, schedules, n_schedules, in, out, bb, ws, skipped_out, stream);
 }
 
 }  // namespace tdes

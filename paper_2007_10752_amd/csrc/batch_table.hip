@@ -1,0 +1,286 @@
+// Batched 3DES-EDE ECB on the table kernel: small batches, and batches of small
+// messages.
+//
+// One block per lane (spbox.hip), the blocks of all messages in a row, `per`
+// lanes of them to a workgroup and step.  The bitsliced batch kernel (batch.hip) gives a
+// message at least one lane of 32 blocks and a wave one pass per 4 to 16
+// messages, each pass 48 rounds of some 240 instructions: ~40 us for the
+// smallest batch, and a wave of 64 messages of 256 bytes or less takes 8 passes.
+//
+// A workgroup has a CU to itself: 64 KiB of tables, the round keys of up to
+// kRows messages (a row each, 784 bytes, padded so that the rows of different
+// messages start on different banks) and the messages' first blocks.  Up to
+// kTableScanMax messages every workgroup scans the descriptors itself, so a
+// batch is one launch (one workgroup more leaves the scan in the workspace);
+// beyond, the scan launches of batch.hip come first and the lanes go by its
+// slices, 32 to a slice.  The round keys are recovered from the device schedule's mask words by one wave per
+// message: lane t the row's entry of round t (make_row).
+//
+// Bound by the latency of its steps (descriptors, schedules, tables, one block's
+// 48 rounds), which a workgroup goes through one after the other: ~10 us for the
+// smallest batch, 150 GB/s on large ones.  Measured (us a submit, bitsliced ->
+// table): 16 messages of 4 KiB 43.5 -> 9.7, 300 of 6.7 KB 45 -> 16, 2,000 of
+// 72 bytes 299 -> 12, 16,000 of 256 bytes 265 -> 53.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "batch_core.h"
+#include "generated/bitslice_keys_gen.h"
+#include "keysched_core.h"
+#include "spbox_core.h"
+
+namespace tdes {
+
+namespace {
+
+constexpr int kThreads = kTableThreads;
+constexpr int kWaves = kThreads / kWave;
+constexpr uint32_t kRows = 64;      // messages whose round keys are in LDS at once
+constexpr uint32_t kRowStride = 49;  // entries (16 bytes) from row to row: 48 rounds and a pad
+constexpr int kRowsPerWave = kRows / kWaves;
+
+// What lane t needs of a message's device schedule: round t's two words and the
+// extra words 96..98.
+struct RowWords {
+    uint2 w;
+    uint32_t e0, e1, e2;
+};
+
+__device__ __forceinline__ RowWords load_row(const tdes_msg &m, const uint32_t *sched,
+                                             uint32_t n_sched, uint32_t lane) {
+    const uint32_t *p = sched + (size_t)(m.sched_idx < n_sched ? m.sched_idx : 0u) * kDeviceScheduleWords +
+                        (m.dir & 1u) * kDirWords;
+    RowWords r;
+    r.w = reinterpret_cast<const uint2 *>(p)[lane < 48 ? lane : 47];
+    r.e0 = p[96];
+    r.e1 = p[97];
+    r.e2 = p[98];
+    return r;
+}
+
+// The table kernel's keys of round t = lane.  The schedule's words are masks the
+// halves carry (keysched_core.h).  Word 2t holds the change of the mask of the
+// half that round t updates, so the mask a half has when round t reads it is the
+// XOR of its changes so far, and of the extra words.  In the order of the right
+// half's bits that mask is the key at every word's primary expansion position;
+// word 2t + 1 holds what its second uses differ by.
+__device__ __forceinline__ uint4 make_row(const RowWords &r, uint32_t lane) {
+    const bool dx = bs_dest_is_x((int)lane);
+    uint32_t x = lane < 48 && dx ? r.w.x : 0u, y = lane < 48 && !dx ? r.w.x : 0u;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const uint32_t ux = __shfl_up(x, d, kWave), uy = __shfl_up(y, d, kWave);
+        if ((int)lane >= d) {
+            x ^= ux;
+            y ^= uy;
+        }
+    }
+    // (round t's own change is in the half it updates, not the one it reads)
+    const uint32_t c = dx ? y : x;
+    uint32_t p = __builtin_bitreverse32(dx ? r.e0 ^ (lane >= 32 ? r.e2 : 0u) : lane >= 16 ? r.e1 : 0u);
+#pragma unroll
+    for (int o = 0; o < 32; o++) p ^= ((c >> o) & 1u) << (31 - kBsOutWord[o]);
+    uint32_t odd = p, even = p, w06 = p, w7 = p;
+#pragma unroll
+    for (int k = 0; k < 16; k++) {
+        const int s = kBsDupE[k] / 6;
+        const uint32_t b = ((r.w.y >> k) & 1u) << (31 - kBsESrc[kBsDupE[k]]);
+        if (s == 7) w7 ^= b;
+        else if (s == 0 || s == 6) w06 ^= b;
+        else if (s & 1) odd ^= b;
+        else even ^= b;
+    }
+    return make_uint4(odd, even, rotl(w06, 12), rotl(w7, 12));
+}
+
+// Exclusive prefix of v over the workgroup's threads; *sum its total.  A barrier
+// comes before sums (one word per wave) may be used again.
+__device__ __forceinline__ uint32_t block_prefix(uint32_t v, uint32_t *sums, uint32_t *sum) {
+    const uint32_t lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const uint32_t incl = (uint32_t)wave_scan(v, (int)lane);
+    if (lane == kWave - 1) sums[wave] = incl;
+    __syncthreads();
+    uint32_t before = 0, s = 0;
+    for (uint32_t w = 0; w < kWaves; w++) {
+        before += w < wave ? sums[w] : 0u;
+        s += sums[w];
+    }
+    *sum = s;
+    return before + incl - v;
+}
+
+// SCAN: the workgroup scans the descriptors itself (n <= kTableScanMax);
+// otherwise ws holds their scan.
+template <bool SCAN>
+__global__ __launch_bounds__(kThreads) void batch_table_kernel(const tdes_msg *__restrict__ msgs,
+                                                              uint32_t n,
+                                                              const uint32_t *__restrict__ sched,
+                                                              uint32_t n_sched, const uint8_t *in,
+                                                              uint8_t *out, BatchBounds bb,
+                                                              uint64_t *ws, uint64_t *skipped_out,
+                                                              uint32_t per) {
+    __shared__ __align__(16) uint32_t table[kTableWords];
+    __shared__ uint4 rows[kRows * kRowStride];
+    // SCAN: first block of every message (entries past the last: the total).
+    // Else first slices of the 1,024 messages after the step's first one, from
+    // the step's first slice on.
+    __shared__ uint32_t start[SCAN ? kTableScanMax : kThreads];
+    __shared__ uint32_t sums[2][kWaves], span[2];
+    const uint32_t tid = threadIdx.x, lane = tid % kWave;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    uint64_t *first = ws + kWsHeader;
+    uint32_t grid = gridDim.x;
+    uint64_t total;  // blocks, or the lanes of all slices
+    if (SCAN) {
+        static_assert(kTableScanMax == 2 * kThreads, "two descriptors a thread");
+        // (a message is no longer than out_bytes, which batch_is_table bounds
+        // for so few messages: the sums fit 32 bits)
+        uint32_t v[2], u[2], bad = 0;
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+            const uint32_t i = 2 * tid + k;
+            bool b = false;
+            v[k] = (uint32_t)units_of(msgs[i < n ? i : n - 1], n_sched, bb, 8, &b);
+            v[k] = i < n ? v[k] : 0u;
+            u[k] = (v[k] + kSlice / 8 - 1) / (kSlice / 8);
+            bad += i < n && b;
+        }
+        uint32_t sum;
+        if (blockIdx.x == --grid) {
+            // the last workgroup: the workspace's table, as the scan launches
+            // leave it, and the skipped count
+            uint32_t skipped;
+            block_prefix(bad, sums[0], &skipped);
+            const uint32_t f = block_prefix(u[0] + u[1], sums[1], &sum);
+            if (2 * tid < n) first[2 * tid] = f;
+            if (2 * tid + 1 < n) first[2 * tid + 1] = f + u[0];
+            if (tid == 0) {
+                ws[0] = first[n] = sum;
+                ws[1] = skipped;
+                if (skipped_out != nullptr) *skipped_out = skipped;
+            }
+            return;
+        }
+        fill_tables(table);
+        const uint32_t f = block_prefix(v[0] + v[1], sums[0], &sum);
+        start[2 * tid] = f;
+        start[2 * tid + 1] = f + v[0];
+        total = sum;
+        __syncthreads();
+    } else {
+        fill_tables(table);
+        total = ws[0] * (kSlice / 8);
+    }
+
+    const uint8_t *sp = reinterpret_cast<const uint8_t *>(table);
+    const uint32_t mask = in_vgpr(kIndexMask);
+    for (uint64_t base = (uint64_t)blockIdx.x * per; base < total; base += (uint64_t)grid * per) {
+        const uint32_t here = (uint32_t)min((uint64_t)per, total - base);  // lanes of this step
+        // this lane's message, and its block's place there
+        uint32_t m = 0;
+        uint64_t at = 0;
+        bool active = tid < here;
+        if (SCAN) {
+            const uint32_t b = (uint32_t)base + tid;
+#pragma unroll
+            for (uint32_t step = kTableScanMax / 2; step >= 1; step /= 2)
+                if (m + step < n && start[m + step] <= b) m += step;
+            at = b - start[m];
+        } else {
+            const uint64_t s0 = base / (kSlice / 8);
+            const uint32_t s = tid / (kSlice / 8);
+            const uint32_t m0 = find_message(first, n, s0, lane);
+            const uint64_t i = (uint64_t)m0 + 1 + tid;
+            const uint64_t rel = i <= n ? first[i] - s0 : ~0ull;
+            start[tid] = rel < ~0u ? (uint32_t)rel : ~0u;
+            __syncthreads();
+            uint32_t r = 0;  // messages that start at or before this lane's slice
+#pragma unroll
+            for (uint32_t step = kThreads / 2; step >= 1; step /= 2)
+                if (start[r + step - 1] <= s) r += step;
+            if (start[r] <= s) r++;
+            m = m0 + (active ? r : 0u);
+            if (active) {
+                while (first[m + 1] <= s0 + s) m++;  // past 1,024 messages: many empty ones
+                at = (s0 + s - first[m]) * (kSlice / 8) + tid % (kSlice / 8);
+            }
+        }
+        if (tid == 0) span[0] = m;
+        if (tid == here - 1) span[1] = m;
+        uint2 w[1] = {};
+        uint8_t *dst = nullptr;
+        if (active) {
+            const tdes_msg d = msgs[m];
+            if (!SCAN) active = at < d.nbytes / 8;  // (a message's last slice may be partial)
+            if (active) {
+                w[0] = *reinterpret_cast<const uint2 *>(in + d.in_off + 8 * at);
+                dst = out + d.out_off + 8 * at;
+            }
+        }
+        __syncthreads();
+        const uint32_t m_lo = __builtin_amdgcn_readfirstlane(span[0]);
+        const uint32_t m_hi = __builtin_amdgcn_readfirstlane(span[1]);
+        // kRows messages at a time: their rows, then their lanes' blocks
+        for (uint32_t g = m_lo; g <= m_hi; g += kRows) {
+            RowWords rw[kRowsPerWave];
+#pragma unroll
+            for (int k = 0; k < kRowsPerWave; k++)
+                rw[k] = load_row(msgs[min(g + wave + k * kWaves, m_hi)], sched, n_sched, lane);
+#pragma unroll
+            for (int k = 0; k < kRowsPerWave; k++) {
+                const uint32_t j = wave + k * kWaves;
+                if (g + j > m_hi) break;
+                const uint4 row = make_row(rw[k], lane);
+                if (lane < 48) rows[j * kRowStride + lane] = row;
+            }
+            __syncthreads();
+            if (active && m - g < kRows) {
+                cipher_blocks<1>(w, sp, (lane % kCopies) * 4u, mask, rows + (m - g) * kRowStride);
+                *reinterpret_cast<uint2 *>(dst) = w[0];
+            }
+            __syncthreads();
+        }
+    }
+}
+
+}  // namespace
+
+bool batch_is_table(size_t n_msgs, uint64_t out_bytes) {
+    // Small batches: 300 messages in 2 MB 16 us against 45 on the bitsliced
+    // kernel, in 6 MB 39 against 44 (256 CUs); 1,000 in 10 MB 62 against 48.
+    // Small messages, which give a bitsliced wave several passes: 4,000 of
+    // 2,000 bytes 72 against 85 us, 16,000 of 1,024 bytes 127 against 145, of
+    // 1,500 bytes 173 against 132.  (out_bytes / n_msgs is their mean length or
+    // more.)
+    const uint64_t small = spbox_one_pass_bytes() / 2 * 3;
+    return out_bytes <= small || (out_bytes <= 2 * small && out_bytes / 2048 <= n_msgs) ||
+           out_bytes / 1024 <= n_msgs;
+}
+
+hipError_t launch_batch_table(const tdes_msg *msgs, size_t n_msgs, const uint32_t *schedules,
+                              size_t n_schedules, const uint8_t *in, uint8_t *out, BatchBounds bb,
+                              uint64_t *ws, uint64_t *skipped_out, hipStream_t stream) {
+    // Lanes per workgroup and step: the fewest that cover out_bytes with one
+    // workgroup a CU, but, where lanes go by blocks, no more than kRows messages
+    // of the batch's mean length hold (each kRows messages more cost a pass).
+    // Outputs do not overlap, so out_bytes bounds the work; any grid is correct.
+    const bool scan = n_msgs <= kTableScanMax;
+    const uint64_t cus = device_cus();
+    const uint64_t work = bb.out_bytes / 8 + (scan ? 0 : n_msgs * (kSlice / 8));
+    const uint64_t fit = scan ? bb.out_bytes / 8 * kRows / n_msgs : kThreads;
+    uint32_t per = 64;
+    while (per < (uint32_t)kThreads && (work + per - 1) / per > cus && 2 * per <= fit) per *= 2;
+    uint64_t grid = (work + per - 1) / per;
+    grid = grid < 1 ? 1 : grid > cus ? cus : grid;
+    if (scan)
+        hipLaunchKernelGGL(batch_table_kernel<true>, dim3((unsigned)grid + 1), dim3(kThreads), 0, stream,
+                           msgs, (uint32_t)n_msgs, schedules, (uint32_t)n_schedules, in, out, bb, ws,
+                           skipped_out, per);
+    else
+        hipLaunchKernelGGL(batch_table_kernel<false>, dim3((unsigned)grid), dim3(kThreads), 0, stream,
+                           msgs, (uint32_t)n_msgs, schedules, (uint32_t)n_schedules, in, out, bb, ws,
+                           skipped_out, per);
+    return hipGetLastError();
+}
+
+}  // namespace tdes
