@@ -283,9 +283,9 @@ tdes_status tdes_ecb_host(const tdes_schedule *ks, int dir, const void *h_in, vo
 /* Configuration of the batched kernel: which compiled variant runs and on
  * how large a grid.  None of it changes results, only speed. */
 typedef struct {
-    uint32_t kmax;      /* messages per wave pass whose key masks share one LDS
-                           table (4, 8 or 16; a wave over more messages takes
-                           one pass per group)                              */
+    uint32_t kmax;      /* most messages of a wave whose key masks share one LDS
+                           table (4, 8 or 16; in a wave over more messages the
+                           lanes make their own)                            */
     uint32_t waves;     /* waves per SIMD the variant's register budget is
                            set for.  Compiled: {4, 8} x {3, 4, 5} and
                            {16, 3}                                          */

@@ -9,12 +9,12 @@
 // finds its message (a 64-way search for the message of the wave's first
 // slice, then a shuffle search over the next 64 message starts), loads its
 // 256 bytes, and runs the same bitsliced core as the plain kernel.  The key
-// masks: a wave's 64 slices lie in a run of consecutive messages; the wave
-// expands the masks of up to KMAX of them together, one round ahead, into a
-// table in LDS (one row per message and round, in the plain kernel's
-// layout), and each lane reads its own message's row with the plain
-// kernel's piped LDS reads.  A wave spanning more messages takes one pass
-// per group of KMAX.
+// masks: a wave's 64 slices lie in a run of consecutive messages; where there
+// are at most KMAX of them the wave expands their masks together, one round
+// ahead, into a table in LDS (one row per message and round, in the plain
+// kernel's layout), and each lane reads its own message's row with the plain
+// kernel's piped LDS reads.  In a wave over more messages each lane widens its
+// own message's key words, one S-box ahead.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -28,7 +28,7 @@
 #include "lds_masks.h"
 
 // The compiled variants of the batched cipher, X(KMAX, WAVES): KMAX
-// messages per wave pass share the LDS mask table; WAVES waves per SIMD is
+// messages of a wave share the LDS mask table; WAVES waves per SIMD is
 // the occupancy the register budget is set for (KMAX 16 does not fit 4).  The first is the default
 // (with a grid of twice the resident workgroups); tdes_batch_autotune picks
 // among all of them and grids of 1..4 times the resident workgroups.
@@ -178,8 +178,8 @@ __global__ __launch_bounds__(kScanThreads) void batch_tile_finish_kernel(size_t 
 // Key masks of the messages a wave works on, expanded cooperatively into a
 // table in LDS one round ahead of use (in place of each lane expanding its
 // own 48 masks per round).  The wave's lanes hold consecutive slices, so a
-// wave spans a run of consecutive messages; up to KMAX of them (a group) are
-// handled per pass.  Table of one wave: 2 round buffers x KMAX rows x
+// wave spans a run of consecutive messages; the table serves waves over up to
+// KMAX of them.  Table of one wave: 2 round buffers x KMAX rows x
 // kRowWords words; a row holds one message's 64 masks of one round in the
 // plain kernel's layout (box j at 8 j: output masks o[0..3], second-use
 // masks e[0..3]), padded so that the rows of different messages start on
@@ -211,7 +211,6 @@ struct TableRounds {
     uint32_t sel;         // byte address (for ds_bpermute) of the lane holding this lane's word
                           // of message 0 (+ 8 j for message j)
     uint32_t bit;         // bit of that word this lane expands
-    uint32_t kg;          // messages in the group (uniform, 1..KMAX)
     BsBoxMasks pm[8];
 
     static constexpr int kBuf = KMAX * kRowWords;  // words per round buffer
@@ -221,8 +220,8 @@ struct TableRounds {
                                                    (woff + 8u * (uint32_t)t));
     }
     // message J's masks of the round whose words are in wcur, into buffer B.
-    // Every row is written, also those of messages past the group (lanes
-    // past 2 kg hold copies of the last message's words): the round body
+    // Every row is written, also those past the wave's messages (the lanes
+    // past them hold copies of the last message's words): the round body
     // must stay free of branches, or the compiler hoists all eight S-boxes'
     // mask reads to the top of the round loop and runs out of registers.
     // (sl: sel, made opaque each round so that sel + 8 j is computed here
@@ -295,6 +294,56 @@ struct TableRounds {
     }
 };
 
+// Key masks of a wave over more than KMAX messages: every lane widens the bits
+// of its own message's two key words of a round, 48 v_bfe_i32 a round (which do
+// not pair) in place of the table's rows.  It replaces one pass of the rounds per
+// KMAX messages, 8 where every lane holds its own (us a submit, passes -> this:
+// 2,000 messages of 72 bytes 299 -> 41, 4,000 of 1,000 bytes 120 -> 41, 16,000 of
+// 2 KiB 139 -> 91, 16,384 log-normal around 4 KiB 160 -> 157).
+struct LaneWords {  // a round's key words and the place (8 a box) of the masks meant
+    uint2 w;
+    int at;
+    __device__ __forceinline__ LaneWords operator+(int k) const { return LaneWords{w, at + k}; }
+};
+struct LaneMasks {
+    // (p.at and n are constants after inlining)
+    __device__ __forceinline__ void operator()(BsBoxMasks &m, LaneWords p, int n) const {
+        const int j = p.at / kBsBoxMasks;
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+            m.o[q] = (uint32_t)__builtin_amdgcn_sbfe((int)p.w.x, (uint32_t)(4 * j + q), 1);
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+            if (i < n)
+                m.e[i] = (uint32_t)__builtin_amdgcn_sbfe((int)p.w.y, (uint32_t)kBsBoxDup[4 * j + i], 1);
+    }
+};
+struct LaneRounds {
+    const uint32_t *words;  // the lane's message: the 100 words of its direction
+    uint2 cur, next;        // key words of this round and the next
+    BsBoxMasks pm[8];
+    __device__ __forceinline__ uint2 load(int t) const {
+        return *reinterpret_cast<const uint2 *>(words + 2 * t);
+    }
+    __device__ __forceinline__ void start() {
+        cur = load(0);
+        next = load(1);
+        LaneMasks{}(pm[0], LaneWords{cur, 0}, BS_BOX_NDUP[0]);
+    }
+    template <int PH>
+    __device__ __forceinline__ void round(uint32_t (&d)[32], const uint32_t (&r)[32], int t) {
+        const uint2 after = load(t + 2);  // past round 47: the extra words, not used
+        bs_round_piped<1>(d, r, LaneWords{cur, 0}, LaneWords{next, 0}, pm, LaneMasks{});
+        cur = next;
+        next = after;
+    }
+    __device__ __forceinline__ void extra(int g, uint32_t (&a)[32]) const {
+        const uint32_t w = words[96 + g];
+#pragma unroll
+        for (int i = 0; i < 32; i++) a[i] ^= (uint32_t)__builtin_amdgcn_sbfe((int)w, (uint32_t)i, 1);
+    }
+};
+
 // A lane's slice between the lookup and the cipher phases of a pass: kept in
 // LDS (volatile, so the compiler cannot forward it in registers), so that
 // nothing of the lookup stays in registers through the rounds.
@@ -306,7 +355,8 @@ struct TableRounds {
 struct LaneSlice {
     uint64_t src, dst;  // device addresses of the lane's run (its message's bytes in this wave)
     uint32_t nb;        // bytes of the run (0: no work for this lane)
-    uint32_t row;       // this lane's row of the mask table
+    uint32_t row;       // this lane's row of the mask table, or in a wave over more
+                        // messages the place of its key words in the schedules
     uint32_t pos;       // byte offset of this lane's first piece in the run: 16 i
     uint32_t stride;    // bytes between its pieces: 16 L
 };
@@ -321,18 +371,13 @@ typedef __attribute__((address_space(1))) v4u_a8 g_u4;
 typedef __attribute__((address_space(1))) const v2u g_cu2;
 typedef __attribute__((address_space(1))) v2u g_u2;
 
-// Messages per mask-table group for a wave spanning n messages: a table of
-// 4 rows if they fit, else of KMAX rows (one pass if they fit; a
-// table builds every one of its rows each round, so fewer rows cost less),
-// else KMAX rows and one pass per KMAX messages.  Most waves of a batch of
+// Rows of the mask table for a wave over n messages: 4 if they fit, else KMAX (a
+// table builds every one of its rows each round, so fewer rows cost less); 0 for
+// more than KMAX messages, which take no table.  Most waves of a batch of
 // kilobyte messages span 2 to 5 of them.
-#ifndef TDES_BATCH_ADAPT
-#define TDES_BATCH_ADAPT 1
-#endif
 template <int KMAX>
-__device__ __forceinline__ uint32_t group_rows(uint32_t n) {
-    if (TDES_BATCH_ADAPT && KMAX > 4 && n <= 4) return 4;
-    return KMAX;
+__device__ __forceinline__ uint32_t table_rows(uint32_t n) {
+    return n <= 4 ? 4 : n <= KMAX ? KMAX : 0;
 }
 
 template <int KMAX, int WAVES>
@@ -350,10 +395,8 @@ void batch_bitslice_kernel(const tdes_msg *__restrict__ msgs, uint32_t n_msgs,
     const uint64_t stride = (uint64_t)gridDim.x * kThreads;
     for (uint64_t base = ((uint64_t)blockIdx.x * kWavesPerBlock + wave) * kWave; base < total;
          base += stride) {
-        // Passes over groups of G consecutive messages of the wave: one pass
-        // unless the wave's 64 slices span more than KMAX messages.
-        uint32_t g0 = 0, n_wave_msgs = 1, G = KMAX;
-        do {
+        uint32_t K;  // rows of the mask table (0: lanes widen their own masks)
+        {
             // Issue priority: the message lookup, loads and input transposes
             // at the highest, the rounds at the lowest, so a wave that has
             // just started reaches its rounds sooner.
@@ -383,10 +426,8 @@ void batch_bitslice_kernel(const tdes_msg *__restrict__ msgs, uint32_t n_msgs,
                 // last active lane the last); this lane's is number m - lo.
                 const uint64_t left = total - base;
                 const int last = left > (uint64_t)kWave ? kWave - 1 : (int)left - 1;
-                n_wave_msgs = (uint32_t)__builtin_amdgcn_readlane((int)m, last) - lo + 1;
-                G = group_rows<KMAX>(n_wave_msgs);
-                const uint32_t slot = m - lo;
-                const bool mine = active && slot - g0 < G;
+                const uint32_t n_wave_msgs = (uint32_t)__builtin_amdgcn_readlane((int)m, last) - lo + 1;
+                K = table_rows<KMAX>(n_wave_msgs);
                 const tdes_msg d = msgs[m];
                 // this lane's run: the slices of message m in this wave
                 const uint64_t f0 = first[m], f1 = first[m + 1];
@@ -397,24 +438,22 @@ void batch_bitslice_kernel(const tdes_msg *__restrict__ msgs, uint32_t n_msgs,
                 const uint64_t rem = d.nbytes - run_off;
                 *(lds_vu64 *)&mine_ls->src = (uint64_t)(uintptr_t)(in + d.in_off + run_off);
                 *(lds_vu64 *)&mine_ls->dst = (uint64_t)(uintptr_t)(out + d.out_off + run_off);
-                *(lds_vu32 *)&mine_ls->nb = mine ? (uint32_t)(rem < run_len ? rem : run_len) : 0u;
+                *(lds_vu32 *)&mine_ls->nb = active ? (uint32_t)(rem < run_len ? rem : run_len) : 0u;
                 *(lds_vu32 *)&mine_ls->pos = (uint32_t)(s - run0) * 16u;
                 *(lds_vu32 *)&mine_ls->stride = (uint32_t)(run1 - run0) * 16u;
-                *(lds_vu32 *)&mine_ls->row = (slot - g0) & (G - 1);  // (any row for other groups)
+                auto words_of = [&](const tdes_msg &q) {
+                    return (q.sched_idx < n_sched ? q.sched_idx : 0u) * (uint32_t)kDeviceScheduleWords +
+                           (q.dir & 1u) * (uint32_t)kDirWords;
+                };
+                *(lds_vu32 *)&mine_ls->row = K != 0 ? m - lo : words_of(d);
                 // lanes 2j, 2j + 1: the two key words of round 0 of the
-                // group's message j (the last one for lanes past the group)
-                const uint32_t kg = min(n_wave_msgs - g0, G);
-                const tdes_msg dj = msgs[lo + g0 + min(lane >> 1, kg - 1)];
-                woff = 4u * ((dj.sched_idx < n_sched ? dj.sched_idx : 0u) *
-                                 (uint32_t)kDeviceScheduleWords +
-                             (dj.dir & 1u) * (uint32_t)kDirWords + (lane & 1u));
-                if (__ballot(mine) == 0) continue;  // a group of empty messages
+                // wave's message j (the last one for lanes past them)
+                woff = 4u * (words_of(msgs[lo + min(lane >> 1, n_wave_msgs - 1)]) + (lane & 1u));
             }
-            // load, transposes, the 48 rounds with a table of K rows (K
-            // uniform over the wave), transposes, store: one copy per table
-            // size, so that nothing but a few scalars is live across the choice
-            auto cipher = [&](auto k_rows) {
-                constexpr int K = decltype(k_rows)::value;
+            // load, transposes, the 48 rounds run by what runner() returns,
+            // transposes, store: one copy per kind of rounds (uniform over the
+            // wave), so that nothing but a few scalars is live across the choice
+            auto cipher = [&](auto runner) {
                 uint32_t h0[32], h1[32];
                 {
                     // the run's piece k for this lane, at min(pos + k stride,
@@ -444,19 +483,7 @@ void batch_bitslice_kernel(const tdes_msg *__restrict__ msgs, uint32_t n_msgs,
                         h1[0] = v[1];
                     }
                 }
-                TableRounds<K, (WAVES >= 5 ? 1 : TDES_BS_PIPE)> rr;
-                rr.kg = min(n_wave_msgs - g0, (uint32_t)K);
-                rr.sched = sched;
-                rr.woff = woff;
-                {
-                    // entry `lane` of a row: bit eb of the round's word pair
-                    // (lo, hi as bits 32..63), found in lane 2j (lo) or 2j + 1 (hi)
-                    const uint32_t eb = row_entry_bit((int)lane);
-                    rr.sel = 4u * (eb >> 5);
-                    rr.bit = eb & 31u;
-                }
-                rr.wr = (lds_u32 *)tables[wave] + lane;
-                rr.p0 = (const lds_u32 *)tables[wave] + *(lds_vu32 *)&mine_ls->row * kRowWords;
+                auto rr = runner();
                 transpose32(h0);
                 __builtin_amdgcn_sched_barrier(0);
                 transpose32(h1);
@@ -488,11 +515,32 @@ void batch_bitslice_kernel(const tdes_msg *__restrict__ msgs, uint32_t n_msgs,
                     }
                 }
             };
-            if (KMAX > 4 && G == 4)
-                cipher(std::integral_constant<int, (KMAX > 4 ? 4 : KMAX)>{});
+            auto table = [&](auto k_rows) {
+                return [&] {
+                    TableRounds<decltype(k_rows)::value, (WAVES >= 5 ? 1 : TDES_BS_PIPE)> rr;
+                    rr.sched = sched;
+                    rr.woff = woff;
+                    // entry `lane` of a row: bit eb of the round's word pair
+                    // (lo, hi as bits 32..63), found in lane 2j (lo) or 2j + 1 (hi)
+                    const uint32_t eb = row_entry_bit((int)lane);
+                    rr.sel = 4u * (eb >> 5);
+                    rr.bit = eb & 31u;
+                    rr.wr = (lds_u32 *)tables[wave] + lane;
+                    rr.p0 = (const lds_u32 *)tables[wave] + *(lds_vu32 *)&mine_ls->row * kRowWords;
+                    return rr;
+                };
+            };
+            if (K == 0)
+                cipher([&] {
+                    LaneRounds rr;
+                    rr.words = sched + *(lds_vu32 *)&mine_ls->row;
+                    return rr;
+                });
+            else if (KMAX > 4 && K == 4)
+                cipher(table(std::integral_constant<int, (KMAX > 4 ? 4 : KMAX)>{}));
             else
-                cipher(std::integral_constant<int, KMAX>{});
-        } while ((g0 += G) < n_wave_msgs);
+                cipher(table(std::integral_constant<int, KMAX>{}));
+        }
     }
 }
 
@@ -648,8 +696,11 @@ hipError_t launch_expand(const uint8_t *keys24, size_t n, uint32_t *schedules, h
 }
 
 hipError_t launch_batch_prefixed(const tdes_msg *msgs, size_t n_msgs, const uint32_t *schedules,
-                                 size_t n_schedules, const uint8_t *in, uint8_t *out,
-                                 const uint64_t *ws, uint64_t total_slices, hipStream_t stream) {
+                                 size_t n_schedules, const uint8_t *in, uint8_t *out, uint64_t *ws,
+                                 uint64_t total_slices, uint64_t total_bytes, hipStream_t stream) {
+    if (n_msgs <= kTableScanMax && batch_is_table(n_msgs, total_bytes))
+        return launch_batch_table(msgs, n_msgs, schedules, n_schedules, in, out,
+                                  BatchBounds{~0ull, ~0ull}, total_bytes, ws, nullptr, stream);
     // a workgroup's waves take kWave consecutive slices each per step
     const uint64_t per_block = (uint64_t)kWave * kWavesPerBlock;
     const uint64_t need = total_slices == 0 ? 1 : (total_slices + per_block - 1) / per_block;
@@ -794,6 +845,7 @@ hipError_t launch_batch(const tdes_msg *msgs, size_t n_msgs, const uint32_t *sch
                         uint64_t out_bytes, uint64_t *ws, uint64_t *skipped_out,
                         hipStream_t stream) {
     const BatchBounds bb{in_bytes, out_bytes};
+    // (outputs do not overlap, so out_bytes bounds the batch's bytes)
     if (!batch_is_table(n_msgs, out_bytes))
         return launch_batch_bitslice(msgs, n_msgs, schedules, n_schedules, in, in_bytes, out,
                                      out_bytes, ws, skipped_out, stream);
@@ -801,7 +853,8 @@ hipError_t launch_batch(const tdes_msg *msgs, size_t n_msgs, const uint32_t *sch
         const hipError_t e = launch_scan(msgs, n_msgs, n_schedules, bb, ws, skipped_out, stream);
         if (e != hipSuccess) return e;
     }
-    return launch_batch_table(msgs, n_msgs, schedules, n_schedules, in, out, bb, ws, skipped_out, stream);
+    return launch_batch_table(msgs, n_msgs, schedules, n_schedules, in, out, bb, out_bytes, ws,
+                              skipped_out, stream);
 }
 
 }  // namespace tdes

@@ -65,12 +65,14 @@ __device__ __forceinline__ uint32_t find_message(const uint64_t *first, uint32_t
 
 // Most messages the batched table kernel scans by itself.
 constexpr uint32_t kTableScanMax = 2048;
-// Whether a batch of n_msgs messages into out_bytes runs on the table kernel.
-bool batch_is_table(size_t n_msgs, uint64_t out_bytes);
+// Whether a batch of n_msgs messages with at most work_bytes in all runs on the
+// table kernel.
+bool batch_is_table(size_t n_msgs, uint64_t work_bytes);
 // The batched table kernel.  For more than kTableScanMax messages ws holds the
-// descriptor scan; for fewer the kernel makes it.
+// descriptor scan; for fewer the kernel makes it.  work_bytes sizes the grid.
 hipError_t launch_batch_table(const tdes_msg *msgs, size_t n_msgs, const uint32_t *schedules,
                               size_t n_schedules, const uint8_t *in, uint8_t *out, BatchBounds bb,
-                              uint64_t *ws, uint64_t *skipped_out, hipStream_t stream);
+                              uint64_t work_bytes, uint64_t *ws, uint64_t *skipped_out,
+                              hipStream_t stream);
 
 }  // namespace tdes

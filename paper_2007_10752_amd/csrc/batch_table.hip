@@ -1,11 +1,9 @@
-// Batched 3DES-EDE ECB on the table kernel: small batches, and batches of small
-// messages.
+// Batched 3DES-EDE ECB on the table kernel, for small batches.
 //
 // One block per lane (spbox.hip), the blocks of all messages in a row, `per`
-// lanes of them to a workgroup and step.  The bitsliced batch kernel (batch.hip) gives a
-// message at least one lane of 32 blocks and a wave one pass per 4 to 16
-// messages, each pass 48 rounds of some 240 instructions: ~40 us for the
-// smallest batch, and a wave of 64 messages of 256 bytes or less takes 8 passes.
+// lanes of them to a workgroup and step.  The lanes of the bitsliced batch
+// kernel (batch.hip) take 32 blocks each through the rounds, ~40 us for the
+// smallest batch.
 //
 // A workgroup has a CU to itself: 64 KiB of tables, the round keys of up to
 // kRows messages (a row each, 784 bytes, padded so that the rows of different
@@ -19,8 +17,8 @@
 // Bound by the latency of its steps (descriptors, schedules, tables, one block's
 // 48 rounds), which a workgroup goes through one after the other: ~10 us for the
 // smallest batch, 150 GB/s on large ones.  Measured (us a submit, bitsliced ->
-// table): 16 messages of 4 KiB 43.5 -> 9.7, 300 of 6.7 KB 45 -> 16, 2,000 of
-// 72 bytes 299 -> 12, 16,000 of 256 bytes 265 -> 53.
+// table): 16 messages of 4 KiB 41 -> 9.7, 300 of 6.7 KB 43 -> 16, 2,000 of 72
+// bytes 41 -> 12.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -133,8 +131,8 @@ __global__ __launch_bounds__(kThreads) void batch_table_kernel(const tdes_msg *_
     uint64_t total;  // blocks, or the lanes of all slices
     if (SCAN) {
         static_assert(kTableScanMax == 2 * kThreads, "two descriptors a thread");
-        // (a message is no longer than out_bytes, which batch_is_table bounds
-        // for so few messages: the sums fit 32 bits)
+        // (batch_is_table bounds the work of so few messages, and a message is no
+        // longer than that where outputs overlap: the sums fit 32 bits)
         uint32_t v[2], u[2], bad = 0;
 #pragma unroll
         for (int k = 0; k < 2; k++) {
@@ -245,29 +243,28 @@ __global__ __launch_bounds__(kThreads) void batch_table_kernel(const tdes_msg *_
 
 }  // namespace
 
-bool batch_is_table(size_t n_msgs, uint64_t out_bytes) {
-    // Small batches: 300 messages in 2 MB 16 us against 45 on the bitsliced
-    // kernel, in 6 MB 39 against 44 (256 CUs); 1,000 in 10 MB 62 against 48.
-    // Small messages, which give a bitsliced wave several passes: 4,000 of
-    // 2,000 bytes 72 against 85 us, 16,000 of 1,024 bytes 127 against 145, of
-    // 1,500 bytes 173 against 132.  (out_bytes / n_msgs is their mean length or
-    // more.)
-    const uint64_t small = spbox_one_pass_bytes() / 2 * 3;
-    return out_bytes <= small || (out_bytes <= 2 * small && out_bytes / 2048 <= n_msgs) ||
-           out_bytes / 1024 <= n_msgs;
+bool batch_is_table(size_t n_msgs, uint64_t work_bytes) {
+    // us a submit, this kernel against the bitsliced one (256 CUs, one launch up
+    // to kTableScanMax messages): 300 messages in 2 MB 16 to 43, in 6 MB 39 to
+    // 42; 1,000 in 6.5 MB 49 to 45.  Three launches, lanes by slices: 4,000 in
+    // 1 MB 24 to 41, in 4 MB 48 to 41; 16,000 in 1.2 MB 39 to 42, in 4.2 MB 53
+    // to 43.
+    if (n_msgs <= kTableScanMax) return work_bytes <= spbox_one_pass_bytes() / 2 * 3;
+    return work_bytes + kSlice * (uint64_t)n_msgs <= spbox_one_pass_bytes();
 }
 
 hipError_t launch_batch_table(const tdes_msg *msgs, size_t n_msgs, const uint32_t *schedules,
                               size_t n_schedules, const uint8_t *in, uint8_t *out, BatchBounds bb,
-                              uint64_t *ws, uint64_t *skipped_out, hipStream_t stream) {
-    // Lanes per workgroup and step: the fewest that cover out_bytes with one
+                              uint64_t work_bytes, uint64_t *ws, uint64_t *skipped_out,
+                              hipStream_t stream) {
+    // Lanes per workgroup and step: the fewest that cover the work with one
     // workgroup a CU, but, where lanes go by blocks, no more than kRows messages
     // of the batch's mean length hold (each kRows messages more cost a pass).
-    // Outputs do not overlap, so out_bytes bounds the work; any grid is correct.
+    // Any grid is correct.
     const bool scan = n_msgs <= kTableScanMax;
     const uint64_t cus = device_cus();
-    const uint64_t work = bb.out_bytes / 8 + (scan ? 0 : n_msgs * (kSlice / 8));
-    const uint64_t fit = scan ? bb.out_bytes / 8 * kRows / n_msgs : kThreads;
+    const uint64_t work = work_bytes / 8 + (scan ? 0 : n_msgs * (kSlice / 8));
+    const uint64_t fit = scan ? work_bytes / 8 * kRows / n_msgs : kThreads;
     uint32_t per = 64;
     while (per < (uint32_t)kThreads && (work + per - 1) / per > cus && 2 * per <= fit) per *= 2;
     uint64_t grid = (work + per - 1) / per;

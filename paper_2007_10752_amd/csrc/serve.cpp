@@ -314,7 +314,7 @@ tdes_status launch_slot(tdes_server *s, Slot &sl) {
         e = tdes::launch_batch_prefixed(
             reinterpret_cast<const tdes_msg *>(sl.d_stage + lay.msgs_off), n, sl.d_sched, n,
             nullptr, static_cast<uint8_t *>(s->cfg.d_arena),
-            reinterpret_cast<const uint64_t *>(sl.d_stage + lay.ws_off), total, sl.stream);
+            reinterpret_cast<uint64_t *>(sl.d_stage + lay.ws_off), total, batch_bytes, sl.stream);
     if (e == hipSuccess) e = hipEventRecord(sl.done, sl.stream);
     return e == hipSuccess ? TDES_OK : fail(TDES_ERR_DEVICE, hipGetErrorString(e));
 }
