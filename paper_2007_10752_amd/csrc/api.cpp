@@ -86,7 +86,7 @@ int tdes::auto_kernel(size_t nbytes) {
 
 bool tdes::auto_is_table(size_t nbytes) {
     // The table kernel as long as its workgroups have a CU each (2 MiB on 256
-    // CUs): one lane's 48 rounds on one block, 6-11 us a launch against 15 for
+    // CUs): one lane's 48 rounds on one block, 4-11 us a launch against 15 for
     // the bitsliced kernel with its S-boxes split over waves.  Two workgroups
     // share a CU's LDS beyond: 17.8 against 15.4 us at 3 MiB.
     return nbytes <= spbox_one_pass_bytes() / 2;

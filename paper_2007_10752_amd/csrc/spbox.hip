@@ -29,10 +29,11 @@
 // IP and FP run once per block as delta swaps; the three DES passes are
 // fused as in the bitsliced kernel (FP then IP cancel between passes).
 //
-// The modes are those of bitslice.hip.  Small inputs are bound by one lane's
-// chain of rounds (203 clocks each; the table fill takes ~2,100), large ones
-// by LDS and VALU issue together.  CTR and CBC decryption of 64 KiB run 6.5 us
-// a launch here, 14.7 on the split bitsliced kernel, 31 on the plain one.
+// The modes are those of bitslice.hip.  Inputs of a block per lane are bound by
+// one lane's chain of rounds (203 clocks each; the table fill takes ~2,100),
+// large ones by LDS and VALU issue together.  CTR and CBC decryption of 1 MiB
+// run 7.5 us a launch here, 14.8 on the split bitsliced kernel, 31 on the plain
+// one.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -121,6 +122,84 @@ __global__ __launch_bounds__(kThreads) void tdes_spbox_kernel(const uint8_t *in,
     for (; b + stride < nblocks; b += 2 * stride)
         blocks<2, MODE>(in, out, mode, b, stride, sp, lane, mask, rk);
     if (b < nblocks) blocks<1, MODE>(in, out, mode, b, stride, sp, lane, mask, rk);
+}
+
+// Small inputs: eight lanes to a block, lane s of them S-box s + 1.  A lane looks
+// one word up in a round and three DPP XORs add the eight, so every lane of the
+// group has both halves.  A round is a rotate that brings the box's window to bits
+// 7..12, one three-input op that keys it and adds the lane's place in the table,
+// the read and the XORs; with one block per lane it is 23 operations and eight
+// reads, which a lone wave issues one after the other (203 clocks a round).
+// Entry v of the table is a row of 32 words, word b SP of S-box b % 8: lane l reads
+// word l % 32, free of bank conflicts, and the whole table is 8 KiB.
+// Measured (us a launch, back to back, one block per lane -> this): 1 KB 6.4 -> 4.4,
+// 64 KiB 6.4 -> 4.5, 256 KiB 7.1 -> 5.4, 384 KiB 6.9 -> 6.8, 512 KiB 7.0 -> 8.1.
+// Four lanes to a block: 5.4 at 64 KiB, 6.6 at 384, 7.5 at 512.
+constexpr int kGroupThreads = 256;
+constexpr int kGroupBlocks = kGroupThreads / 8;  // blocks per workgroup
+
+template <int MODE>
+__global__ __launch_bounds__(kGroupThreads) void tdes_spbox_group_kernel(const uint8_t *in,
+                                                                        uint8_t *out,
+                                                                        size_t nblocks,
+                                                                        SpboxKeys keys,
+                                                                        ModeArgs mode) {
+    __shared__ __align__(16) uint32_t table[64 * kCopies];
+    __shared__ uint32_t rk[48 * kCopies];
+    const uint32_t tid = threadIdx.x, place = tid % kCopies, box = tid % 8;
+    const size_t b = (size_t)blockIdx.x * kGroupBlocks + tid / 8;
+    const size_t from = b < nblocks ? b : nblocks - 1;  // (lanes past the end repeat the last block)
+    const uint2 w = cipher_input<MODE>(in, mode, from);
+    const uint2 x = xor_input<MODE>(in, mode, from);
+#pragma unroll
+    for (int j = 0; j < 64 * kCopies / 4 / kGroupThreads; j++) {
+        const uint32_t c = tid + j * kGroupThreads;  // row c / 8, words 4 (c % 8) ..
+        reinterpret_cast<uint4 *>(table)[c] =
+            reinterpret_cast<const uint4 *>(SP_BY_CHUNK)[2 * (c / 8) + c % 2];
+    }
+    // round keys: chunk `box` of round r at bits 7..12, with the lane's place in
+    // the table below
+    const uint32_t word = box == 7 ? 3u : box == 0 || box == 6 ? 2u : box % 2 ? 0u : 1u;
+    const uint32_t sh = box == 7 ? 11u : box == 0 ? 7u : box == 6 ? 15u : 27u - 4u * box;
+#pragma unroll
+    for (int j = 0; j < 48 * kCopies / kGroupThreads; j++) {
+        const uint32_t r = tid / kCopies + j * (kGroupThreads / kCopies);
+        rk[r * kCopies + place] = ((keys.w[r][word] >> sh) & 63u) << 7 | 4u * place;
+    }
+    __syncthreads();
+    const uint8_t *sp = reinterpret_cast<const uint8_t *>(table);
+    const uint32_t rot = (20u - 4u * box) & 31u;  // window `box` of R down to bits 7..12
+    const uint32_t mask = in_vgpr(kIndexMask);
+    auto round = [&](uint32_t L, uint32_t R, uint32_t k) {
+        // 0x6A: (first & second) ^ third
+        const uint32_t a =
+            __builtin_amdgcn_bitop3_b32(__builtin_amdgcn_alignbit(R, R, rot), mask, k, 0x6A);
+        uint32_t v = *reinterpret_cast<const uint32_t *>(sp + a);
+        v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);   // lanes 1 0 3 2
+        v ^= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);   // lanes 2 3 0 1
+        return L ^ v ^ (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);  // 7 - l
+    };
+    uint32_t X, Y;
+    SP_IP(w.x, w.y, X, Y);
+    const uint32_t *kp = rk + place;
+#pragma unroll 1
+    for (int pass = 0; pass < 3; pass++, kp += 16 * kCopies) {
+        uint32_t k[16];
+#pragma unroll
+        for (int r = 0; r < 16; r++) k[r] = kp[r * kCopies];
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+            X = round(X, Y, k[r]);
+            Y = round(Y, X, k[r + 1]);
+        }
+        const uint32_t t = X;  // R16 || L16
+        X = Y;
+        Y = t;
+    }
+    uint32_t o0, o1;
+    SP_FP(Y, X, o0, o1);  // (the halves have changed places once more)
+    if (box == 0 && b < nblocks)
+        *reinterpret_cast<uint2 *>(out + 8 * b) = make_uint2(o0 ^ x.x, o1 ^ x.y);
 }
 
 // ECB over device-mapped host memory.  Bound by the PCIe link, which carries
@@ -227,6 +306,13 @@ template <int MODE>
 hipError_t launch_spbox(const SpboxKeys &k, const ModeArgs &m, const uint8_t *in, uint8_t *out,
                         size_t nbytes, hipStream_t stream) {
     const size_t nblocks = nbytes / 8;
+    // up to four waves of groups a SIMD (256 KiB on 256 CUs)
+    if (nblocks <= 128 * device_cus()) {
+        hipLaunchKernelGGL(tdes_spbox_group_kernel<MODE>,
+                           dim3((unsigned)((nblocks + kGroupBlocks - 1) / kGroupBlocks)),
+                           dim3(kGroupThreads), 0, stream, in, out, nblocks, k, m);
+        return hipGetLastError();
+    }
     const uint32_t per = working_lanes(nblocks);
     size_t grid = (nblocks + per - 1) / per;
     // Two workgroups per resident slot: the second wave of workgroups fills

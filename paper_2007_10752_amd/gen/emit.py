@@ -515,6 +515,10 @@ def emit_spbox():
     s.append("// Combined S-box + straight permutation tables: SP[s*64 + v] is P applied to\n"
              "// the output of S-box s+1 on chunk v, f bit j at bit position 32 - j.\n")
     s.append(c_array("static __device__ const uint32_t SP_TABLE", ["0x%08xu" % v for v in sp_tables()], 8))
+    sp = sp_tables()
+    s.append("// The same by chunk: SP_BY_CHUNK[8 v + s].\n")
+    s.append(c_array("static __device__ const uint32_t SP_BY_CHUNK",
+                     ["0x%08xu" % sp[64 * box + v] for v in range(64) for box in range(8)], 8))
     for name, table, head, tail, what in (
             ("SP_IP(w0, w1, L, R)", T.IP,
              "    uint32_t hi = __builtin_bswap32(w0), lo = __builtin_bswap32(w1), t;",

@@ -1,7 +1,8 @@
 """CTR and CBC decryption on both sides of the table kernel's limit (its
-workgroups one to a CU) and of the switches between its working lanes, in
-place and 8-byte aligned, bit for bit against the oracle; ECB's automatic
-choice at the same sizes."""
+workgroups one to a CU) and of the limit up to which eight lanes share a block
+(128 blocks a CU), and around a workgroup of such groups (32 blocks), in place
+and 8-byte aligned, bit for bit against the oracle; ECB's automatic choice at
+the same sizes."""
 import numpy as np
 import pytest
 
@@ -13,8 +14,8 @@ pytestmark = pytest.mark.gpu
 
 
 # (blocks per CU, blocks beyond)
-@pytest.mark.parametrize("per_cu,extra", [(0, 1), (0, 65), (64, 0), (64, 1), (1024, -1), (1024, 0),
-                                          (1024, 1)])
+@pytest.mark.parametrize("per_cu,extra", [(0, 1), (0, 31), (0, 32), (0, 33), (128, 0), (128, 1),
+                                          (1024, -1), (1024, 0), (1024, 1)])
 @pytest.mark.parametrize("offset", [0, 8])
 def test_modes_around_the_table_kernels_limit(per_cu, extra, offset):
     import torch
