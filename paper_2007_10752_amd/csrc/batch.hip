@@ -545,55 +545,116 @@ void batch_bitslice_kernel(const tdes_msg *__restrict__ msgs, uint32_t n_msgs,
 }
 
 // Key expansion, one wave per bundle (four per workgroup), both directions.
-// The rounds are independent once each round key is computed on its own
-// (des_round_key), so lanes 0..47 each make one of the 48 round keys, then
-// the primary mask of one round per direction; the mask walk that links the
-// rounds is short and runs on every lane alike; lane t then forms the two
-// words of round t and lanes 48..51 the four extra words.  A wave finishes
-// in a few microseconds, so small batches (a request server's) do not wait
-// on one thread working through a whole bundle.
+// Lane r < 48 makes round key r on its own, from the key's two halves rotated once
+// by the summed shift table, and what depends on it alone: its primary mask in the
+// order word 2t wants it, and its second-use word.  The masks a half carries before
+// and after a round are other rounds' primary masks (bs_mask_before,
+// bs_mask_after), so lane t then forms word 2t of either direction from two of
+// them.  Bound by VALU issue (shifts and fields, which do not pair).  16,384
+// bundles: 35 us with the walk from round to round on every lane and each
+// direction's masks on their own, 20 with neither, 12.8 with the fields below.
 constexpr int kExpandWaves = 4;
+
+// Bit i of the result is bit SRC::at(i) of src (64 bits), i < N <= 32; a run of
+// consecutive source bits is moved as one field.
+template <class SRC, int N, int I = 0>
+__device__ __forceinline__ uint32_t pick_bits(uint64_t src) {
+    if constexpr (I >= N) {
+        return 0;
+    } else {
+        constexpr int len = [] {
+            int n = 1;
+            while (I + n < N && SRC::at(I + n) == SRC::at(I) + n &&
+                   SRC::at(I) / 32 == (SRC::at(I) + n) / 32)
+                n++;
+            return n;
+        }();
+        const uint32_t w = SRC::at(I) < 32 ? (uint32_t)src : (uint32_t)(src >> 32);
+        const uint32_t field = (w >> (SRC::at(I) % 32)) & (uint32_t)((1ull << len) - 1);
+        return field << I | pick_bits<SRC, N, I + len>(src);
+    }
+}
+struct PrimaryBits {  // of the expanded key: bit e at e
+    static constexpr int at(int i) { return kBsPrimaryE[i]; }
+};
+struct DupKeyBits {
+    static constexpr int at(int i) { return kBsDupE[i]; }
+};
+struct DupMaskBits {  // of the primary mask
+    static constexpr int at(int i) { return kBsESrc[kBsDupE[i]]; }
+};
+struct OutBits {
+    static constexpr int at(int i) { return kBsOutWord[i]; }
+};
+// PC-2 (Sec. III-A), round-key bit e (0..31, 32..47) at bit e % 32, of the halves d
+// (bits 0..27) and c (32..59).
+constexpr int pc2_at(int e) { return kPC2[e] <= 28 ? 32 + 28 - kPC2[e] : 56 - kPC2[e]; }
+struct Pc2Lo {
+    static constexpr int at(int i) { return pc2_at(i); }
+};
+struct Pc2Hi {
+    static constexpr int at(int i) { return pc2_at(32 + i); }
+};
+
+// PC-1 of a key read as a little-endian word: the 8x8 bit matrix of its bytes, last
+// byte first, transposed by exchanging index bits (the two-word method of Warren,
+// Hacker's Delight, Sec. 7-3), has row j = bit j + 1 of bytes 8 .. 1.
+__device__ __forceinline__ uint64_t pc1_halves(uint64_t key) {
+    uint32_t hi = (uint32_t)(key >> 32), lo = (uint32_t)key, t;
+    t = (hi ^ (hi >> 7)) & 0x00AA00AAu, hi ^= t ^ (t << 7);
+    t = (lo ^ (lo >> 7)) & 0x00AA00AAu, lo ^= t ^ (t << 7);
+    t = (hi ^ (hi >> 14)) & 0x0000CCCCu, hi ^= t ^ (t << 14);
+    t = (lo ^ (lo >> 14)) & 0x0000CCCCu, lo ^= t ^ (t << 14);
+    t = (hi & 0xF0F0F0F0u) | ((lo >> 4) & 0x0F0F0F0Fu);
+    lo = ((hi << 4) & 0xF0F0F0F0u) | (lo & 0x0F0F0F0Fu);
+    hi = t;
+    // C: rows 1-3 and half of row 4; D: rows 7, 6, 5 and the other half of row 4
+    const uint32_t c = hi >> 4;
+    const uint32_t d = ((lo >> 8) & 0xFFu) << 20 | ((lo >> 16) & 0xFFu) << 12 | (lo >> 24) << 4 | (hi & 15u);
+    return (uint64_t)c << 32 | d;
+}
 
 __global__ __launch_bounds__(kExpandWaves * kWave) void expand_kernel(const uint8_t *keys24,
                                                                       size_t n,
                                                                       uint32_t *schedules) {
-    __shared__ uint64_t rk_s[kExpandWaves][48];
-    __shared__ uint32_t p_s[kExpandWaves][2][48];
+    // per round key: its primary mask, the same in the order of the S-box outputs,
+    // and its second-use word
+    __shared__ uint32_t p_s[kExpandWaves][48], o_s[kExpandWaves][48], d_s[kExpandWaves][48];
     const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     const size_t b = (size_t)blockIdx.x * kExpandWaves + w;
-    const bool live = b < n;  // uniform per wave; every wave reaches the barriers
+    const bool live = b < n;  // uniform per wave; every wave reaches the barrier
     if (live && lane < 48) {
         const uint8_t *kp = keys24 + 24 * b + 8 * (lane / 16);
-        uint8_t key[8];
-        for (int i = 0; i < 8; i++) key[i] = kp[i];
-        rk_s[w][lane] = des_round_key(key, lane % 16);
+        uint64_t key = 0;
+        for (int i = 0; i < 8; i++) key |= (uint64_t)kp[i] << (8 * i);
+        const uint64_t cd = pc1_halves(key);
+        int s = 0;
+#pragma unroll
+        for (int j = 0; j < 16; j++) s += j <= lane % 16 ? (int)kShifts[j] : 0;
+        s %= 28;
+        const uint64_t r = (uint64_t)ks_rotl28((uint32_t)(cd >> 32), s) << 32 |
+                           ks_rotl28((uint32_t)cd & 0x0FFFFFFFu, s);
+        const uint64_t rk = (uint64_t)pick_bits<Pc2Hi, 16>(r) << 32 | pick_bits<Pc2Lo, 32>(r);
+        const uint32_t p = pick_bits<PrimaryBits, 32>(rk);
+        p_s[w][lane] = p;
+        o_s[w][lane] = pick_bits<OutBits, 32>(p);
+        d_s[w][lane] = pick_bits<DupKeyBits, 16>(rk) ^ pick_bits<DupMaskBits, 16>(p);
     }
     __syncthreads();
-    if (live && lane < 48)
-        for (int dir = 0; dir < 2; dir++)
-            p_s[w][dir][lane] = bs_primary_mask(rk_s[w][round_key_slot(dir, lane)]);
-    __syncthreads();
-    if (!live) return;
+    if (!live || lane >= 50) return;
     for (int dir = 0; dir < 2; dir++) {
-        uint32_t ms = 0, md = 0, nm = 0, extra[4];
-        bs_mask_walk(
-            p_s[w][dir],
-            [&](int t, uint32_t s0, uint32_t d0, uint32_t n0) {
-                if (t == lane) {
-                    ms = s0;
-                    md = d0;
-                    nm = n0;
-                }
-            },
-            extra);
-        uint32_t *out = schedules + b * kDeviceScheduleWords + dir * kDirWords;
+        auto P = [&](int t) { return p_s[w][round_key_slot(dir, t)]; };
+        uint2 out;
         if (lane < 48) {
-            out[2 * lane + 1] = bs_dup_word(ms, rk_s[w][round_key_slot(dir, lane)]);
-            out[2 * lane] = bs_comp_word(md, nm);
-        } else if (lane < 52) {
-            const int i = lane - 48;
-            out[96 + i] = i == 0 ? extra[0] : i == 1 ? extra[1] : i == 2 ? extra[2] : extra[3];
+            const int before = bs_mask_before(lane), after = bs_mask_after(lane);
+            out.x = (before < 0 ? 0u : o_s[w][round_key_slot(dir, before)]) ^
+                    (after < 0 ? 0u : o_s[w][round_key_slot(dir, after)]);
+            out.y = d_s[w][round_key_slot(dir, lane)];
+        } else {  // words 96, 97 and 98, 99 (bs_extra_word)
+            out.x = lane == 48 ? P(0) : P(31) ^ P(32);
+            out.y = lane == 48 ? P(15) ^ P(16) : P(47);
         }
+        reinterpret_cast<uint2 *>(schedules + b * kDeviceScheduleWords + dir * kDirWords)[lane] = out;
     }
 }
 

@@ -130,8 +130,8 @@ TDES_HD inline uint32_t bs_comp_word(uint32_t md, uint32_t nm) {
 // P[t] of the rounds' keys: f(t, ms, md, nm) for every round (ms: mask of
 // the source half when round t reads it; md, nm: mask of the destination
 // half before and after round t), and the four extra words (initial mask of
-// Y, re-masks before rounds 16 and 32, final mask of X).  Only this walk is
-// sequential; the words of different rounds can be formed in parallel.
+// Y, re-masks before rounds 16 and 32, final mask of X).  The definition of the
+// scheme; the closed form below is what runs.
 template <class F>
 TDES_HD inline void bs_mask_walk(const uint32_t *P, F &&f, uint32_t extra[4]) {
     uint32_t mx = 0, my = P[0];  // current mask of each half
@@ -155,19 +155,28 @@ TDES_HD inline void bs_mask_walk(const uint32_t *P, F &&f, uint32_t extra[4]) {
     extra[3] = mx;
 }
 
+// The walk's masks in closed form, so that the rounds' words need nothing from
+// each other: the half round t updates carries mask P[bs_mask_before(t)] before
+// the round and P[bs_mask_after(t)] after it (-1: none).  A half is read in every
+// round in which it is not updated; around the passes' ends the same half is
+// updated twice in a row (rounds 15 and 16, 31 and 32).
+TDES_HD inline int bs_mask_before(int t) { return t == 16 || t == 32 ? t + 1 : t - 1; }
+TDES_HD inline int bs_mask_after(int t) { return t == 47 ? -1 : t == 15 || t == 31 ? t + 2 : t + 1; }
+// The four extra words.
+TDES_HD inline uint32_t bs_extra_word(const uint32_t *P, int i) {
+    return i == 0 ? P[0] : i == 1 ? P[15] ^ P[16] : i == 2 ? P[31] ^ P[32] : P[47];
+}
+
 // The 100 mask words of direction dir for round keys k.
 TDES_HD inline void bitslice_mask_words(const uint64_t (&k)[3][16], int dir, uint32_t *w) {
     uint32_t P[48];
     for (int t = 0; t < 48; t++) P[t] = bs_primary_mask(round_key_at(k, dir, t));
-    uint32_t extra[4];
-    bs_mask_walk(
-        P,
-        [&](int t, uint32_t ms, uint32_t md, uint32_t nm) {
-            w[2 * t + 1] = bs_dup_word(ms, round_key_at(k, dir, t));
-            w[2 * t] = bs_comp_word(md, nm);
-        },
-        extra);
-    for (int i = 0; i < 4; i++) w[96 + i] = extra[i];
+    for (int t = 0; t < 48; t++) {
+        const int b = bs_mask_before(t), a = bs_mask_after(t);
+        w[2 * t] = bs_comp_word(b < 0 ? 0u : P[b], a < 0 ? 0u : P[a]);
+        w[2 * t + 1] = bs_dup_word(P[t], round_key_at(k, dir, t));
+    }
+    for (int i = 0; i < 4; i++) w[96 + i] = bs_extra_word(P, i);
 }
 
 }  // namespace tdes
