@@ -175,6 +175,52 @@ __global__ __launch_bounds__(kScanThreads) void batch_tile_finish_kernel(size_t 
     }
 }
 
+// The whole scan in one launch, for at most kOneScanTiles tiles: workgroup b also
+// validates and sums the descriptors of the tiles before its own, in place of a
+// second launch that waits for every tile: 4,000 messages of 2,000 bytes 46.5 ->
+// 44.6 us a submit.  (16 tiles: 154 -> 158, the loads of the last one's threads
+// take longer than the launch.)
+constexpr size_t kOneScanTiles = 8;
+
+__global__ __launch_bounds__(kScanThreads) void batch_scan_kernel(const tdes_msg *msgs, size_t n,
+                                                                 size_t n_sched, BatchBounds bb,
+                                                                 uint64_t *ws, uint64_t *skipped_out) {
+    __shared__ uint64_t red[kScanThreads / kWave];
+    const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+    uint64_t part = 0, skipped = 0;
+#pragma unroll 8
+    for (uint32_t t = 0; t < blockIdx.x; t++) {
+        bool bad = false;
+        part += units_of(msgs[(size_t)t * kTile + threadIdx.x], n_sched, bb, kSlice, &bad);
+        skipped += bad;
+    }
+    const size_t i = (size_t)blockIdx.x * kTile + threadIdx.x;
+    bool bad = false;
+    const uint64_t v0 = units_of(msgs[i < n ? i : n - 1], n_sched, bb, kSlice, &bad);
+    const uint64_t v = i < n ? v0 : 0;
+    skipped += i < n && bad;
+    const uint64_t before_tile = block_sum(part, red);
+    const uint64_t incl = wave_scan(v, lane);
+    if (lane == kWave - 1) red[w] = incl;
+    __syncthreads();
+    uint64_t before = before_tile, total = before_tile;
+    for (int k = 0; k < kScanThreads / kWave; k++) {
+        before += k < w ? red[k] : 0;
+        total += red[k];
+    }
+    if (i < n) ws[kWsHeader + i] = before + incl - v;
+    if (blockIdx.x == gridDim.x - 1) {
+        __syncthreads();
+        skipped = block_sum(skipped, red);
+        if (threadIdx.x == 0) {
+            ws[0] = total;
+            ws[1] = skipped;
+            ws[kWsHeader + n] = total;
+            if (skipped_out != nullptr) *skipped_out = skipped;
+        }
+    }
+}
+
 // Key masks of the messages a wave works on, expanded cooperatively into a
 // table in LDS one round ahead of use (in place of each lane expanding its
 // own 48 masks per round).  The wave's lanes hold consecutive slices, so a
@@ -775,6 +821,11 @@ hipError_t launch_scan(const tdes_msg *msgs, size_t n_msgs, size_t n_schedules, 
                        uint64_t *ws, uint64_t *skipped_out, hipStream_t stream) {
     const size_t T = (n_msgs + kTile - 1) / kTile;  // n_msgs >= 1
     if (T > 0x7fffffffu) return hipErrorInvalidValue;
+    if (T <= kOneScanTiles) {
+        hipLaunchKernelGGL(batch_scan_kernel, dim3((unsigned)T), dim3(kScanThreads), 0, stream, msgs,
+                           n_msgs, n_schedules, bb, ws, skipped_out);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(batch_tile_scan_kernel, dim3((unsigned)T), dim3(kScanThreads), 0, stream,
                        msgs, n_msgs, n_schedules, bb, ws);
     hipError_t e = hipGetLastError();
