@@ -30,9 +30,11 @@
 // IV before the first), re-read after the rounds.
 //
 // Bound by VALU issue: 92 % of the SIMDs' issue slots are busy on 1 GiB, with
-// 0.875 of the instructions issued in pairs, at ~1.93 GHz under load.  With 224
-// operations a round (176 S-box gates) 1 GiB takes 1,028 us (1,044 GB/s);
-// with 242 (196 gates) it took 1,083 us.
+// 0.875 of the instructions issued in pairs, at ~1.93 GHz under load.  1 GiB by
+// the operations of a round, each pair on one machine: 242 (196 S-box gates) 1,083
+// us, 224 (176 gates) 1,028; 224 1,066 us, 211 (163 gates) 1,015.
+// Two waves a workgroup, masks one S-box ahead, or a 5-wave register budget: no
+// faster (1,016-1,026 us where this took 1,013-1,020).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
