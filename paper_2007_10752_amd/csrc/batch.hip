@@ -14,7 +14,8 @@
 // ahead, into a table in LDS (one row per message and round, in the plain
 // kernel's layout), and each lane reads its own message's row with the plain
 // kernel's piped LDS reads.  In a wave over more messages each lane widens its
-// own message's key words, one S-box ahead.
+// own message's key words, one S-box ahead, and in a wave inside one message the
+// masks are scalars.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -364,6 +365,33 @@ struct LaneMasks {
                 m.e[i] = (uint32_t)__builtin_amdgcn_sbfe((int)p.w.y, (uint32_t)kBsBoxDup[4 * j + i], 1);
     }
 };
+// Key masks of a wave inside one message: the words are uniform, and so are the
+// masks, which stay in scalar registers (an operand from there keeps an operation
+// from pairing, but there is no table to build and read: 64 messages of 800 KB 78 ->
+// 71 us a submit, 3,000 of 40 KB 157 -> 149; 16,384 of 4 KiB the same, 152).
+struct ScalarRounds {
+    const uint32_t *words;  // the message: the 100 words of its direction (uniform)
+    uint2 cur, next;
+    BsBoxMasks pm[8];
+    __device__ __forceinline__ uint2 load(int t) const { return make_uint2(words[2 * t], words[2 * t + 1]); }
+    __device__ __forceinline__ void start() {
+        cur = load(0);
+        next = load(1);
+        LaneMasks{}(pm[0], LaneWords{cur, 0}, BS_BOX_NDUP[0]);
+    }
+    template <int PH>
+    __device__ __forceinline__ void round(uint32_t (&d)[32], const uint32_t (&r)[32], int t) {
+        const uint2 after = load(t + 2);  // past round 47: the extra words, not used
+        bs_round_piped<1>(d, r, LaneWords{cur, 0}, LaneWords{next, 0}, pm, LaneMasks{});
+        cur = next;
+        next = after;
+    }
+    __device__ __forceinline__ void extra(int g, uint32_t (&a)[32]) const {
+        const uint32_t w = words[96 + g];
+#pragma unroll
+        for (int i = 0; i < 32; i++) a[i] ^= (uint32_t)__builtin_amdgcn_sbfe((int)w, (uint32_t)i, 1);
+    }
+};
 struct LaneRounds {
     const uint32_t *words;  // the lane's message: the 100 words of its direction
     uint2 cur, next;        // key words of this round and the next
@@ -418,12 +446,12 @@ typedef __attribute__((address_space(1))) const v2u g_cu2;
 typedef __attribute__((address_space(1))) v2u g_u2;
 
 // Rows of the mask table for a wave over n messages: 4 if they fit, else KMAX (a
-// table builds every one of its rows each round, so fewer rows cost less); 0 for
-// more than KMAX messages, which take no table.  Most waves of a batch of
+// table builds every one of its rows each round, so fewer rows cost less).  No table
+// for one message (1) and for more than KMAX (0).  Most waves of a batch of
 // kilobyte messages span 2 to 5 of them.
 template <int KMAX>
 __device__ __forceinline__ uint32_t table_rows(uint32_t n) {
-    return n <= 4 ? 4 : n <= KMAX ? KMAX : 0;
+    return n == 1 ? 1 : n <= 4 ? 4 : n <= KMAX ? KMAX : 0;
 }
 
 template <int KMAX, int WAVES>
@@ -441,7 +469,7 @@ void batch_bitslice_kernel(const tdes_msg *__restrict__ msgs, uint32_t n_msgs,
     const uint64_t stride = (uint64_t)gridDim.x * kThreads;
     for (uint64_t base = ((uint64_t)blockIdx.x * kWavesPerBlock + wave) * kWave; base < total;
          base += stride) {
-        uint32_t K;  // rows of the mask table (0: lanes widen their own masks)
+        uint32_t K;  // table_rows of the wave
         {
             // Issue priority: the message lookup, loads and input transposes
             // at the highest, the rounds at the lowest, so a wave that has
@@ -580,6 +608,12 @@ void batch_bitslice_kernel(const tdes_msg *__restrict__ msgs, uint32_t n_msgs,
                 cipher([&] {
                     LaneRounds rr;
                     rr.words = sched + *(lds_vu32 *)&mine_ls->row;
+                    return rr;
+                });
+            else if (K == 1)
+                cipher([&] {
+                    ScalarRounds rr;
+                    rr.words = sched + ((__builtin_amdgcn_readfirstlane(woff) >> 2) & ~1u);  // (lane 0's)
                     return rr;
                 });
             else if (KMAX > 4 && K == 4)
