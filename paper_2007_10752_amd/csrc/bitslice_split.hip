@@ -17,12 +17,15 @@
 // The key masks are bits of the launch's key words, widened by scalar
 // instructions: no mask table in LDS, and nothing to build before the rounds.
 //
-// Bound by the latency of the exchange (write, barrier, read: about 380 of the
-// ~530 clocks of a round) up to two chunks a CU, then by LDS bandwidth: 80 rows
-// a round and chunk, against none for the plain kernel, which is the faster one
-// where its SIMDs hold two waves or more.  Measured (kernel time, us, plain ->
-// split): 1 MiB 31.3 -> 14.9, 4 MiB 31.8 -> 15.7, 8 MiB 31.3 -> 17.6, 12 MiB
-// 32.0 -> 21.7, 16 MiB 32.3 -> 26.9, 20 MiB 35.4 -> 33.5, 24 MiB 37.7 -> 38.5.
+// A round takes ~540 clocks, most of it the exchange, which all waves make at
+// once: 80 rows of LDS traffic (160 clocks at 128 B a clock), two LDS latencies and
+// the barrier.  From three chunks a CU on LDS bandwidth and the masks' unpaired
+// operations bound it, and the plain kernel is the faster one where its SIMDs hold
+// two waves or more.  Measured (kernel time, us, plain -> split, 176 S-box gates):
+// 1 MiB 31.3 -> 14.9, 4 MiB 31.8 -> 15.7, 8 MiB 31.3 -> 17.6, 12 MiB 32.0 -> 21.7, 16
+// MiB 32.3 -> 26.9, 20 MiB 35.4 -> 33.5, 24 MiB 37.7 -> 38.5; with 163 gates 8 MiB 17.2,
+// 12 MiB 21.5, and with the round loop unrolled four times 16.5 and 21.1.  Key words
+// picked from vector registers by v_readlane in place of scalar loads: 18.3 and 22.8.
 // Two boxes a wave (four waves, fewer rows): 19.2 at 1 MiB, 27.9 at 16 MiB.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -125,7 +128,7 @@ __device__ __forceinline__ void split_rounds(const BitsliceKeys &keys, Exchange 
 #pragma unroll
         for (int i = 0; i < 6; i++) S[i] ^= mask_bit(kx, src_word(B, i));
         const int left = pass & 1;
-#pragma unroll 1
+#pragma unroll 4
         for (int r = 0; r < 8; r++) {
             t += 2;
             const uint32_t n0 = keys.w[2 * t], n1 = keys.w[2 * t + 1];
