@@ -248,7 +248,7 @@ tdes_status tdes_schedule_expand(const void *d_keys24, size_t n, void *d_schedul
     if (d_keys24 == nullptr || d_schedules == nullptr) return fail(TDES_ERR_ARG, "NULL pointer");
     if ((uintptr_t)d_schedules % 16 != 0) return fail(TDES_ERR_ALIGN, "schedules must be 16-byte aligned");
     hipError_t e = tdes::launch_expand(static_cast<const uint8_t *>(d_keys24), n,
-                                       static_cast<uint32_t *>(d_schedules),
+                                       static_cast<uint32_t *>(d_schedules), nullptr, nullptr, 0,
                                        static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail(TDES_ERR_DEVICE, "expand launch failed: %s", hipGetErrorString(e));
     return TDES_OK;

@@ -26,6 +26,7 @@
 #include "batch_core.h"
 #include "bitslice_core.h"
 #include "internal.h"
+#include "keysched_device.h"
 #include "lds_masks.h"
 
 // The compiled variants of the batched cipher, X(KMAX, WAVES): KMAX
@@ -635,25 +636,6 @@ void batch_bitslice_kernel(const tdes_msg *__restrict__ msgs, uint32_t n_msgs,
 // direction's masks on their own, 20 with neither, 12.8 with the fields below.
 constexpr int kExpandWaves = 4;
 
-// Bit i of the result is bit SRC::at(i) of src (64 bits), i < N <= 32; a run of
-// consecutive source bits is moved as one field.
-template <class SRC, int N, int I = 0>
-__device__ __forceinline__ uint32_t pick_bits(uint64_t src) {
-    if constexpr (I >= N) {
-        return 0;
-    } else {
-        constexpr int len = [] {
-            int n = 1;
-            while (I + n < N && SRC::at(I + n) == SRC::at(I) + n &&
-                   SRC::at(I) / 32 == (SRC::at(I) + n) / 32)
-                n++;
-            return n;
-        }();
-        const uint32_t w = SRC::at(I) < 32 ? (uint32_t)src : (uint32_t)(src >> 32);
-        const uint32_t field = (w >> (SRC::at(I) % 32)) & (uint32_t)((1ull << len) - 1);
-        return field << I | pick_bits<SRC, N, I + len>(src);
-    }
-}
 struct PrimaryBits {  // of the expanded key: bit e at e
     static constexpr int at(int i) { return kBsPrimaryE[i]; }
 };
@@ -666,37 +648,26 @@ struct DupMaskBits {  // of the primary mask
 struct OutBits {
     static constexpr int at(int i) { return kBsOutWord[i]; }
 };
-// PC-2 (Sec. III-A), round-key bit e (0..31, 32..47) at bit e % 32, of the halves d
-// (bits 0..27) and c (32..59).
-constexpr int pc2_at(int e) { return kPC2[e] <= 28 ? 32 + 28 - kPC2[e] : 56 - kPC2[e]; }
-struct Pc2Lo {
+struct Pc2Lo {  // round-key bit e (0..31, 32..47) at bit e % 32
     static constexpr int at(int i) { return pc2_at(i); }
 };
 struct Pc2Hi {
     static constexpr int at(int i) { return pc2_at(32 + i); }
 };
 
-// PC-1 of a key read as a little-endian word: the 8x8 bit matrix of its bytes, last
-// byte first, transposed by exchanging index bits (the two-word method of Warren,
-// Hacker's Delight, Sec. 7-3), has row j = bit j + 1 of bytes 8 .. 1.
-__device__ __forceinline__ uint64_t pc1_halves(uint64_t key) {
-    uint32_t hi = (uint32_t)(key >> 32), lo = (uint32_t)key, t;
-    t = (hi ^ (hi >> 7)) & 0x00AA00AAu, hi ^= t ^ (t << 7);
-    t = (lo ^ (lo >> 7)) & 0x00AA00AAu, lo ^= t ^ (t << 7);
-    t = (hi ^ (hi >> 14)) & 0x0000CCCCu, hi ^= t ^ (t << 14);
-    t = (lo ^ (lo >> 14)) & 0x0000CCCCu, lo ^= t ^ (t << 14);
-    t = (hi & 0xF0F0F0F0u) | ((lo >> 4) & 0x0F0F0F0Fu);
-    lo = ((hi << 4) & 0xF0F0F0F0u) | (lo & 0x0F0F0F0Fu);
-    hi = t;
-    // C: rows 1-3 and half of row 4; D: rows 7, 6, 5 and the other half of row 4
-    const uint32_t c = hi >> 4;
-    const uint32_t d = ((lo >> 8) & 0xFFu) << 20 | ((lo >> 16) & 0xFFu) << 12 | (lo >> 24) << 4 | (hi & 15u);
-    return (uint64_t)c << 32 | d;
-}
-
+// The workgroups past the bundles' copy copy16 16-byte pieces from copy_src to
+// copy_dst (a server batch's descriptors and slice table, from host memory).
 __global__ __launch_bounds__(kExpandWaves * kWave) void expand_kernel(const uint8_t *keys24,
-                                                                      size_t n,
-                                                                      uint32_t *schedules) {
+                                                                      size_t n, uint32_t *schedules,
+                                                                      const uint4 *copy_src,
+                                                                      uint4 *copy_dst,
+                                                                      size_t copy16) {
+    const size_t key_groups = (n + kExpandWaves - 1) / kExpandWaves;
+    if (blockIdx.x >= key_groups) {
+        const size_t at = (blockIdx.x - key_groups) * (size_t)(kExpandWaves * kWave) + threadIdx.x;
+        if (at < copy16) copy_dst[at] = copy_src[at];
+        return;
+    }
     // per round key: its primary mask, the same in the order of the S-box outputs,
     // and its second-use word
     __shared__ uint32_t p_s[kExpandWaves][48], o_s[kExpandWaves][48], d_s[kExpandWaves][48];
@@ -704,16 +675,8 @@ __global__ __launch_bounds__(kExpandWaves * kWave) void expand_kernel(const uint
     const size_t b = (size_t)blockIdx.x * kExpandWaves + w;
     const bool live = b < n;  // uniform per wave; every wave reaches the barrier
     if (live && lane < 48) {
-        const uint8_t *kp = keys24 + 24 * b + 8 * (lane / 16);
-        uint64_t key = 0;
-        for (int i = 0; i < 8; i++) key |= (uint64_t)kp[i] << (8 * i);
-        const uint64_t cd = pc1_halves(key);
-        int s = 0;
-#pragma unroll
-        for (int j = 0; j < 16; j++) s += j <= lane % 16 ? (int)kShifts[j] : 0;
-        s %= 28;
-        const uint64_t r = (uint64_t)ks_rotl28((uint32_t)(cd >> 32), s) << 32 |
-                           ks_rotl28((uint32_t)cd & 0x0FFFFFFFu, s);
+        const uint64_t r = round_halves(
+            load_key(keys24 + 24 * b + 8 * (lane / 16), ((uintptr_t)keys24 & 7u) == 0), lane % 16);
         const uint64_t rk = (uint64_t)pick_bits<Pc2Hi, 16>(r) << 32 | pick_bits<Pc2Lo, 32>(r);
         const uint32_t p = pick_bits<PrimaryBits, 32>(rk);
         p_s[w][lane] = p;
@@ -828,11 +791,14 @@ int batch_config_list(BatchConfig *out, int cap) {
     return n;
 }
 
-hipError_t launch_expand(const uint8_t *keys24, size_t n, uint32_t *schedules, hipStream_t stream) {
-    const size_t blocks = (n + kExpandWaves - 1) / kExpandWaves;
+hipError_t launch_expand(const uint8_t *keys24, size_t n, uint32_t *schedules,
+                         const void *copy_src, void *copy_dst, size_t copy_bytes, hipStream_t stream) {
+    const size_t copy16 = (copy_bytes + 15) / 16, threads = kExpandWaves * kWave;
+    const size_t blocks = (n + kExpandWaves - 1) / kExpandWaves + (copy16 + threads - 1) / threads;
     if (blocks > 0x7fffffffu) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(expand_kernel, dim3((unsigned)blocks), dim3(kExpandWaves * kWave), 0, stream,
-                       keys24, n, schedules);
+    hipLaunchKernelGGL(expand_kernel, dim3((unsigned)blocks), dim3((unsigned)threads), 0, stream, keys24,
+                       n, schedules, static_cast<const uint4 *>(copy_src), static_cast<uint4 *>(copy_dst),
+                       copy16);
     return hipGetLastError();
 }
 

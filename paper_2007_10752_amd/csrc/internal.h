@@ -108,7 +108,10 @@ std::string tune_cache_path();
 int cache_load(const char *path, const char *device, long cus, BatchConfig *out);
 bool cache_save(const char *path, const char *device, long cus, const BatchConfig &c,
                 double us_per_batch);
-hipError_t launch_expand(const uint8_t *keys24, size_t n, uint32_t *schedules, hipStream_t stream);
+// Device schedules of n bundles; the same launch copies copy_bytes bytes (rounded
+// up to 16) from copy_src to copy_dst.  Both may read device-mapped host memory.
+hipError_t launch_expand(const uint8_t *keys24, size_t n, uint32_t *schedules,
+                         const void *copy_src, void *copy_dst, size_t copy_bytes, hipStream_t stream);
 // The batched cipher alone, for messages known to be valid and a workspace whose
 // first-slice table the caller filled already ([0] total slices, [1] 0, [2 + i]
 // first slice of message i, [2 + n] total; a message has ceil(nbytes / 256)
@@ -179,17 +182,20 @@ struct SpboxMsg {
     uint8_t *out;
     uint64_t nblocks;
     uint32_t first_wg;
-    uint32_t pad;
+    uint32_t dir;
 };
 constexpr uint32_t kSpboxMultiMax = 64;  // messages per launch
 // Working lanes per workgroup for messages of these block counts: the fewest
 // of 64, 128, .. 1,024 whose workgroups fit the CUs once (1,024 if none).
 uint32_t spbox_multi_lanes(const uint64_t *nblocks, size_t n);
-// d_msgs: n device descriptors (1 <= n <= kSpboxMultiMax); d_keys: n
-// SpboxKeys in device memory, 16-byte aligned; n_wg: the workgroups the
-// descriptors cover (first_wg + ceil(nblocks / per) of the last message).
-hipError_t launch_spbox_multi(const SpboxMsg *d_msgs, uint32_t n, const SpboxKeys *d_keys,
-                              uint32_t per, uint32_t n_wg, hipStream_t stream);
+// h_msgs: n descriptors (1 <= n <= kSpboxMultiMax) and h_keys24: their bundles,
+// both in device-mapped host memory (read until the launches are done), 16-byte
+// aligned; d_msgs, d_keys: device memory for n SpboxMsg and SpboxKeys, which a
+// launch of its own fills; n_wg: the workgroups the descriptors cover
+// (first_wg + ceil(nblocks / per) of the last message).
+hipError_t launch_spbox_multi(const SpboxMsg *h_msgs, const uint8_t *h_keys24, SpboxMsg *d_msgs,
+                              SpboxKeys *d_keys, uint32_t n, uint32_t per, uint32_t n_wg,
+                              hipStream_t stream);
 
 // One DES pass of the one-thread-per-bit comparison kernel (in may equal out).
 hipError_t launch_replica_pass(const ReplicaKeyBits &k, const uint8_t *in, uint8_t *out,

@@ -179,4 +179,27 @@ TDES_HD inline void bitslice_mask_words(const uint64_t (&k)[3][16], int dir, uin
     for (int i = 0; i < 4; i++) w[96 + i] = bs_extra_word(P, i);
 }
 
+// The table kernel's keys of a round.  Key chunk s (bits 6s+1..6s+6 of the round
+// key) lines up with S-box window s of the right half R (bit i of R at position
+// 32 - i):
+//   windows 1..5 sit at positions 27-4s .. 32-4s of R; odd and even windows
+//   are disjoint, so one word carries the odd chunks and one the even ones;
+//   windows 0 and 7 wrap around, and are read from R rotated left by 12,
+//   at positions 7..12 and 11..16; window 6 is read there too, at 15..20,
+//   apart from window 0, so one word carries chunks 0 and 6 and another
+//   chunk 7.
+struct SpboxRound {
+    uint32_t w[4];
+};
+TDES_HD inline SpboxRound spbox_round_keys(uint64_t rk) {
+    uint32_t c[8];
+    for (int s = 0; s < 8; s++) c[s] = (uint32_t)((rk >> (42 - 6 * s)) & 0x3Fu);
+    SpboxRound k;
+    k.w[0] = c[1] << 23 | c[3] << 15 | c[5] << 7;
+    k.w[1] = c[2] << 19 | c[4] << 11;
+    k.w[2] = c[0] << 7 | c[6] << 15;
+    k.w[3] = c[7] << 11;
+    return k;
+}
+
 }  // namespace tdes

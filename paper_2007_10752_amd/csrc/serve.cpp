@@ -21,13 +21,14 @@ constexpr int kPlainEvents = 4096;
 // and batched kernel (~45 us) would finish.
 constexpr size_t kPlainBatchMax = 3;
 // Larger batches of at most this many requests and this many bytes in all
-// run as one launch of the table kernel over the requests (one block per
-// lane, each request's round keys built on the host), which finishes well
-// before the batched bitsliced path, whose lanes run 32 blocks each.
+// run on the table kernel over the requests (one block per lane), which
+// finishes well before the batched bitsliced path, whose lanes run 32 blocks
+// each.
 constexpr size_t kTableBatchMax = tdes::kSpboxMultiMax;
-// Its staging area: descriptors, then round keys (one pinned host buffer
-// mirrored by one device buffer, so a batch needs a single copy).
+// Its staging: descriptors, then raw bundles, in a pinned host buffer that a
+// kernel reads in place, and descriptors, then round keys, in a device buffer.
 constexpr size_t kTabKeysOff = kTableBatchMax * sizeof(tdes::SpboxMsg);
+constexpr size_t kTabHostBytes = kTabKeysOff + kTableBatchMax * 24;
 constexpr size_t kTabBytes = kTabKeysOff + kTableBatchMax * sizeof(tdes::SpboxKeys);
 static_assert(kTabKeysOff % 16 == 0, "round keys 16-byte aligned");
 
@@ -86,9 +87,10 @@ struct Active {
     double t_submit, t_admit;
 };
 
-// A slot's staging area, one pinned host buffer mirrored by one device
-// buffer so a batch needs a single copy: [first-slice table as the batched
-// cipher's workspace | descriptors | key bundles].
+// A slot's staging area, a pinned host buffer and a device buffer of the same
+// layout: [first-slice table as the batched cipher's workspace | descriptors |
+// key bundles].  The key expansion's launch reads the bundles in host memory and
+// copies the rest (a copy of its own takes 8 us more).
 struct Staging {
     size_t ws_off = 0, msgs_off = 0, keys_off = 0, bytes = 0;
     void layout(size_t n) {
@@ -111,6 +113,7 @@ struct Slot {
     uint8_t *h_stage = nullptr, *d_stage = nullptr;
     uint32_t *d_sched = nullptr;
     uint8_t *h_tab = nullptr, *d_tab = nullptr;  // table-kernel batches
+    uint8_t *m_stage = nullptr, *m_tab = nullptr;  // h_stage, h_tab as the device sees them
 };
 
 struct PlainEntry {
@@ -253,38 +256,31 @@ tdes_status launch_slot(tdes_server *s, Slot &sl) {
     for (const Active &a : sl.reqs) batch_bytes += a.req.nbytes;
     if (n <= kTableBatchMax && batch_bytes <= tdes::spbox_one_pass_bytes()) {
         tdes::SpboxMsg *tm = reinterpret_cast<tdes::SpboxMsg *>(sl.h_tab);
-        tdes::SpboxKeys *tk = reinterpret_cast<tdes::SpboxKeys *>(sl.h_tab + kTabKeysOff);
+        uint8_t *tk = sl.h_tab + kTabKeysOff;
         uint64_t nb[kTableBatchMax];
         for (size_t i = 0; i < n; i++) nb[i] = sl.reqs[i].req.nbytes / 8;
         const uint32_t per = tdes::spbox_multi_lanes(nb, n);
         uint64_t wg = 0;
         for (size_t i = 0; i < n; i++) {
             const Active &a = sl.reqs[i];
-            tdes_schedule ks;
-            for (int b = 0; b < 3; b++) tdes::des_round_keys(a.req.key24 + 8 * b, ks.k[b]);
-            tdes::RoundSequence seq;
-            tdes::round_sequence(ks, (int)a.req.dir, &seq);
-            tdes::spbox_keys(seq, &tk[i]);
+            memcpy(tk + 24 * i, a.req.key24, 24);
             tm[i].in = static_cast<const uint8_t *>(a.req.d_in);
             tm[i].out = static_cast<uint8_t *>(s->cfg.d_arena) + a.out_off;
             tm[i].nblocks = nb[i];
             tm[i].first_wg = (uint32_t)wg;
-            tm[i].pad = 0;
+            tm[i].dir = a.req.dir;
             wg += (nb[i] + per - 1) / per;
         }
-        // (the tail of the descriptor area is copied too: it is small)
-        e = hipMemcpyAsync(sl.d_tab, sl.h_tab, kTabKeysOff + n * sizeof(tdes::SpboxKeys),
-                           hipMemcpyHostToDevice, sl.stream);
-        if (e == hipSuccess)
-            e = tdes::launch_spbox_multi(
-                reinterpret_cast<const tdes::SpboxMsg *>(sl.d_tab), (uint32_t)n,
-                reinterpret_cast<const tdes::SpboxKeys *>(sl.d_tab + kTabKeysOff), per,
-                (uint32_t)wg, sl.stream);
+        e = tdes::launch_spbox_multi(reinterpret_cast<const tdes::SpboxMsg *>(sl.m_tab),
+                                     sl.m_tab + kTabKeysOff,
+                                     reinterpret_cast<tdes::SpboxMsg *>(sl.d_tab),
+                                     reinterpret_cast<tdes::SpboxKeys *>(sl.d_tab + kTabKeysOff),
+                                     (uint32_t)n, per, (uint32_t)wg, sl.stream);
         if (e == hipSuccess) e = hipEventRecord(sl.done, sl.stream);
         return e == hipSuccess ? TDES_OK : fail(TDES_ERR_DEVICE, hipGetErrorString(e));
     }
     // laid out for this batch's size (the buffers hold the largest batch), so
-    // the copy carries only what the batch uses
+    // only what the batch uses is copied
     Staging lay;
     lay.layout(n);
     uint64_t *ws = reinterpret_cast<uint64_t *>(sl.h_stage + lay.ws_off);
@@ -307,9 +303,8 @@ tdes_status launch_slot(tdes_server *s, Slot &sl) {
     ws[0] = total;
     ws[1] = 0;
     ws[2 + n] = total;
-    e = hipMemcpyAsync(sl.d_stage, sl.h_stage, lay.bytes, hipMemcpyHostToDevice, sl.stream);
-    if (e == hipSuccess)
-        e = tdes::launch_expand(sl.d_stage + lay.keys_off, n, sl.d_sched, sl.stream);
+    e = tdes::launch_expand(sl.m_stage + lay.keys_off, n, sl.d_sched, sl.m_stage, sl.d_stage,
+                            lay.keys_off, sl.stream);
     if (e == hipSuccess)
         e = tdes::launch_batch_prefixed(
             reinterpret_cast<const tdes_msg *>(sl.d_stage + lay.msgs_off), n, sl.d_sched, n,
@@ -479,8 +474,10 @@ tdes_status tdes_server_create(const tdes_server_config *cfg, tdes_server **out)
             if (e == hipSuccess) e = hipHostMalloc((void **)&sl.h_stage, sl.lay.bytes, 0);
             if (e == hipSuccess) e = hipMalloc((void **)&sl.d_stage, sl.lay.bytes);
             if (e == hipSuccess) e = hipMalloc((void **)&sl.d_sched, n * TDES_DEVICE_SCHEDULE_BYTES);
-            if (e == hipSuccess) e = hipHostMalloc((void **)&sl.h_tab, kTabBytes, 0);
+            if (e == hipSuccess) e = hipHostMalloc((void **)&sl.h_tab, kTabHostBytes, 0);
             if (e == hipSuccess) e = hipMalloc((void **)&sl.d_tab, kTabBytes);
+            if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&sl.m_stage, sl.h_stage, 0);
+            if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&sl.m_tab, sl.h_tab, 0);
         }
     }
     if (e != hipSuccess) {

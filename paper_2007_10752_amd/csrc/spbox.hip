@@ -40,6 +40,7 @@
 #include <atomic>
 
 #include "internal.h"
+#include "keysched_device.h"
 #include "spbox_core.h"
 
 namespace tdes {
@@ -256,6 +257,38 @@ __global__ __launch_bounds__(kThreads) void tdes_spbox_multi_kernel(const SpboxM
                             (threadIdx.x % kCopies) * 4u, in_vgpr(kIndexMask), rk);
 }
 
+// What a multi-message launch needs in device memory, from the messages' descriptors
+// and raw bundles in host memory, a wave to a message: lane t < 48 makes the table
+// kernel's keys of round t, four more copy the descriptor.  (A copy of host-built
+// keys took 8 us, and the host 1 us a message to build them.)
+struct Pc2Low {  // round-key bit e at bit 47 - e, as host code has it
+    static constexpr int at(int i) { return pc2_at(47 - i); }
+};
+struct Pc2High {
+    static constexpr int at(int i) { return pc2_at(15 - i); }
+};
+constexpr int kPrepareWaves = 4;
+
+__global__ __launch_bounds__(64 * kPrepareWaves) void tdes_spbox_prepare_kernel(
+    const SpboxMsg *h_msgs, const uint8_t *h_keys24, uint32_t n, SpboxMsg *msgs, SpboxKeys *keys) {
+    const uint32_t lane = threadIdx.x % 64;
+    const uint32_t m = blockIdx.x * kPrepareWaves + threadIdx.x / 64;
+    if (m >= n) return;
+    const uint32_t dir = h_msgs[m].dir & 1u;
+    if (lane >= 48) {
+        static_assert(sizeof(SpboxMsg) == 32, "four 8-byte words");
+        if (lane < 52)
+            reinterpret_cast<uint64_t *>(&msgs[m])[lane - 48] =
+                reinterpret_cast<const uint64_t *>(&h_msgs[m])[lane - 48];
+        return;
+    }
+    const int slot = round_key_slot((int)dir, (int)lane);
+    const uint64_t r = round_halves(load_key(h_keys24 + 24 * m + 8 * (slot / 16), true), slot % 16);
+    const uint64_t rk = (uint64_t)pick_bits<Pc2High, 16>(r) << 32 | pick_bits<Pc2Low, 32>(r);
+    const SpboxRound k = spbox_round_keys(rk);
+    *reinterpret_cast<uint4 *>(keys[m].w[lane]) = make_uint4(k.w[0], k.w[1], k.w[2], k.w[3]);
+}
+
 // Workgroups that fit on the current device at once: 64 KiB of tables per
 // workgroup, two in a CU's 160 KiB of LDS.
 size_t resident_workgroups() { return 2 * device_cus(); }
@@ -341,11 +374,16 @@ uint32_t spbox_multi_lanes(const uint64_t *nblocks, size_t n) {
     return per;
 }
 
-hipError_t launch_spbox_multi(const SpboxMsg *d_msgs, uint32_t n, const SpboxKeys *d_keys,
-                              uint32_t per, uint32_t n_wg, hipStream_t stream) {
+hipError_t launch_spbox_multi(const SpboxMsg *h_msgs, const uint8_t *h_keys24, SpboxMsg *d_msgs,
+                              SpboxKeys *d_keys, uint32_t n, uint32_t per, uint32_t n_wg,
+                              hipStream_t stream) {
     if (n == 0 || n > kSpboxMultiMax || n_wg == 0 || per == 0 || per % 64 != 0 ||
         per > (uint32_t)kThreads)
         return hipErrorInvalidValue;
+    hipLaunchKernelGGL(tdes_spbox_prepare_kernel, dim3((n + kPrepareWaves - 1) / kPrepareWaves),
+                       dim3(64 * kPrepareWaves), 0, stream, h_msgs, h_keys24, n, d_msgs, d_keys);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(tdes_spbox_multi_kernel, dim3(n_wg), dim3(kThreads), 0, stream, d_msgs, n,
                        d_keys, per);
     return hipGetLastError();
