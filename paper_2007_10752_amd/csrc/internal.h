@@ -186,7 +186,7 @@ struct SpboxMsg {
 };
 constexpr uint32_t kSpboxMultiMax = 64;  // messages per launch
 // Working lanes per workgroup for messages of these block counts: the fewest
-// of 64, 128, .. 1,024 whose workgroups fit the CUs once (1,024 if none).
+// whole waves whose workgroups fit the CUs once, at most 1,024 lanes.
 uint32_t spbox_multi_lanes(const uint64_t *nblocks, size_t n);
 // h_msgs: n descriptors (1 <= n <= kSpboxMultiMax) and h_keys24: their bundles,
 // both in device-mapped host memory (read until the launches are done), 16-byte
