@@ -1,9 +1,9 @@
 // Batched 3DES-EDE ECB on the table kernel, for small batches.
 //
-// One block per lane (spbox.hip), the blocks of all messages in a row, `per`
-// lanes of them to a workgroup and step.  The lanes of the bitsliced batch
-// kernel (batch.hip) take 32 blocks each through the rounds, ~40 us for the
-// smallest batch.
+// One block per lane (spbox.hip), or two or three, interleaved; the blocks of all
+// messages in a row, `per` of them to a workgroup and step.  The lanes of the
+// bitsliced batch kernel (batch.hip) take 32 blocks each through the rounds, ~40 us
+// for the smallest batch.
 //
 // A workgroup has a CU to itself: 64 KiB of tables, the round keys of up to
 // kRows messages (a row each, 784 bytes, padded so that the rows of different
@@ -109,7 +109,8 @@ __device__ __forceinline__ uint32_t block_prefix(uint32_t v, uint32_t *sums, uin
 
 // SCAN: the workgroup scans the descriptors itself (n <= kTableScanMax);
 // otherwise ws holds their scan.
-template <bool SCAN>
+// NB: blocks a lane takes in a step.
+template <bool SCAN, int NB>
 __global__ __launch_bounds__(kThreads) void batch_table_kernel(const tdes_msg *__restrict__ msgs,
                                                               uint32_t n,
                                                               const uint32_t *__restrict__ sched,
@@ -173,18 +174,30 @@ __global__ __launch_bounds__(kThreads) void batch_table_kernel(const tdes_msg *_
     const uint8_t *sp = reinterpret_cast<const uint8_t *>(table);
     const uint32_t mask = in_vgpr(kIndexMask);
     for (uint64_t base = (uint64_t)blockIdx.x * per; base < total; base += (uint64_t)grid * per) {
-        const uint32_t here = (uint32_t)min((uint64_t)per, total - base);  // lanes of this step
-        // this lane's message, and its block's place there
-        uint32_t m = 0;
-        uint64_t at = 0;
-        bool active = tid < here;
+        const uint32_t here = (uint32_t)min((uint64_t)per, total - base);  // blocks of this step
+        // this lane's blocks (tid, tid + lanes, ...): their messages, and their
+        // places there
+        const uint32_t lanes = NB == 1 ? kThreads : per / NB;
+        uint32_t m[NB];
+        uint64_t at[NB];
+        bool active[NB];
+#pragma unroll
+        for (int k = 0; k < NB; k++) {
+            m[k] = 0;
+            at[k] = 0;
+            active[k] = tid < lanes && tid + k * lanes < here;
+        }
         if (SCAN) {
-            const uint32_t b = (uint32_t)base + tid;
 #pragma unroll
             for (uint32_t step = kTableScanMax / 2; step >= 1; step /= 2)
-                if (m + step < n && start[m + step] <= b) m += step;
-            at = b - start[m];
+#pragma unroll
+                for (int k = 0; k < NB; k++)
+                    if (m[k] + step < n && start[m[k] + step] <= (uint32_t)base + tid + k * lanes)
+                        m[k] += step;
+#pragma unroll
+            for (int k = 0; k < NB; k++) at[k] = (uint32_t)base + tid + k * lanes - start[m[k]];
         } else {
+            static_assert(SCAN || NB == 1, "lanes by slices take one block");
             const uint64_t s0 = base / (kSlice / 8);
             const uint32_t s = tid / (kSlice / 8);
             const uint32_t m0 = find_message(first, n, s0, lane);
@@ -197,22 +210,30 @@ __global__ __launch_bounds__(kThreads) void batch_table_kernel(const tdes_msg *_
             for (uint32_t step = kThreads / 2; step >= 1; step /= 2)
                 if (start[r + step - 1] <= s) r += step;
             if (start[r] <= s) r++;
-            m = m0 + (active ? r : 0u);
-            if (active) {
-                while (first[m + 1] <= s0 + s) m++;  // past 1,024 messages: many empty ones
-                at = (s0 + s - first[m]) * (kSlice / 8) + tid % (kSlice / 8);
+            m[0] = m0 + (active[0] ? r : 0u);
+            if (active[0]) {
+                while (first[m[0] + 1] <= s0 + s) m[0]++;  // past 1,024 messages: many empty ones
+                at[0] = (s0 + s - first[m[0]]) * (kSlice / 8) + tid % (kSlice / 8);
             }
         }
-        if (tid == 0) span[0] = m;
-        if (tid == here - 1) span[1] = m;
-        uint2 w[1] = {};
-        uint8_t *dst = nullptr;
-        if (active) {
-            const tdes_msg d = msgs[m];
-            if (!SCAN) active = at < d.nbytes / 8;  // (a message's last slice may be partial)
-            if (active) {
-                w[0] = *reinterpret_cast<const uint2 *>(in + d.in_off + 8 * at);
-                dst = out + d.out_off + 8 * at;
+#pragma unroll
+        for (int k = 0; k < NB; k++) {
+            if (k == 0 && tid == 0) span[0] = m[0];
+            if (active[k] && tid + k * lanes == here - 1) span[1] = m[k];
+        }
+        uint2 w[NB] = {};
+        uint8_t *dst[NB];
+#pragma unroll
+        for (int k = 0; k < NB; k++) {
+            dst[k] = nullptr;
+            if (active[k]) {
+                const tdes_msg d = msgs[m[k]];
+                // (by slices, a message's last slice may be partial)
+                if (!SCAN) active[k] = at[k] < d.nbytes / 8;
+                if (active[k]) {
+                    w[k] = *reinterpret_cast<const uint2 *>(in + d.in_off + 8 * at[k]);
+                    dst[k] = out + d.out_off + 8 * at[k];
+                }
             }
         }
         __syncthreads();
@@ -232,9 +253,24 @@ __global__ __launch_bounds__(kThreads) void batch_table_kernel(const tdes_msg *_
                 if (lane < 48) rows[j * kRowStride + lane] = row;
             }
             __syncthreads();
-            if (active && m - g < kRows) {
-                cipher_blocks<1>(w, sp, (lane % kCopies) * 4u, mask, rows + (m - g) * kRowStride);
-                *reinterpret_cast<uint2 *>(dst) = w[0];
+            const uint4 *rk[NB];
+            bool now[NB];
+            bool any = false;
+#pragma unroll
+            for (int k = 0; k < NB; k++) {
+                now[k] = active[k] && m[k] - g < kRows;
+                any |= now[k];
+                // (a block of another pass runs along, on row 0, and is not stored)
+                rk[k] = rows + (now[k] ? m[k] - g : 0u) * kRowStride;
+            }
+            if (any) {
+                uint2 v[NB];
+#pragma unroll
+                for (int k = 0; k < NB; k++) v[k] = w[k];
+                cipher_blocks<NB>(v, sp, (lane % kCopies) * 4u, mask, rk);
+#pragma unroll
+                for (int k = 0; k < NB; k++)
+                    if (now[k]) *reinterpret_cast<uint2 *>(dst[k]) = v[k];
             }
             __syncthreads();
         }
@@ -245,8 +281,8 @@ __global__ __launch_bounds__(kThreads) void batch_table_kernel(const tdes_msg *_
 
 bool batch_is_table(size_t n_msgs, uint64_t work_bytes) {
     // us a submit, this kernel against the bitsliced one (256 CUs, one launch up
-    // to kTableScanMax messages): 300 messages in 2 MB 16 to 43, in 6 MB 39 to
-    // 42; 1,000 in 6.5 MB 49 to 45.  Three launches, lanes by slices: 4,000 in
+    // to kTableScanMax messages): 300 messages in 2 MB 16 to 43, in 6 MB 37 to
+    // 40; 1,000 in 6.5 MB 49 to 45.  Three launches, lanes by slices: 4,000 in
     // 1 MB 24 to 41, in 4 MB 48 to 41; 16,000 in 1.2 MB 39 to 42, in 4.2 MB 53
     // to 43.
     if (n_msgs <= kTableScanMax) return work_bytes <= spbox_one_pass_bytes() / 2 * 3;
@@ -257,30 +293,35 @@ hipError_t launch_batch_table(const tdes_msg *msgs, size_t n_msgs, const uint32_
                               size_t n_schedules, const uint8_t *in, uint8_t *out, BatchBounds bb,
                               uint64_t work_bytes, uint64_t *ws, uint64_t *skipped_out,
                               hipStream_t stream) {
-    // Lanes per workgroup and step: the work evenly over the CUs, one workgroup
-    // each, in as few steps as 1,024 lanes allow (the lookups of a step take LDS
-    // time by the lane: 2.1 MB, a little over one step of 1,024 lanes, take 21
-    // us in two even steps and 20 where one workgroup makes a second full step).
-    // Where lanes go by blocks, no more than kRows messages of the batch's mean
-    // length hold: each kRows messages more cost a pass.  Any grid is correct.
+    // Blocks per workgroup and step: the work evenly over the CUs, one workgroup
+    // each, in as few steps as lanes of up to three blocks allow.  The lookups of a
+    // step take LDS time by the block, a step itself ~6 us of dependent loads, so
+    // more blocks a lane beat more steps (300 messages: 2.1 MB 21.2 -> 20.1 us, 4
+    // MiB 28.4 -> 27.1, 6 MiB 39.8 -> 37.3), and even steps beat full ones with a
+    // small last one (2.1 MB 25.5 -> 21.4).  No more than kRows messages of the
+    // batch's mean length hold: each kRows messages more cost a pass.  Where lanes
+    // go by slices, one block a lane.  Any grid is correct.
     const bool scan = n_msgs <= kTableScanMax;
     const uint64_t cus = device_cus();
     const uint64_t work = work_bytes / 8 + (scan ? 0 : n_msgs * (kSlice / 8));
     const uint64_t fit = scan ? work * kRows / n_msgs : kThreads;
-    const uint64_t steps = work / (cus * kThreads) + (work % (cus * kThreads) != 0);
-    uint64_t per = steps == 0 ? 1 : (work + cus * steps - 1) / (cus * steps);
-    per = (per + kWave - 1) / kWave * kWave;
-    if (per > fit) per = fit < kWave ? kWave : fit / kWave * kWave;
+    const uint64_t cu_work = (work + cus - 1) / cus;
+    const uint32_t nb = !scan || cu_work <= kThreads ? 1 : cu_work <= 2 * kThreads ? 2 : 3;
+    const uint64_t steps = (cu_work + nb * kThreads - 1) / (nb * kThreads);
+    uint64_t per = steps == 0 ? 1 : (cu_work + steps - 1) / steps;
+    const uint32_t unit = nb * kWave;
+    per = (per + unit - 1) / unit * unit;
+    if (per > fit) per = fit < unit ? unit : fit / unit * unit;
     uint64_t grid = (work + per - 1) / per;
     grid = grid < 1 ? 1 : grid > cus ? cus : grid;
-    if (scan)
-        hipLaunchKernelGGL(batch_table_kernel<true>, dim3((unsigned)grid + 1), dim3(kThreads), 0, stream,
-                           msgs, (uint32_t)n_msgs, schedules, (uint32_t)n_schedules, in, out, bb, ws,
-                           skipped_out, (uint32_t)per);
-    else
-        hipLaunchKernelGGL(batch_table_kernel<false>, dim3((unsigned)grid), dim3(kThreads), 0, stream,
-                           msgs, (uint32_t)n_msgs, schedules, (uint32_t)n_schedules, in, out, bb, ws,
-                           skipped_out, (uint32_t)per);
+    auto launch = [&](auto kernel, uint64_t g) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)g), dim3(kThreads), 0, stream, msgs, (uint32_t)n_msgs,
+                           schedules, (uint32_t)n_schedules, in, out, bb, ws, skipped_out, (uint32_t)per);
+    };
+    if (!scan) launch(batch_table_kernel<false, 1>, grid);
+    else if (nb == 1) launch(batch_table_kernel<true, 1>, grid + 1);
+    else if (nb == 2) launch(batch_table_kernel<true, 2>, grid + 1);
+    else launch(batch_table_kernel<true, 3>, grid + 1);
     return hipGetLastError();
 }
 

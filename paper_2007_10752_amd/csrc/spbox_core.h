@@ -51,10 +51,10 @@ __device__ __forceinline__ uint32_t round_step(uint32_t L, uint32_t R, const uin
 }
 
 // IP, the 48 rounds and FP of N blocks at once, in place, interleaved so that
-// one block's LDS reads wait while the others compute.
+// one block's LDS reads wait while the others compute.  rk[i]: block i's keys.
 template <int N>
 __device__ __forceinline__ void cipher_blocks(uint2 (&w)[N], const uint8_t *sp, uint32_t lane,
-                                              uint32_t mask, const uint4 *rk) {
+                                              uint32_t mask, const uint4 *const (&rk)[N]) {
     uint32_t X[N], Y[N];
 #pragma unroll
     for (int i = 0; i < N; i++) SP_IP(w[i].x, w[i].y, X[i], Y[i]);
@@ -62,25 +62,25 @@ __device__ __forceinline__ void cipher_blocks(uint2 (&w)[N], const uint8_t *sp, 
 #pragma unroll 2
     for (int r = 0; r < 16; r += 2) {
 #pragma unroll
-        for (int i = 0; i < N; i++) X[i] = round_step(X[i], Y[i], sp, lane, mask, rk[r]);
+        for (int i = 0; i < N; i++) X[i] = round_step(X[i], Y[i], sp, lane, mask, rk[i][r]);
 #pragma unroll
-        for (int i = 0; i < N; i++) Y[i] = round_step(Y[i], X[i], sp, lane, mask, rk[r + 1]);
+        for (int i = 0; i < N; i++) Y[i] = round_step(Y[i], X[i], sp, lane, mask, rk[i][r + 1]);
     }
     // Pass 2 from R16 || L16: L = Y, R = X.
 #pragma unroll 2
     for (int r = 16; r < 32; r += 2) {
 #pragma unroll
-        for (int i = 0; i < N; i++) Y[i] = round_step(Y[i], X[i], sp, lane, mask, rk[r]);
+        for (int i = 0; i < N; i++) Y[i] = round_step(Y[i], X[i], sp, lane, mask, rk[i][r]);
 #pragma unroll
-        for (int i = 0; i < N; i++) X[i] = round_step(X[i], Y[i], sp, lane, mask, rk[r + 1]);
+        for (int i = 0; i < N; i++) X[i] = round_step(X[i], Y[i], sp, lane, mask, rk[i][r + 1]);
     }
     // Pass 3: L = X, R = Y.
 #pragma unroll 2
     for (int r = 32; r < 48; r += 2) {
 #pragma unroll
-        for (int i = 0; i < N; i++) X[i] = round_step(X[i], Y[i], sp, lane, mask, rk[r]);
+        for (int i = 0; i < N; i++) X[i] = round_step(X[i], Y[i], sp, lane, mask, rk[i][r]);
 #pragma unroll
-        for (int i = 0; i < N; i++) Y[i] = round_step(Y[i], X[i], sp, lane, mask, rk[r + 1]);
+        for (int i = 0; i < N; i++) Y[i] = round_step(Y[i], X[i], sp, lane, mask, rk[i][r + 1]);
     }
 #pragma unroll
     for (int i = 0; i < N; i++) {
@@ -88,6 +88,16 @@ __device__ __forceinline__ void cipher_blocks(uint2 (&w)[N], const uint8_t *sp, 
         SP_FP(X[i], Y[i], o0, o1);  // preoutput R16 || L16 = Y || X
         w[i] = make_uint2(o0, o1);
     }
+}
+
+// The same with one key.
+template <int N>
+__device__ __forceinline__ void cipher_blocks(uint2 (&w)[N], const uint8_t *sp, uint32_t lane,
+                                              uint32_t mask, const uint4 *rk) {
+    const uint4 *rks[N];
+#pragma unroll
+    for (int i = 0; i < N; i++) rks[i] = rk;
+    cipher_blocks<N>(w, sp, lane, mask, rks);
 }
 
 // The workgroup's tables; no barrier.

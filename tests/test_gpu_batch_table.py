@@ -78,3 +78,36 @@ def test_table_and_bitsliced_batches(kind):
             assert int(skipped.item()) == (bad is not None)
             assert np.array_equal(out.cpu().numpy()[:total], want), cfg
     T.batch_set_config(8, 4, 2)
+
+
+@pytest.mark.parametrize("n, blocks_per_cu", [(3, 1023), (40, 1025), (300, 2049), (2048, 1100), (5, 3072)])
+def test_several_blocks_a_lane(n, blocks_per_cu):
+    # Around the sizes at which a lane takes one, two or three blocks of a batch.
+    # (The oracle checks each message's ends and a part in its middle, the plain
+    # kernel the whole of it.)
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    total = 8 * (blocks_per_cu * cus - 3)
+    g = W.rng(W.SEED_BASE + 0x3B0 + n)
+    cuts = np.sort(g.choice(total // 8 - 1, size=n - 1, replace=False) + 1)
+    starts = np.concatenate([[0], cuts]).astype(np.int64) * 8
+    lengths = np.diff(np.concatenate([starts, [total]]))
+    keys, dirs = W.key_bundles(g, n), g.integers(0, 2, size=n).astype(np.uint32)
+    data = W.uniform_bytes(g, total)
+    x = torch.from_numpy(data).cuda()
+    out, ref = torch.full_like(x, 0xA5), torch.empty_like(x)
+    b = T.Batch(keys, starts, starts, lengths, dirs)
+    b.submit(x, out)
+    for i in range(n):
+        seg = slice(int(starts[i]), int(starts[i] + lengths[i]))
+        T.ecb(bytes(keys[i]), x[seg], ref[seg], decrypt=bool(dirs[i]), kernel="bitslice")
+    torch.cuda.synchronize()
+    assert b.skipped() == 0
+    assert torch.equal(out, ref)
+    got = out.cpu().numpy()
+    for i in g.choice(n, size=min(n, 24), replace=False):
+        for at in (0, int(lengths[i]) // 16 * 8, max(0, int(lengths[i]) - 64)):
+            seg = slice(int(starts[i]) + at, int(starts[i]) + min(at + 64, int(lengths[i])))
+            assert np.array_equal(got[seg], oracle.tdes_ecb(keys[i], data[seg], bool(dirs[i]))), (i, at)
