@@ -27,7 +27,7 @@
 #include "bitslice_core.h"
 #include "internal.h"
 #include "keysched_device.h"
-#include "lds_masks.h"
+#include "key_masks.h"
 
 // The compiled variants of the batched cipher, X(KMAX, WAVES): KMAX
 // messages of a wave share the LDS mask table; WAVES waves per SIMD is
@@ -342,82 +342,13 @@ struct TableRounds {
     }
 };
 
-// Key masks of a wave over more than KMAX messages: every lane widens the bits
-// of its own message's two key words of a round, 48 v_bfe_i32 a round (which do
-// not pair) in place of the table's rows.  It replaces one pass of the rounds per
-// KMAX messages, 8 where every lane holds its own (us a submit, passes -> this:
-// 2,000 messages of 72 bytes 299 -> 41, 4,000 of 1,000 bytes 120 -> 41, 16,000 of
-// 2 KiB 139 -> 91, 16,384 log-normal around 4 KiB 160 -> 157).
-struct LaneWords {  // a round's key words and the place (8 a box) of the masks meant
-    uint2 w;
-    int at;
-    __device__ __forceinline__ LaneWords operator+(int k) const { return LaneWords{w, at + k}; }
-};
-struct LaneMasks {
-    // (p.at and n are constants after inlining)
-    __device__ __forceinline__ void operator()(BsBoxMasks &m, LaneWords p, int n) const {
-        const int j = p.at / kBsBoxMasks;
-#pragma unroll
-        for (int q = 0; q < 4; q++)
-            m.o[q] = (uint32_t)__builtin_amdgcn_sbfe((int)p.w.x, (uint32_t)(4 * j + q), 1);
-#pragma unroll
-        for (int i = 0; i < 4; i++)
-            if (i < n)
-                m.e[i] = (uint32_t)__builtin_amdgcn_sbfe((int)p.w.y, (uint32_t)kBsBoxDup[4 * j + i], 1);
-    }
-};
-// Key masks of a wave inside one message: the words are uniform, and so are the
-// masks, which stay in scalar registers (an operand from there keeps an operation
-// from pairing, but there is no table to build and read: 64 messages of 800 KB 78 ->
-// 71 us a submit, 3,000 of 40 KB 157 -> 149; 16,384 of 4 KiB the same, 152).
-struct ScalarRounds {
-    const uint32_t *words;  // the message: the 100 words of its direction (uniform)
-    uint2 cur, next;
-    BsBoxMasks pm[8];
-    __device__ __forceinline__ uint2 load(int t) const { return make_uint2(words[2 * t], words[2 * t + 1]); }
-    __device__ __forceinline__ void start() {
-        cur = load(0);
-        next = load(1);
-        LaneMasks{}(pm[0], LaneWords{cur, 0}, BS_BOX_NDUP[0]);
-    }
-    template <int PH>
-    __device__ __forceinline__ void round(uint32_t (&d)[32], const uint32_t (&r)[32], int t) {
-        const uint2 after = load(t + 2);  // past round 47: the extra words, not used
-        bs_round_piped<1>(d, r, LaneWords{cur, 0}, LaneWords{next, 0}, pm, LaneMasks{});
-        cur = next;
-        next = after;
-    }
-    __device__ __forceinline__ void extra(int g, uint32_t (&a)[32]) const {
-        const uint32_t w = words[96 + g];
-#pragma unroll
-        for (int i = 0; i < 32; i++) a[i] ^= (uint32_t)__builtin_amdgcn_sbfe((int)w, (uint32_t)i, 1);
-    }
-};
-struct LaneRounds {
-    const uint32_t *words;  // the lane's message: the 100 words of its direction
-    uint2 cur, next;        // key words of this round and the next
-    BsBoxMasks pm[8];
-    __device__ __forceinline__ uint2 load(int t) const {
-        return *reinterpret_cast<const uint2 *>(words + 2 * t);
-    }
-    __device__ __forceinline__ void start() {
-        cur = load(0);
-        next = load(1);
-        LaneMasks{}(pm[0], LaneWords{cur, 0}, BS_BOX_NDUP[0]);
-    }
-    template <int PH>
-    __device__ __forceinline__ void round(uint32_t (&d)[32], const uint32_t (&r)[32], int t) {
-        const uint2 after = load(t + 2);  // past round 47: the extra words, not used
-        bs_round_piped<1>(d, r, LaneWords{cur, 0}, LaneWords{next, 0}, pm, LaneMasks{});
-        cur = next;
-        next = after;
-    }
-    __device__ __forceinline__ void extra(int g, uint32_t (&a)[32]) const {
-        const uint32_t w = words[96 + g];
-#pragma unroll
-        for (int i = 0; i < 32; i++) a[i] ^= (uint32_t)__builtin_amdgcn_sbfe((int)w, (uint32_t)i, 1);
-    }
-};
+// A wave over more than KMAX messages has no table: every lane widens its own
+// message's key words (WordRounds), 48 v_bfe_i32 a round, which do not pair, in place
+// of one pass of the rounds per KMAX messages (us a submit, passes -> this: 2,000
+// messages of 72 bytes 299 -> 41, 4,000 of 1,000 bytes 120 -> 41, 16,000 of 2 KiB 139
+// -> 91, 16,384 log-normal around 4 KiB 160 -> 157).  Nor has a wave inside one
+// message, whose words are uniform and whose masks stay in scalar registers (64
+// messages of 800 KB 78 -> 71, 3,000 of 40 KB 157 -> 149; 16,384 of 4 KiB the same).
 
 // A lane's slice between the lookup and the cipher phases of a pass: kept in
 // LDS (volatile, so the compiler cannot forward it in registers), so that
@@ -607,13 +538,13 @@ void batch_bitslice_kernel(const tdes_msg *__restrict__ msgs, uint32_t n_msgs,
             };
             if (K == 0)
                 cipher([&] {
-                    LaneRounds rr;
+                    WordRounds rr;
                     rr.words = sched + *(lds_vu32 *)&mine_ls->row;
                     return rr;
                 });
             else if (K == 1)
                 cipher([&] {
-                    ScalarRounds rr;
+                    WordRounds rr;
                     rr.words = sched + ((__builtin_amdgcn_readfirstlane(woff) >> 2) & ~1u);  // (lane 0's)
                     return rr;
                 });

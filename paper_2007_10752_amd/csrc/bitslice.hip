@@ -29,23 +29,24 @@
 // loaded blocks, then XORs each with the ciphertext block before it (the
 // IV before the first), re-read after the rounds.
 //
-// Bound by VALU issue: 92 % of the SIMDs' issue slots are busy on 1 GiB, with
-// 0.875 of the instructions issued in pairs, at ~1.93 GHz under load.  1 GiB by
-// the operations of a round, each pair on one machine: 242 (196 S-box gates) 1,083
-// us, 224 (176 gates) 1,028; 224 1,066 us, 211 (163 gates) 1,015.
-// Two waves a workgroup, masks one S-box ahead, or a 5-wave register budget: no
-// faster (1,016-1,026 us where this took 1,013-1,020).
+// Bound by VALU issue: an instruction takes 2.2 clocks of its SIMD on 1 GiB, 2.0
+// where every one pairs with another wave's.  1 GiB by the operations of a round,
+// each pair on one machine: 242 (196 S-box gates) 1,083 us, 224 (176 gates) 1,028;
+// 224 1,066 us, 211 (163 gates) 1,015.  The key masks are scalars, widened from the
+// key words by scalar instructions.  Read from a table in LDS, 17 reads a round
+// (vector operands, which were thought to pair where scalar ones do not), they cost
+// issue slots: 1 GiB 986 -> 918 us, 64 MiB 69.2 -> 64.8, CTR of 256 MiB 255 -> 239,
+// CBC decryption 264 -> 248.  Workgroups of one wave or two: the same at most sizes
+// (48 MiB: 59 us with two, 50 with one or four); of eight: 36 MiB 58 to 48.  A 6-wave
+// register budget: 64 MiB 68 to 66.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include "bitslice_core.h"
-#include "lds_masks.h"
+#include "key_masks.h"
 #include "generated/bitslice_keys_gen.h"
 #include "internal.h"
 
-#ifndef TDES_CTR_MIN_WAVES
-#define TDES_CTR_MIN_WAVES 5  // CTR's and CBC's budget (a few spills between the passes)
-#endif
 #ifndef TDES_BS_MIN_WAVES
 #define TDES_BS_MIN_WAVES 4  // waves per SIMD the register budget must allow
 #endif
@@ -150,18 +151,17 @@ __device__ __forceinline__ void xor_store_blocks(const uint32_t (&h0)[32], const
     }
 }
 
-// ECB fits 5 waves per SIMD (96 registers) at the budget of 4; the other
-// modes need the 5-wave budget asked for explicitly.
+// Every mode takes 84-89 registers (5 waves per SIMD).
 template <bool VEC16, int MODE>
 __global__ __launch_bounds__(kWave *kWavesPerBlock)
-__attribute__((amdgpu_waves_per_eu(MODE == kModeEcb ? TDES_BS_MIN_WAVES : TDES_CTR_MIN_WAVES, 8)))
+__attribute__((amdgpu_waves_per_eu(TDES_BS_MIN_WAVES, 8)))
 void tdes_bitslice_kernel(const uint8_t *in, uint8_t *out, size_t nbytes, BitsliceKeys keys,
                           ModeArgs mode) {
-    // Issue priority: a new wave's loads, mask expansion and transposes run
-    // at the highest priority and its rounds at the lowest.  The SIMD's
-    // arbiter otherwise favours the older waves, which are in their rounds,
-    // so a new wave reaches its own rounds late and fewer waves are there to
-    // pair instructions (measured: 6-9 % faster).
+    // Issue priority: a new wave's loads and transposes run at the highest
+    // priority and its rounds at the lowest.  The SIMD's arbiter otherwise
+    // favours the older waves, which are in their rounds, so a new wave
+    // reaches its own rounds late and fewer waves are there to pair
+    // instructions (1 GiB 872 us, 928 without).
     __builtin_amdgcn_s_setprio(3);
     // the wave index is uniform within the wave; say so, so the chunk base
     // and the buffer resources below live in scalar registers
@@ -185,7 +185,7 @@ void tdes_bitslice_kernel(const uint8_t *in, uint8_t *out, size_t nbytes, Bitsli
     const __amdgpu_buffer_rsrc_t dst =
         __builtin_amdgcn_make_buffer_rsrc((void *)(out + base), 0, (int)avail, kBufferFlags);
 
-    // Request the chunk: its memory latency overlaps the mask expansion.
+    // the chunk
     uint32_t h0[32], h1[32];
     if (MODE == kModeCtr) {
         if (live) {
@@ -222,30 +222,6 @@ void tdes_bitslice_kernel(const uint8_t *in, uint8_t *out, size_t nbytes, Bitsli
         }
     }
 
-    // Expand the launch's key masks (bits) into 0 / ~0 words in LDS.  A
-    // round's 64 words are one per lane: lane l is slot l % 8 of S-box l / 8,
-    // slot q < 4 bit 4j + q of word 2t (output XOR masks), slot 4 + i bit
-    // kBsBoxDup[4j + i] of word 2t + 1 (second uses).  Wave w builds rounds
-    // w, w + 4, ...; its key words are uniform, read with scalar loads.  Past
-    // the 48 rounds the pipeline requests kBsBoxMasks * TDES_BS_PIPE words
-    // that are never used; they fall inside the extra groups.
-    static_assert(kBsBoxMasks == 8 && kBsRoundMasks == kWave && kWavesPerBlock == 4, "mask layout");
-    static_assert(kBsNumMasks - kBsInitY >= kBsBoxMasks * TDES_BS_PIPE, "mask pipeline overrun");
-    __shared__ __align__(16) uint32_t km[kBsNumMasks];
-    {
-        const int lane = threadIdx.x % kWave;
-        const RoundMaskLane rml(lane);
-#pragma unroll
-        for (int r = 0; r < 48 / kWavesPerBlock; r++) {
-            const int t = (int)wave + kWavesPerBlock * r;
-            // both words as scalars (read once per wave), then a per-lane pick
-            km[kBsRoundMasks * t + lane] = rml(__builtin_amdgcn_readfirstlane(keys.w[2 * t]),
-                                               __builtin_amdgcn_readfirstlane(keys.w[2 * t + 1]));
-        }
-        // extra group g = w, entry n = lane < 32: bit n of word 96 + g
-        if (lane < 32) km[kBsInitY + 32 * wave + lane] = 0u - ((keys.w[96 + wave] >> lane) & 1u);
-    }
-    __syncthreads();
     if (!live) return;
 
     // one transpose at a time: interleaved, they hold more words live than
@@ -255,9 +231,9 @@ void tdes_bitslice_kernel(const uint8_t *in, uint8_t *out, size_t nbytes, Bitsli
     transpose32(h1);
     __builtin_amdgcn_sched_barrier(0);
 
-    const uint32_t *kml = km;
     __builtin_amdgcn_s_setprio(0);
-    LdsPipedRounds rr{kml};
+    WordRounds rr;
+    rr.words = keys.w;
     des3_planes(h0, h1, rr);
     __builtin_amdgcn_sched_barrier(0);
     transpose32(h0);

@@ -88,38 +88,6 @@ __device__ __forceinline__ void transpose32(uint32_t (&x)[32]) {
 // rounds 16 and 32, final unmask of X.
 enum { kGroupInitY = 0, kGroupRemask16 = 1, kGroupRemask32 = 2, kGroupFinalX = 3 };
 
-// Round masks fetched a whole round at a time: rm.load(t) fetches what
-// round t needs and rm.masks(v) turns it into the mask source bs_round reads.
-// Fetches are issued two rounds ahead, so memory latency overlaps the two
-// rounds before.  em(g, i) gives mask i of extra group g.
-template <class RoundMasks, class ExtraMasks>
-struct PrefetchRounds {
-    RoundMasks rm;
-    ExtraMasks em;
-    decltype(rm.load(0)) buf[2];
-    __device__ __forceinline__ void start() {
-        buf[0] = rm.load(0);
-        buf[1] = rm.load(1);
-    }
-    // PH = t % 2, known at compile time so buf stays in registers
-    template <int PH>
-    __device__ __forceinline__ void round(uint32_t (&d)[32], const uint32_t (&r)[32], int t) {
-        const auto next = rm.load(t + 2);  // past round 47: harmless, unused
-        bs_round(d, r, rm.masks(buf[PH]));
-        buf[PH] = next;
-    }
-    __device__ __forceinline__ void extra(int g, uint32_t (&a)[32]) const {
-#pragma unroll
-        for (int i = 0; i < 32; i++) a[i] ^= em(g, i);
-    }
-};
-
-template <class RoundMasks, class ExtraMasks>
-__device__ __forceinline__ PrefetchRounds<RoundMasks, ExtraMasks> prefetch_rounds(
-    const RoundMasks &rm, const ExtraMasks &em) {
-    return PrefetchRounds<RoundMasks, ExtraMasks>{rm, em, {}};
-}
-
 // 3DES-EDE on 32 blocks held as planes h0 (word 0) and h1 (word 1), in
 // place.  rr runs the rounds: rr.start() once, then rr.round<t % 2>(d, r, t)
 // for t = 0..47 (d ^= f(r, K_t)); rr.extra(g, a) XORs extra mask group g
