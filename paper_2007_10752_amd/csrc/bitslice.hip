@@ -32,7 +32,8 @@
 // Bound by VALU issue: an instruction takes 2.2 clocks of its SIMD on 1 GiB, 2.0
 // where every one pairs with another wave's.  1 GiB by the operations of a round,
 // each pair on one machine: 242 (196 S-box gates) 1,083 us, 224 (176 gates) 1,028;
-// 224 1,066 us, 211 (163 gates) 1,015.  The key masks are scalars, widened from the
+// 224 1,066 us, 211 (163 gates) 1,015; 211 919, 202 (159 gates, five of the sixteen
+// second-use masks folded into them) 892.  The key masks are scalars, widened from the
 // key words by scalar instructions.  Read from a table in LDS, 17 reads a round
 // (vector operands, which were thought to pair where scalar ones do not), they cost
 // issue slots: 1 GiB 986 -> 918 us, 64 MiB 69.2 -> 64.8, CTR of 256 MiB 255 -> 239,

@@ -21,282 +21,12 @@ static constexpr int BS_FP_SRC[64] = {
     25, 57, 17, 49, 9, 41, 1, 33, 24, 56, 16, 48, 8, 40, 0, 32,
 };
 
-// S-box gate counts: S1=23, S2=20, S3=22, S4=15, S5=23, S6=22, S7=20, S8=18 (total 163 per round)
-#define BS_SBOX_GATES_PER_ROUND 163
+// S-box gate counts: S1=23, S2=19, S3=21, S4=15, S5=22, S6=21, S7=20, S8=18 (total 159 per round)
+#define BS_SBOX_GATES_PER_ROUND 159
 // XORs per round: 32 of S-box outputs into the other half, and the second
-// uses whose masks are not folded into the gates (0 of 16 are)
-#define BS_XORS_PER_ROUND 48
+// uses whose masks are not folded into the gates (5 of 16 are)
+#define BS_XORS_PER_ROUND 43
 
-// One Feistel round on 32 blocks per lane (Sec. III-B): d ^= P(S(E(r) ^ K)).
-// The halves are stored XORed with key masks: each word of r already
-// carries the round-key bit of its primary expansion position, so only
-// second uses need their mask (km(32 + k)): XORed in, or taken as the third
-// operand of the gates that read the input; km(4*box + q) re-masks the
-// updated word of d for its next use, folded into the output XOR.
-// km(i) returns mask i of the round (0 or ~0): km(4*box + q), km(32 + k).
-template <class KM>
-__device__ __forceinline__ void bs_round(uint32_t (&d)[32], const uint32_t (&r)[32],
-                                         const KM &km) {
-    {  // S1
-        const uint32_t x0 = r[31];
-        const uint32_t x1 = r[0];
-        const uint32_t x2 = r[1];
-        const uint32_t x3 = r[2];
-        const uint32_t x4 = r[3];
-        const uint32_t x5 = r[4] ^ km(32);
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x2, x3, 0x96);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x2, x5, g6, 0x46);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x4, g6, g7, 0x1a);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x3, g6, g8, 0xab);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x0, x3, x4, 0x43);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x5, g9, g10, 0xdc);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x2, x3, g11, 0x40);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x1, g10, g12, 0x2f);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x3, g11, g13, 0x48);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(g8, g9, g14, 0x79);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x1, g8, g10, 0xc9);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x4, g6, g15, 0x2c);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x2, x5, g17, 0x6a);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(g12, g16, g18, 0x3e);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g9, g15, g19, 0x38);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(g13, g16, g17, 0x38);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(g7, g19, g21, 0x49);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(g8, g13, g18, 0xc6);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(g11, g19, g23, 0x89);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(x4, g14, g24, 0xa7);
-        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(g8, g14, g25, 0x8f);
-        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g22, g23, g25, 0xc7);
-        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(x1, g26, g27, 0x69);
-        d[8] = __builtin_amdgcn_bitop3_b32(d[8], g20, km(0), 0x69);
-        d[16] = __builtin_amdgcn_bitop3_b32(d[16], g22, km(1), 0x69);
-        d[22] = __builtin_amdgcn_bitop3_b32(d[22], g24, km(2), 0x69);
-        d[30] = __builtin_amdgcn_bitop3_b32(d[30], g28, km(3), 0x96);
-    }
-    {  // S2
-        const uint32_t x0 = r[3] ^ km(33);
-        const uint32_t x1 = r[4];
-        const uint32_t x2 = r[5];
-        const uint32_t x3 = r[6];
-        const uint32_t x4 = r[7];
-        const uint32_t x5 = r[8];
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x1, x4, 0xd3);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x4, x5, g6, 0xd7);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x1, x5, g7, 0xf9);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x0, x5, g8, 0x96);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x2, x5, g6, 0xb4);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x2, g8, g9, 0x4d);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x3, g7, g11, 0x4b);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(g8, g10, g12, 0x93);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x4, g9, g13, 0x96);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x5, g6, g13, 0x26);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x5, g14, g15, 0x47);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(g8, g12, g16, 0x63);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x5, g10, g12, 0xb0);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x1, x4, g18, 0x4b);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g7, g14, g15, 0x21);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(g17, g19, g20, 0x69);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x0, g16, g17, 0x94);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x5, g17, g22, 0xac);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(g17, g21, g23, 0xae);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g7, g15, g24, 0x96);
-        d[12] = __builtin_amdgcn_bitop3_b32(d[12], g14, km(4), 0x96);
-        d[27] = __builtin_amdgcn_bitop3_b32(d[27], g21, km(5), 0x69);
-        d[1] = __builtin_amdgcn_bitop3_b32(d[1], g25, km(6), 0x96);
-        d[17] = __builtin_amdgcn_bitop3_b32(d[17], g17, km(7), 0x69);
-    }
-    {  // S3
-        const uint32_t x0 = r[7] ^ km(34);
-        const uint32_t x1 = r[8] ^ km(35);
-        const uint32_t x2 = r[9];
-        const uint32_t x3 = r[10];
-        const uint32_t x4 = r[11];
-        const uint32_t x5 = r[12] ^ km(36);
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x1, x4, x5, 0x96);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x0, x2, g6, 0x69);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x5, g6, g7, 0xc5);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x2, x4, g8, 0x87);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x1, g7, g9, 0xc6);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x3, x4, g9, 0x5a);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x4, g7, g11, 0x39);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x5, g11, g12, 0xc6);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x1, g12, g13, 0x9c);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x0, g9, g14, 0xf6);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x3, g10, g15, 0x39);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(g11, g14, g15, 0x6d);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x5, g8, g17, 0x1d);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x1, g7, g17, 0xd9);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x0, g12, g19, 0x29);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x3, g18, g20, 0x17);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x2, g12, g21, 0x69);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x5, g10, g13, 0xd9);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x0, g12, g23, 0x9c);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(x4, g16, g21, 0x96);
-        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(x2, g24, g25, 0x6d);
-        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g9, g19, g26, 0x8d);
-        d[23] = __builtin_amdgcn_bitop3_b32(d[23], g16, km(8), 0x96);
-        d[15] = __builtin_amdgcn_bitop3_b32(d[15], g22, km(9), 0x69);
-        d[29] = __builtin_amdgcn_bitop3_b32(d[29], g27, km(10), 0x96);
-        d[5] = __builtin_amdgcn_bitop3_b32(d[5], g24, km(11), 0x69);
-    }
-    {  // S4
-        const uint32_t x0 = r[11] ^ km(37);
-        const uint32_t x1 = r[12];
-        const uint32_t x2 = r[13];
-        const uint32_t x3 = r[14];
-        const uint32_t x4 = r[15];
-        const uint32_t x5 = r[16];
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x2, x3, x4, 0xbd);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x0, x4, g6, 0xc3);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x1, g7, g6, 0x97);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x0, x2, g8, 0x69);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x1, g8, g9, 0xd6);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x4, g8, g10, 0x87);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(g7, g6, g10, 0xa3);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x3, g9, g12, 0x39);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x1, x3, g11, 0xe8);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x5, g13, g14, 0x9a);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x1, g12, g15, 0x66);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x5, g13, g16, 0x69);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x3, x5, g12, 0x1e);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(g11, g17, g18, 0x69);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g15, g17, g19, 0x69);
-        d[25] = __builtin_amdgcn_bitop3_b32(d[25], g19, km(12), 0x96);
-        d[19] = __builtin_amdgcn_bitop3_b32(d[19], g20, km(13), 0x69);
-        d[9] = __builtin_amdgcn_bitop3_b32(d[9], g17, km(14), 0x96);
-        d[0] = __builtin_amdgcn_bitop3_b32(d[0], g16, km(15), 0x96);
-    }
-    {  // S5
-        const uint32_t x0 = r[15] ^ km(38);
-        const uint32_t x1 = r[16] ^ km(39);
-        const uint32_t x2 = r[17];
-        const uint32_t x3 = r[18];
-        const uint32_t x4 = r[19];
-        const uint32_t x5 = r[20];
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x1, x4, 0x4a);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x1, x3, x4, 0x65);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x2, g6, g7, 0xb5);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x0, x3, g7, 0x6c);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x1, x5, g9, 0x69);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x1, x5, g6, 0x21);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x2, x3, g11, 0x12);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(g8, g10, g12, 0x63);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x2, g6, g8, 0xb9);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x5, g6, g14, 0x83);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x3, x4, g15, 0x69);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(g10, g15, g16, 0x35);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(g9, g14, g16, 0xb8);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x0, x4, g8, 0x47);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g13, g18, g19, 0x93);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x0, g14, g20, 0x79);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(g21, g20, g10, 0xc9);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x4, g7, g22, 0x79);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x2, x5, g23, 0xe1);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g9, g17, g24, 0x96);
-        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(x1, g6, g20, 0x8d);
-        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g23, g24, g26, 0x54);
-        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(g13, g25, g27, 0x96);
-        d[7] = __builtin_amdgcn_bitop3_b32(d[7], g28, km(16), 0x69);
-        d[13] = __builtin_amdgcn_bitop3_b32(d[13], g13, km(17), 0x96);
-        d[24] = __builtin_amdgcn_bitop3_b32(d[24], g25, km(18), 0x69);
-        d[2] = __builtin_amdgcn_bitop3_b32(d[2], g20, km(19), 0x69);
-    }
-    {  // S6
-        const uint32_t x0 = r[19] ^ km(40);
-        const uint32_t x1 = r[20] ^ km(41);
-        const uint32_t x2 = r[21];
-        const uint32_t x3 = r[22];
-        const uint32_t x4 = r[23];
-        const uint32_t x5 = r[24];
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x2, x4, x5, 0x64);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x0, x2, g6, 0xbc);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x5, g6, g7, 0x0e);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x0, x1, g6, 0xb6);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x0, x1, g7, 0xd7);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x2, x5, g10, 0xa4);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x0, g9, g11, 0x85);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(g7, g8, g12, 0xb6);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x3, g10, g13, 0x4b);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x4, g9, g14, 0x7a);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x5, g9, g11, 0x8f);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x4, g15, g16, 0xe9);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x2, g14, g17, 0x72);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(g8, g9, g18, 0x69);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x2, g15, g16, 0x96);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x4, x5, g19, 0x16);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x3, g6, g21, 0x6f);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x4, g12, g22, 0x96);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x1, g13, g23, 0xe1);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g12, g14, g23, 0x83);
-        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(g19, g24, g25, 0x39);
-        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g20, g23, g26, 0x96);
-        d[3] = __builtin_amdgcn_bitop3_b32(d[3], g19, km(20), 0x96);
-        d[28] = __builtin_amdgcn_bitop3_b32(d[28], g27, km(21), 0x96);
-        d[10] = __builtin_amdgcn_bitop3_b32(d[10], g20, km(22), 0x96);
-        d[18] = __builtin_amdgcn_bitop3_b32(d[18], g23, km(23), 0x96);
-    }
-    {  // S7
-        const uint32_t x0 = r[23] ^ km(42);
-        const uint32_t x1 = r[24] ^ km(43);
-        const uint32_t x2 = r[25];
-        const uint32_t x3 = r[26];
-        const uint32_t x4 = r[27];
-        const uint32_t x5 = r[28];
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x1, x3, x5, 0x93);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x1, x5, g6, 0xa9);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x2, x3, g6, 0x68);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x1, x3, x4, 0xb4);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x2, x3, g9, 0xb7);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(g7, g8, g10, 0x78);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(g7, g8, g9, 0xe1);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x2, x5, g12, 0x3b);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x0, g9, g13, 0xbf);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x0, x2, x5, 0x96);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(g6, g11, g15, 0xd1);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x0, g12, g16, 0x69);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(g6, g11, g17, 0x78);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(g14, g17, g18, 0x59);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g13, g10, g19, 0x09);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x1, x4, g16, 0x69);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x0, g21, g18, 0x4c);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(g11, g20, g22, 0x69);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(g13, g19, g23, 0x9c);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g17, g21, g14, 0x2d);
-        d[31] = __builtin_amdgcn_bitop3_b32(d[31], g23, km(24), 0x69);
-        d[11] = __builtin_amdgcn_bitop3_b32(d[11], g21, km(25), 0x69);
-        d[21] = __builtin_amdgcn_bitop3_b32(d[21], g24, km(26), 0x96);
-        d[6] = __builtin_amdgcn_bitop3_b32(d[6], g25, km(27), 0x69);
-    }
-    {  // S8
-        const uint32_t x0 = r[27] ^ km(44);
-        const uint32_t x1 = r[28] ^ km(45);
-        const uint32_t x2 = r[29];
-        const uint32_t x3 = r[30];
-        const uint32_t x4 = r[31] ^ km(46);
-        const uint32_t x5 = r[0] ^ km(47);
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x3, x5, 0xaf);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x1, x4, g6, 0xf2);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x2, x3, g7, 0xd2);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x1, x4, g8, 0xc9);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x0, x1, g8, 0x86);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x3, g9, g10, 0x4b);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x0, x1, g11, 0x93);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x4, g8, g12, 0xc9);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x5, g11, g13, 0xea);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x1, x4, g14, 0xc9);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x0, g11, g14, 0x69);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x1, g15, g16, 0xb4);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x5, g11, g17, 0xc6);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x0, x5, g18, 0x1c);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g11, g13, g19, 0x96);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(g6, g18, g20, 0x96);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(g6, g15, g16, 0x96);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(g16, g17, g18, 0x69);
-        d[4] = __builtin_amdgcn_bitop3_b32(d[4], g21, km(28), 0x69);
-        d[26] = __builtin_amdgcn_bitop3_b32(d[26], g20, km(29), 0x69);
-        d[14] = __builtin_amdgcn_bitop3_b32(d[14], g22, km(30), 0x96);
-        d[20] = __builtin_amdgcn_bitop3_b32(d[20], g23, km(31), 0x96);
-    }
-}
 
 // Number of second-use inputs of each S-box (mask words e[] it reads).
 static constexpr int BS_BOX_NDUP[8] = {
@@ -309,9 +39,14 @@ struct BsBoxMasks {
     uint32_t o[4], e[4];
 };
 
-// bs_round with masks laid out by round and S-box (8 words per box, 64 per
-// round: o[0..3], e[0..3]) and software-pipelined D boxes ahead: before box j
-// runs, load(pm[(j + D) %% 8], q, n) requests the masks of the box D places
+// One Feistel round on 32 blocks per lane (Sec. III-B): d ^= P(S(E(r) ^ K)).
+// The halves are stored XORed with key masks: each word of r already carries the
+// round-key bit of its primary expansion position, so only second uses need their
+// mask: XORed in, or taken as the third operand of the gates that read the input;
+// the output masks re-mask the updated words of d for their next use.  Masks are
+// laid out by round and S-box (8 words per box, 64 per round: o[0..3], e[0..3])
+// and software-pipelined D boxes ahead: before box j
+// runs, load(pm[(j + D) % 8], q, n) requests the masks of the box D places
 // later, q = p + 8 * (j + D), or past the last box pn + 8 * (j + D - 8) (pn: the
 // next round's masks).
 // A scheduling barrier between boxes keeps each request and each box's
@@ -370,36 +105,35 @@ __device__ __forceinline__ void bs_round_piped(uint32_t (&d)[32], const uint32_t
              1 + D < 8 ? p + 8 * (1 + D) : pn + 8 * (1 + D - 8),
              BS_BOX_NDUP[(1 + D) % 8]);
         const BsBoxMasks &m = pm[1];
-        const uint32_t x0 = r[3] ^ m.e[0];
+        const uint32_t x0 = r[3];  // mask folded into its gates
         const uint32_t x1 = r[4];
         const uint32_t x2 = r[5];
         const uint32_t x3 = r[6];
         const uint32_t x4 = r[7];
         const uint32_t x5 = r[8];
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x1, x4, 0xd3);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x4, x5, g6, 0xd7);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x1, x5, g7, 0xf9);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x0, x5, g8, 0x96);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x2, x5, g6, 0xb4);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x2, g8, g9, 0x4d);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x3, g7, g11, 0x4b);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(g8, g10, g12, 0x93);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x4, g9, g13, 0x96);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x5, g6, g13, 0x26);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x5, g14, g15, 0x47);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(g8, g12, g16, 0x63);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x5, g10, g12, 0xb0);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x1, x4, g18, 0x4b);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g7, g14, g15, 0x21);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(g17, g19, g20, 0x69);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x0, g16, g17, 0x94);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x5, g17, g22, 0xac);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(g17, g21, g23, 0xae);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g7, g15, g24, 0x96);
+        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x5, m.e[0], 0x69);
+        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x1, x4, g6, 0x7c);
+        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x4, x5, g7, 0xd2);
+        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x1, g6, g8, 0x76);
+        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x2, x3, g8, 0x1b);
+        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x5, g7, g10, 0x7b);
+        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x2, g9, g11, 0x78);
+        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x1, x4, g10, 0x69);
+        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x3, g12, g13, 0x96);
+        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x5, g6, g14, 0x8c);
+        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x1, g7, g15, 0x2d);
+        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(g13, g15, g16, 0xc3);
+        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x5, g14, g16, 0x5e);
+        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(g10, g15, g18, 0x69);
+        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g17, g16, g19, 0x36);
+        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(g6, g14, g20, 0x24);
+        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x5, g17, g21, 0x93);
+        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x5, g15, g22, 0x2f);
+        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(g14, g20, g23, 0x69);
         d[12] = __builtin_amdgcn_bitop3_b32(d[12], g14, m.o[0], 0x96);
-        d[27] = __builtin_amdgcn_bitop3_b32(d[27], g21, m.o[1], 0x69);
-        d[1] = __builtin_amdgcn_bitop3_b32(d[1], g25, m.o[2], 0x96);
-        d[17] = __builtin_amdgcn_bitop3_b32(d[17], g17, m.o[3], 0x69);
+        d[27] = __builtin_amdgcn_bitop3_b32(d[27], g22, m.o[1], 0x96);
+        d[1] = __builtin_amdgcn_bitop3_b32(d[1], g24, m.o[2], 0x96);
+        d[17] = __builtin_amdgcn_bitop3_b32(d[17], g19, m.o[3], 0x69);
     }
     {  // S3
         __builtin_amdgcn_sched_barrier(0);
@@ -408,37 +142,36 @@ __device__ __forceinline__ void bs_round_piped(uint32_t (&d)[32], const uint32_t
              BS_BOX_NDUP[(2 + D) % 8]);
         const BsBoxMasks &m = pm[2];
         const uint32_t x0 = r[7] ^ m.e[0];
-        const uint32_t x1 = r[8] ^ m.e[1];
+        const uint32_t x1 = r[8];  // mask folded into its gates
         const uint32_t x2 = r[9];
         const uint32_t x3 = r[10];
         const uint32_t x4 = r[11];
         const uint32_t x5 = r[12] ^ m.e[2];
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x1, x4, x5, 0x96);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x0, x2, g6, 0x69);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x5, g6, g7, 0xc5);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x2, x4, g8, 0x87);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x1, g7, g9, 0xc6);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x3, x4, g9, 0x5a);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x4, g7, g11, 0x39);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x5, g11, g12, 0xc6);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x1, g12, g13, 0x9c);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x0, g9, g14, 0xf6);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x3, g10, g15, 0x39);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(g11, g14, g15, 0x6d);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x5, g8, g17, 0x1d);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x1, g7, g17, 0xd9);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x0, g12, g19, 0x29);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x3, g18, g20, 0x17);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x2, g12, g21, 0x69);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x5, g10, g13, 0xd9);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x0, g12, g23, 0x9c);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(x4, g16, g21, 0x96);
-        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(x2, g24, g25, 0x6d);
-        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g9, g19, g26, 0x8d);
-        d[23] = __builtin_amdgcn_bitop3_b32(d[23], g16, m.o[0], 0x96);
-        d[15] = __builtin_amdgcn_bitop3_b32(d[15], g22, m.o[1], 0x69);
-        d[29] = __builtin_amdgcn_bitop3_b32(d[29], g27, m.o[2], 0x96);
-        d[5] = __builtin_amdgcn_bitop3_b32(d[5], g24, m.o[3], 0x69);
+        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x3, x4, x5, 0x96);
+        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x1, x1, m.e[1], 0xa5);
+        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x0, x2, g7, 0x89);
+        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x3, x4, g7, 0x95);
+        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x2, x4, g9, 0x59);
+        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x0, g6, g10, 0x69);
+        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x3, x4, g11, 0x4e);
+        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(g6, g8, g12, 0xb3);
+        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x2, g11, g13, 0x38);
+        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x0, x5, g14, 0xf6);
+        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(g10, g11, g15, 0x1e);
+        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(g13, g14, g16, 0x61);
+        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x5, g15, g16, 0x60);
+        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x3, g14, g18, 0x9c);
+        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g6, g8, g16, 0xe2);
+        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x2, x3, g16, 0xd8);
+        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(g6, g9, g21, 0x46);
+        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(g19, g20, g22, 0x93);
+        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x5, g12, g23, 0x87);
+        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g14, g20, g24, 0x76);
+        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(x0, g11, g25, 0x9c);
+        d[23] = __builtin_amdgcn_bitop3_b32(d[23], g17, m.o[0], 0x96);
+        d[15] = __builtin_amdgcn_bitop3_b32(d[15], g19, m.o[1], 0x96);
+        d[29] = __builtin_amdgcn_bitop3_b32(d[29], g23, m.o[2], 0x69);
+        d[5] = __builtin_amdgcn_bitop3_b32(d[5], g26, m.o[3], 0x96);
     }
     {  // S4
         __builtin_amdgcn_sched_barrier(0);
@@ -446,31 +179,31 @@ __device__ __forceinline__ void bs_round_piped(uint32_t (&d)[32], const uint32_t
              3 + D < 8 ? p + 8 * (3 + D) : pn + 8 * (3 + D - 8),
              BS_BOX_NDUP[(3 + D) % 8]);
         const BsBoxMasks &m = pm[3];
-        const uint32_t x0 = r[11] ^ m.e[0];
+        const uint32_t x0 = r[11];  // mask folded into its gates
         const uint32_t x1 = r[12];
         const uint32_t x2 = r[13];
         const uint32_t x3 = r[14];
         const uint32_t x4 = r[15];
         const uint32_t x5 = r[16];
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x2, x3, x4, 0xbd);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x0, x4, g6, 0xc3);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x1, g7, g6, 0x97);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x0, x2, g8, 0x69);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x1, g8, g9, 0xd6);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x4, g8, g10, 0x87);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(g7, g6, g10, 0xa3);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x3, g9, g12, 0x39);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x1, x3, g11, 0xe8);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x5, g13, g14, 0x9a);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x1, g12, g15, 0x66);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x5, g13, g16, 0x69);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x3, x5, g12, 0x1e);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(g11, g17, g18, 0x69);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g15, g17, g19, 0x69);
-        d[25] = __builtin_amdgcn_bitop3_b32(d[25], g19, m.o[0], 0x96);
-        d[19] = __builtin_amdgcn_bitop3_b32(d[19], g20, m.o[1], 0x69);
-        d[9] = __builtin_amdgcn_bitop3_b32(d[9], g17, m.o[2], 0x96);
-        d[0] = __builtin_amdgcn_bitop3_b32(d[0], g16, m.o[3], 0x96);
+        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x2, m.e[0], 0x69);
+        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x4, x5, g6, 0x96);
+        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x2, x4, x2, 0xc3);
+        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x1, g6, g8, 0x24);
+        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x2, x3, x4, 0x99);
+        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x1, g8, g10, 0xd2);
+        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(g6, g10, g11, 0xf6);
+        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x3, g9, g12, 0x6c);
+        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(g6, g8, g10, 0x2c);
+        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(g11, g13, g14, 0xb4);
+        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(g7, g13, g15, 0xc9);
+        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x5, g16, g15, 0x69);
+        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(g7, g12, g14, 0x62);
+        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(g12, g17, g18, 0x63);
+        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g14, g16, g18, 0x69);
+        d[25] = __builtin_amdgcn_bitop3_b32(d[25], g16, m.o[0], 0x96);
+        d[19] = __builtin_amdgcn_bitop3_b32(d[19], g17, m.o[1], 0x96);
+        d[9] = __builtin_amdgcn_bitop3_b32(d[9], g19, m.o[2], 0x69);
+        d[0] = __builtin_amdgcn_bitop3_b32(d[0], g20, m.o[3], 0x69);
     }
     {  // S5
         __builtin_amdgcn_sched_barrier(0);
@@ -478,39 +211,38 @@ __device__ __forceinline__ void bs_round_piped(uint32_t (&d)[32], const uint32_t
              4 + D < 8 ? p + 8 * (4 + D) : pn + 8 * (4 + D - 8),
              BS_BOX_NDUP[(4 + D) % 8]);
         const BsBoxMasks &m = pm[4];
-        const uint32_t x0 = r[15] ^ m.e[0];
+        const uint32_t x0 = r[15];  // mask folded into its gates
         const uint32_t x1 = r[16] ^ m.e[1];
         const uint32_t x2 = r[17];
         const uint32_t x3 = r[18];
         const uint32_t x4 = r[19];
         const uint32_t x5 = r[20];
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x1, x4, 0x4a);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x1, x3, x4, 0x65);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x2, g6, g7, 0xb5);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x0, x3, g7, 0x6c);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x1, x5, g9, 0x69);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x1, x5, g6, 0x21);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x2, x3, g11, 0x12);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(g8, g10, g12, 0x63);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x2, g6, g8, 0xb9);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x5, g6, g14, 0x83);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x3, x4, g15, 0x69);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(g10, g15, g16, 0x35);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(g9, g14, g16, 0xb8);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x0, x4, g8, 0x47);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g13, g18, g19, 0x93);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x0, g14, g20, 0x79);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(g21, g20, g10, 0xc9);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x4, g7, g22, 0x79);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x2, x5, g23, 0xe1);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g9, g17, g24, 0x96);
-        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(x1, g6, g20, 0x8d);
-        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g23, g24, g26, 0x54);
-        const uint32_t g28 = __builtin_amdgcn_bitop3_b32(g13, g25, g27, 0x96);
-        d[7] = __builtin_amdgcn_bitop3_b32(d[7], g28, m.o[0], 0x69);
-        d[13] = __builtin_amdgcn_bitop3_b32(d[13], g13, m.o[1], 0x96);
-        d[24] = __builtin_amdgcn_bitop3_b32(d[24], g25, m.o[2], 0x69);
-        d[2] = __builtin_amdgcn_bitop3_b32(d[2], g20, m.o[3], 0x69);
+        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x0, m.e[0], 0xa5);
+        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x2, x3, g6, 0x4b);
+        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x3, x5, g7, 0xc2);
+        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x2, x4, g8, 0x28);
+        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x2, x4, g7, 0x62);
+        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x2, x5, g6, 0x6b);
+        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(g9, g10, g11, 0xa9);
+        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x2, x5, g12, 0x2e);
+        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x1, x4, g6, 0x96);
+        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(g11, g13, g14, 0xa3);
+        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(g15, g10, x3, 0xd8);
+        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x3, g11, g14, 0x4e);
+        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(g7, g13, g14, 0xc4);
+        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x1, g8, g16, 0x69);
+        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x4, g9, g19, 0xf6);
+        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(g17, g18, g20, 0xac);
+        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(g13, g16, g21, 0x96);
+        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x3, g10, g20, 0x29);
+        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x1, g12, g23, 0x63);
+        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g14, g21, g24, 0x62);
+        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(g13, g14, g22, 0x0e);
+        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g8, g25, g26, 0x96);
+        d[7] = __builtin_amdgcn_bitop3_b32(d[7], g22, m.o[0], 0x69);
+        d[13] = __builtin_amdgcn_bitop3_b32(d[13], g19, m.o[1], 0x69);
+        d[24] = __builtin_amdgcn_bitop3_b32(d[24], g27, m.o[2], 0x69);
+        d[2] = __builtin_amdgcn_bitop3_b32(d[2], g24, m.o[3], 0x96);
     }
     {  // S6
         __builtin_amdgcn_sched_barrier(0);
@@ -518,38 +250,37 @@ __device__ __forceinline__ void bs_round_piped(uint32_t (&d)[32], const uint32_t
              5 + D < 8 ? p + 8 * (5 + D) : pn + 8 * (5 + D - 8),
              BS_BOX_NDUP[(5 + D) % 8]);
         const BsBoxMasks &m = pm[5];
-        const uint32_t x0 = r[19] ^ m.e[0];
+        const uint32_t x0 = r[19];  // mask folded into its gates
         const uint32_t x1 = r[20] ^ m.e[1];
         const uint32_t x2 = r[21];
         const uint32_t x3 = r[22];
         const uint32_t x4 = r[23];
         const uint32_t x5 = r[24];
-        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x2, x4, x5, 0x64);
-        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x0, x2, g6, 0xbc);
-        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x5, g6, g7, 0x0e);
-        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x0, x1, g6, 0xb6);
-        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x0, x1, g7, 0xd7);
-        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x2, x5, g10, 0xa4);
-        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x0, g9, g11, 0x85);
-        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(g7, g8, g12, 0xb6);
-        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x3, g10, g13, 0x4b);
-        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x4, g9, g14, 0x7a);
-        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x5, g9, g11, 0x8f);
-        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x4, g15, g16, 0xe9);
-        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x2, g14, g17, 0x72);
-        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(g8, g9, g18, 0x69);
-        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x2, g15, g16, 0x96);
-        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x4, x5, g19, 0x16);
-        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(x3, g6, g21, 0x6f);
-        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(x4, g12, g22, 0x96);
-        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(x1, g13, g23, 0xe1);
-        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g12, g14, g23, 0x83);
-        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(g19, g24, g25, 0x39);
-        const uint32_t g27 = __builtin_amdgcn_bitop3_b32(g20, g23, g26, 0x96);
-        d[3] = __builtin_amdgcn_bitop3_b32(d[3], g19, m.o[0], 0x96);
-        d[28] = __builtin_amdgcn_bitop3_b32(d[28], g27, m.o[1], 0x96);
-        d[10] = __builtin_amdgcn_bitop3_b32(d[10], g20, m.o[2], 0x96);
-        d[18] = __builtin_amdgcn_bitop3_b32(d[18], g23, m.o[3], 0x96);
+        const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x1, m.e[0], 0x96);
+        const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x5, x1, g6, 0x8d);
+        const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x4, g6, g7, 0x61);
+        const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x2, x1, g8, 0x7c);
+        const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x4, g6, g9, 0x19);
+        const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x4, g7, g9, 0x07);
+        const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x1, g10, g11, 0x97);
+        const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x3, g7, g12, 0x2d);
+        const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x5, g12, g13, 0x59);
+        const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x5, g6, g8, 0x35);
+        const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x4, g14, g15, 0x1c);
+        const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x2, g15, g16, 0x17);
+        const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x2, x5, g16, 0x69);
+        const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x1, g17, g18, 0x38);
+        const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g8, g14, g19, 0xc9);
+        const uint32_t g21 = __builtin_amdgcn_bitop3_b32(x3, x5, g20, 0xd3);
+        const uint32_t g22 = __builtin_amdgcn_bitop3_b32(g10, g11, g21, 0xb4);
+        const uint32_t g23 = __builtin_amdgcn_bitop3_b32(g15, g21, g22, 0x96);
+        const uint32_t g24 = __builtin_amdgcn_bitop3_b32(g20, g22, g23, 0xba);
+        const uint32_t g25 = __builtin_amdgcn_bitop3_b32(g13, g14, g24, 0x57);
+        const uint32_t g26 = __builtin_amdgcn_bitop3_b32(x1, g18, g25, 0x69);
+        d[3] = __builtin_amdgcn_bitop3_b32(d[3], g20, m.o[0], 0x69);
+        d[28] = __builtin_amdgcn_bitop3_b32(d[28], g26, m.o[1], 0x69);
+        d[10] = __builtin_amdgcn_bitop3_b32(d[10], g18, m.o[2], 0x69);
+        d[18] = __builtin_amdgcn_bitop3_b32(d[18], g23, m.o[3], 0x69);
     }
     {  // S7
         __builtin_amdgcn_sched_barrier(0);

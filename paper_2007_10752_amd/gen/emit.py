@@ -185,8 +185,6 @@ def emit_bitslice(nets):
     fp_src = [0] * 64
     for n in range(1, 65):
         fp_src[plane_of(n)] = T.FP[n - 1] - 1  # 0..31 -> R16[i], 32..63 -> L16[i-32]
-    src, primary, dup_of_e, dup_e = e_structure(nets)
-    ow = out_word()
 
     s = [BANNER, "#pragma once\n#include <stdint.h>\n\n"]
     s.append("// Initial permutation as renaming: L[i] / R[i] read plane BS_IP_L[i] / BS_IP_R[i]\n")
@@ -203,39 +201,13 @@ def emit_bitslice(nets):
     s.append("// XORs per round: 32 of S-box outputs into the other half, and the second\n"
              "// uses whose masks are not folded into the gates (%d of 16 are)\n" % len(folded))
     s.append("#define BS_XORS_PER_ROUND %d\n\n" % (32 + 16 - len(folded)))
-    s.append("// One Feistel round on 32 blocks per lane (Sec. III-B): d ^= P(S(E(r) ^ K)).\n"
-             "// The halves are stored XORed with key masks: each word of r already\n"
-             "// carries the round-key bit of its primary expansion position, so only\n"
-             "// second uses need their mask (km(32 + k)): XORed in, or taken as the third\n"
-             "// operand of the gates that read the input; km(4*box + q) re-masks the\n"
-             "// updated word of d for its next use, folded into the output XOR.\n")
-    s.append("// km(i) returns mask i of the round (0 or ~0): km(4*box + q), km(32 + k).\n")
-    s.append("template <class KM>\n"
-             "__device__ __forceinline__ void bs_round(uint32_t (&d)[32], const uint32_t (&r)[32],\n"
-             "                                         const KM &km) {\n")
-    for box in range(8):
-        net = box_network(nets, box)
-        s.append("    {  // S%d\n" % (box + 1))
-        decl, names = box_signals(box, src, dup_of_e, net, lambda i, k: "km(%d)" % (32 + k))
-        s.extend(decl)
-        for i, (a, b, c, imm) in enumerate(net["gates"]):
-            nm = "g%d" % (6 + i)
-            s.append("        const uint32_t %s = __builtin_amdgcn_bitop3_b32(%s, %s, %s, 0x%02x);\n"
-                     % (nm, names[a], names[b], names[c], imm))
-            names[6 + i] = nm
-        for q, (sig, neg) in enumerate(net["outs"]):
-            j = ow[4 * box + q]
-            s.append("        d[%d] = __builtin_amdgcn_bitop3_b32(d[%d], %s, km(%d), 0x%02x);\n"
-                     % (j, j, names[sig], 4 * box + q, 0x69 if neg else 0x96))
-        s.append("    }\n")
-    s.append("}\n")
     s.append(emit_round_piped(nets))
     return "".join(s)
 
 
 def emit_round_piped(nets):
-    """bs_round with the key masks of each S-box in registers, requested from
-    memory D boxes before they are used."""
+    """One Feistel round with the key masks of each S-box in registers, made D
+    boxes before they are used."""
     src, primary, dup_of_e, dup_e = e_structure(nets)
     ow = out_word()
     s = ["\n// Number of second-use inputs of each S-box (mask words e[] it reads).\n",
@@ -243,9 +215,14 @@ def emit_round_piped(nets):
          "\n// Key masks of one S-box in registers: o[q] is folded into the XOR of output q\n"
          "// into the other half, e[i] is the mask of the box's i-th second-use input.\n"
          "struct BsBoxMasks {\n    uint32_t o[4], e[4];\n};\n\n"
-         "// bs_round with masks laid out by round and S-box (8 words per box, 64 per\n"
-         "// round: o[0..3], e[0..3]) and software-pipelined D boxes ahead: before box j\n"
-         "// runs, load(pm[(j + D) %% 8], q, n) requests the masks of the box D places\n"
+         "// One Feistel round on 32 blocks per lane (Sec. III-B): d ^= P(S(E(r) ^ K)).\n"
+         "// The halves are stored XORed with key masks: each word of r already carries the\n"
+         "// round-key bit of its primary expansion position, so only second uses need their\n"
+         "// mask: XORed in, or taken as the third operand of the gates that read the input;\n"
+         "// the output masks re-mask the updated words of d for their next use.  Masks are\n"
+         "// laid out by round and S-box (8 words per box, 64 per round: o[0..3], e[0..3])\n"
+         "// and software-pipelined D boxes ahead: before box j\n"
+         "// runs, load(pm[(j + D) % 8], q, n) requests the masks of the box D places\n"
          "// later, q = p + 8 * (j + D), or past the last box pn + 8 * (j + D - 8) (pn: the\n"
          "// next round's masks).\n"
          "// A scheduling barrier between boxes keeps each request and each box's\n"

@@ -15,8 +15,15 @@
 // probability exp(-growth / temperature) up to `slack` gates over the best.
 // Every accepted network is checked on all 64 inputs.
 //
+// Built with -DKEYS=n (1..3) the network also takes the key masks of n inputs:
+// signals 6 .. 5 + n, each XORed to its input by a gate of the start network.
+// That gate counts like the others, so the search saves it where the mask can
+// enter a gate that has an operand free (networks.fold_network writes such
+// networks out).
+//
 // Usage: sbox_walk <seconds> <seed> <temperature> <slack> <box table: 64
-// values, row-major 4x16> < network.  Prints the smallest network found.
+// values, row-major 4x16> [inputs with key masks] < network.  Prints the
+// smallest network found.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -27,8 +34,40 @@
 
 typedef uint64_t u64;
 
-constexpr int kMax = 56;        // signals of a network: 6 inputs, then gates
+#ifndef KEYS
+#define KEYS 0
+#endif
+constexpr int kIn = 6 + KEYS;   // inputs: S-box inputs, then key masks
+constexpr int kWords = 1 << KEYS;
+constexpr int kMax = 56;        // signals of a network: the inputs, then gates
 constexpr double kStall = 150;  // seconds without progress before starting over from the best
+
+// A signal's values: bit v of word k for S-box input v under key masks k.
+struct Vec {
+    u64 w[kWords] = {};
+    explicit operator bool() const {
+        u64 any = 0;
+        for (u64 x : w) any |= x;
+        return any != 0;
+    }
+    bool operator==(const Vec &o) const { return memcmp(w, o.w, sizeof w) == 0; }
+    void set(int v, int k) { w[k] |= 1ull << v; }
+};
+#define VEC_OP(op)                                                  \
+    static Vec operator op(const Vec &a, const Vec &b) {            \
+        Vec r;                                                      \
+        for (int i = 0; i < kWords; i++) r.w[i] = a.w[i] op b.w[i]; \
+        return r;                                                   \
+    }
+VEC_OP(&)
+VEC_OP(|)
+VEC_OP(^)
+static void operator|=(Vec &a, const Vec &b) { a = a | b; }
+static Vec operator~(const Vec &a) {
+    Vec r;
+    for (int i = 0; i < kWords; i++) r.w[i] = ~a.w[i];
+    return r;
+}
 
 struct Gate {
     int a, b, c, imm;
@@ -36,7 +75,7 @@ struct Gate {
 struct Net {
     int n;  // signals
     Gate g[kMax];
-    u64 t[kMax];
+    Vec t[kMax];
     int out[4], neg[4];
 };
 
@@ -49,30 +88,30 @@ static u64 rnd() {
 }
 static int below(int n) { return (int)((rnd() >> 33) % (u64)n); }
 
-static u64 lut(int imm, u64 a, u64 b, u64 c) {
-    u64 r = 0;
+static Vec lut(int imm, const Vec &a, const Vec &b, const Vec &c) {
+    Vec r;
     for (int i = 0; i < 8; i++)
         if ((imm >> i) & 1) r |= ((i & 4) ? a : ~a) & ((i & 2) ? b : ~b) & ((i & 1) ? c : ~c);
     return r;
 }
 
-static u64 target[4];
+static Vec target[4];
 
 static bool correct(const Net &n) {
     for (int q = 0; q < 4; q++)
-        if ((n.neg[q] ? ~n.t[n.out[q]] : n.t[n.out[q]]) != target[q]) return false;
+        if (!((n.neg[q] ? ~n.t[n.out[q]] : n.t[n.out[q]]) == target[q])) return false;
     return true;
 }
 
-// The live part of gates g[6..n), which may be in any order, as a network in
+// The live part of gates g[kIn..n), which may be in any order, as a network in
 // topological order; false if it is cyclic.
 static bool rebuild(const Gate *g, int n, const int *out, const int *neg, Net &r) {
     int map[kMax + 1], seen[kMax + 1] = {};
     struct Frame {
         int v, k;
     } stack[kMax + 8];
-    for (int i = 0; i < n; i++) map[i] = i < 6 ? i : -1;
-    r.n = 6;
+    for (int i = 0; i < n; i++) map[i] = i < kIn ? i : -1;
+    r.n = kIn;
     for (int q = 0; q < 4; q++) {
         if (map[out[q]] >= 0) continue;
         int sp = 0;
@@ -107,8 +146,8 @@ static bool rebuild(const Gate *g, int n, const int *out, const int *neg, Net &r
 }
 
 // Input vectors on which gate v matters; *dep: the signals that depend on v.
-static u64 observability(const Net &n, int v, u64 *dep) {
-    u64 f[kMax];
+static Vec observability(const Net &n, int v, u64 *dep) {
+    Vec f[kMax];
     *dep = 1ull << v;
     f[v] = ~n.t[v];
     for (int i = v + 1; i < n.n; i++) {
@@ -118,7 +157,7 @@ static u64 observability(const Net &n, int v, u64 *dep) {
         f[i] = lut(x.imm, val(x.a), val(x.b), val(x.c));
         *dep |= 1ull << i;
     }
-    u64 care = 0;
+    Vec care;
     for (int q = 0; q < 4; q++)
         if ((*dep >> n.out[q]) & 1) care |= f[n.out[q]] ^ n.t[n.out[q]];
     return care;
@@ -133,14 +172,14 @@ static u64 fanout_free_cone(const Net &n, int v) {
         if (x.b != x.a) f(x.b);
         if (x.c != x.a && x.c != x.b) f(x.c);
     };
-    for (int i = 6; i < n.n; i++) each(i, [&](int c) { refs[c]++; });
+    for (int i = kIn; i < n.n; i++) each(i, [&](int c) { refs[c]++; });
     for (int q = 0; q < 4; q++) refs[n.out[q]]++;
     u64 cone = 1ull << v;
     int stack[kMax], sp = 0;
     stack[sp++] = v;
     while (sp)
         each(stack[--sp], [&](int c) {
-            if (c >= 6 && --refs[c] == 0) {
+            if (c >= kIn && --refs[c] == 0) {
                 cone |= 1ull << c;
                 stack[sp++] = c;
             }
@@ -151,20 +190,20 @@ static u64 fanout_free_cone(const Net &n, int v) {
 // Calls f(a, b, c) for every triple of the signals s[0..ns) on which some gate
 // is 1 on `on` and 0 on `off`.
 template <class F>
-static void triples(const Net &n, const int *s, int ns, u64 on, u64 off, F f) {
+static void triples(const Net &n, const int *s, int ns, const Vec &on, const Vec &off, F f) {
     for (int i = 0; i < ns; i++)
         for (int j = i + 1; j < ns; j++) {
-            const u64 A = n.t[s[i]], B = n.t[s[j]];
-            const u64 cell[4] = {~A & ~B, ~A & B, A & ~B, A & B};
-            u64 p[4], z[4];
+            const Vec A = n.t[s[i]], B = n.t[s[j]];
+            const Vec cell[4] = {~A & ~B, ~A & B, A & ~B, A & B};
+            Vec p[4], z[4];
             int k = 0;
-            for (u64 m : cell)
+            for (const Vec &m : cell)
                 if ((on & m) && (off & m)) {
                     p[k] = on & m;
                     z[k++] = off & m;
                 }
             for (int l = j + 1; l < ns; l++) {
-                const u64 C = n.t[s[l]];
+                const Vec C = n.t[s[l]];
                 bool ok = true;
                 for (int q = 0; q < k && ok; q++)
                     ok = !((p[q] & C) && (z[q] & C)) && !((p[q] & ~C) && (z[q] & ~C));
@@ -175,10 +214,10 @@ static void triples(const Net &n, const int *s, int ns, u64 on, u64 off, F f) {
 
 // The table of a gate over (a, b, c) that is 1 on `on` and 0 on `off`, its
 // free entries at random.
-static int table_of(const Net &n, int a, int b, int c, u64 on, u64 off) {
+static int table_of(const Net &n, int a, int b, int c, const Vec &on, const Vec &off) {
     int imm = 0, free = 0;
     for (int i = 0; i < 8; i++) {
-        const u64 m = ((i & 4) ? n.t[a] : ~n.t[a]) & ((i & 2) ? n.t[b] : ~n.t[b]) &
+        const Vec m = ((i & 4) ? n.t[a] : ~n.t[a]) & ((i & 2) ? n.t[b] : ~n.t[b]) &
                       ((i & 1) ? n.t[c] : ~n.t[c]);
         if (m & on) imm |= 1 << i;
         else if (!(m & off)) free |= 1 << i;
@@ -187,15 +226,15 @@ static int table_of(const Net &n, int a, int b, int c, u64 on, u64 off) {
 }
 
 static void print(const Net &n) {
-    printf("gates %d\n", n.n - 6);
-    for (int i = 6; i < n.n; i++)
+    printf("gates %d\n", n.n - kIn);
+    for (int i = kIn; i < n.n; i++)
         printf("g %d %d %d %d %d\n", i, n.g[i].a, n.g[i].b, n.g[i].c, n.g[i].imm);
     for (int q = 0; q < 4; q++) printf("out %d %d %d\n", q, n.out[q], n.neg[q]);
 }
 
 int main(int argc, char **argv) {
-    if (argc != 5 + 64) {
-        fprintf(stderr, "usage: %s seconds seed temperature slack v0 .. v63 < network\n", argv[0]);
+    if (argc != 5 + 64 + KEYS) {
+        fprintf(stderr, "usage: %s seconds seed temperature slack v0 .. v63 [inputs] < network\n", argv[0]);
         return 1;
     }
     const double seconds = atof(argv[1]), temperature = atof(argv[3]);
@@ -205,26 +244,41 @@ int main(int argc, char **argv) {
     for (int v = 0; v < 64; v++) {
         const int row = ((v >> 5) << 1) | (v & 1), col = (v >> 1) & 15;
         const int val = atoi(argv[5 + row * 16 + col]);
-        for (int q = 0; q < 4; q++)
-            if ((val >> (3 - q)) & 1) target[q] |= 1ull << v;
+        for (int k = 0; k < kWords; k++) {
+            int u = v;  // the raw input that the masks turn into v
+            for (int j = 0; j < KEYS; j++)
+                if ((k >> j) & 1) u ^= 1 << (5 - atoi(argv[69 + j]));
+            for (int q = 0; q < 4; q++)
+                if ((val >> (3 - q)) & 1) target[q].set(u, k);
+        }
     }
     static Net cur, best, next;
     for (Net *n : {&cur, &next})
-        for (int q = 0; q < 6; q++) {
-            n->t[q] = 0;
+        for (int q = 0; q < kIn; q++)
             for (int v = 0; v < 64; v++)
-                if ((v >> (5 - q)) & 1) n->t[q] |= 1ull << v;
-        }
-    cur.n = 6;
+                for (int k = 0; k < kWords; k++)
+                    if (q < 6 ? (v >> (5 - q)) & 1 : (k >> (q - 6)) & 1) n->t[q].set(v, k);
+    cur.n = kIn;
+    auto add = [&](const Gate &x) {
+        cur.g[cur.n] = x;
+        cur.t[cur.n] = lut(x.imm, cur.t[x.a], cur.t[x.b], cur.t[x.c]);
+        return cur.n++;
+    };
+    int map[kMax];  // signals of the given network, in this one
+    for (int q = 0; q < 6; q++) map[q] = q;
+    for (int j = 0; j < KEYS; j++) {
+        const int q = atoi(argv[69 + j]);
+        if (q < 0 || q > 5) return 1;
+        map[q] = add({q, 6 + j, 6 + j, 0x3C});
+    }
     char line[200];
     while (fgets(line, sizeof line, stdin)) {
         int x, a, b, c, m;
-        if (sscanf(line, "g %d %d %d %d %d", &x, &a, &b, &c, &m) == 5 && x == cur.n && x < kMax - 2) {
-            cur.g[x] = {a, b, c, m};
-            cur.t[x] = lut(m, cur.t[a], cur.t[b], cur.t[c]);
-            cur.n++;
-        } else if (sscanf(line, "out %d %d %d", &x, &a, &b) == 3 && x >= 0 && x < 4) {
-            cur.out[x] = a;
+        if (sscanf(line, "g %d %d %d %d %d", &x, &a, &b, &c, &m) == 5 && x >= 6 &&
+            x < kMax - 2 - 2 * KEYS && std::min({a, b, c}) >= 0 && std::max({a, b, c}) < x) {
+            map[x] = add({map[a], map[b], map[c], m});
+        } else if (sscanf(line, "out %d %d %d", &x, &a, &b) == 3 && x >= 0 && x < 4 && a >= 0 && a < kMax - 2) {
+            cur.out[x] = map[a];
             cur.neg[x] = b;
         }
     }
@@ -244,12 +298,12 @@ int main(int argc, char **argv) {
                 progress = t;
             }
         }
-        const int v = 6 + below(cur.n - 6);
-        u64 dep;
-        const u64 care = observability(cur, v, &dep);
+        const int v = kIn + below(cur.n - kIn);
+        u64 dep;  // (signal set)
+        const Vec care = observability(cur, v, &dep);
         const u64 cone = fanout_free_cone(cur, v);
         const int freed = __builtin_popcountll(cone);
-        const u64 on = cur.t[v] & care, off = ~cur.t[v] & care;
+        const Vec on = cur.t[v] & care, off = ~cur.t[v] & care;
         int s[kMax], ns = 0;
         for (int i = 0; i < cur.n; i++)
             if (!((dep >> i) & 1)) s[ns++] = i;
@@ -264,10 +318,10 @@ int main(int argc, char **argv) {
         bool have = false;
         for (int k = 0; k < ns && !have; k++) {
             const int x = s[(k + it) % ns];
-            const u64 d = (cur.t[x] ^ cur.t[v]) & care;
-            if (d != 0 && d != care) continue;
-            const int inv = d != 0;
-            for (int i = 6; i < n; i++) {
+            const Vec d = (cur.t[x] ^ cur.t[v]) & care;
+            if (d && !(d == care)) continue;
+            const int inv = (bool)d;
+            for (int i = kIn; i < n; i++) {
                 auto swap_in = [&](int &r, int bit) {
                     if (r != v) return;
                     r = x;
@@ -310,10 +364,10 @@ int main(int argc, char **argv) {
         } else if (!have) {
             const int d = s[below(ns)], e = s[below(ns)];
             if (d == e) continue;
-            u64 w1 = 0, w0 = 0;  // where w must be 1, 0
+            Vec w1, w0;          // where w must be 1, 0
             int outer = 0;       // LUT3(w, d, e)
             for (int cell = 0; cell < 4; cell++) {
-                const u64 m = ((cell & 2) ? cur.t[d] : ~cur.t[d]) & ((cell & 1) ? cur.t[e] : ~cur.t[e]);
+                const Vec m = ((cell & 2) ? cur.t[d] : ~cur.t[d]) & ((cell & 1) ? cur.t[e] : ~cur.t[e]);
                 if ((on & m) && (off & m)) {
                     const int flip = below(2);
                     w1 |= flip ? off & m : on & m;

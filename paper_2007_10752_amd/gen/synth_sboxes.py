@@ -15,9 +15,12 @@ the emitter reads, so a normal build does not search.
 
 With --walk SECONDS it shrinks networks by local search instead
 (sbox_walk.cpp): each job starts from the stored network or, every other
-one, from a fresh result of sbox_synth.cpp.
+one, from a fresh result of sbox_synth.cpp.  With --keys N it searches over
+the S-box inputs and the key masks of N of its second uses together, so that a
+mask's XOR counts like a gate and is saved where the mask fits into one.
 
     python -m paper_2007_10752_amd.gen.synth_sboxes --walk 300 --jobs 8
+    python -m paper_2007_10752_amd.gen.synth_sboxes --walk 300 --jobs 8 --keys 1
 """
 import argparse
 import concurrent.futures as cf
@@ -27,23 +30,51 @@ import subprocess
 import tempfile
 
 from .des_tables import SBOX
-from .networks import (NETWORKS_PATH, foldable, format_networks, load_networks, parse_network,
-                       second_use_plan, verify_network)
+from .networks import (NETWORKS_PATH, SECOND_USES, foldable, format_networks, live_signals,
+                       load_networks, lut3, parse_network, second_use_plan, verify_network)
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 
-def _build(tmpdir, name="sbox_synth"):
-    exe = os.path.join(tmpdir, name)
-    subprocess.run(["g++", "-O2", "-o", exe, os.path.join(HERE, name + ".cpp")], check=True)
+def _build(tmpdir, name="sbox_synth", keys=0):
+    exe = os.path.join(tmpdir, "%s%d" % (name, keys))
+    subprocess.run(["g++", "-O2", "-DKEYS=%d" % keys, "-o", exe, os.path.join(HERE, name + ".cpp")],
+                   check=True)
     return exe
 
 
-def _walk(exe, box, seconds, seed, start):
+def _without_keys(text):
+    """A network over the S-box inputs and key masks (signals from 6 on), as
+    sbox_walk.cpp prints it, with the masks 0: gates that then pass a signal on
+    are left out.  foldable() says which masks fit back in."""
+    gates, outs, of = [], [None] * 4, {q: q for q in range(6)}
+    for line in text.splitlines():
+        f = line.split()
+        if f and f[0] == "g":
+            v, ops, imm = int(f[1]), [int(x) for x in f[2:5]], int(f[5])
+            sig = [of.get(x, 0) for x in ops]  # (a mask's slot: any signal, ignored)
+            new = 0
+            for idx in range(8):
+                val = [(idx >> (2 - i)) & 1 if ops[i] in of else 0 for i in range(3)]
+                new |= lut3(imm, *val) << idx
+            live = live_signals((*sig, new))
+            same = len(live) == 1 and all(
+                lut3(new, *(b if x in live else 0 for x in sig)) == b for b in (0, 1))
+            if same:
+                of[v] = live.pop()
+            else:
+                of[v] = 6 + len(gates)
+                gates.append((*sig, new))
+        elif f and f[0] == "out":
+            outs[int(f[1])] = (of[int(f[2])], int(f[3]))
+    return {"gates": gates, "outs": outs}
+
+
+def _walk(exe, box, seconds, seed, start, keys=()):
     vals = [str(v) for row in SBOX[box] for v in row]
-    r = subprocess.run([exe, str(seconds), str(seed), "0.35", "2"] + vals, check=True,
-                       input=format_networks({box: start}), capture_output=True, text=True)
-    return parse_network(r.stdout)
+    r = subprocess.run([exe, str(seconds), str(seed), "0.6", "4"] + vals + [str(q) for q in keys],
+                       check=True, input=format_networks({box: start}), capture_output=True, text=True)
+    return _without_keys(r.stdout)
 
 
 def _run(exe, box, restarts, seed, restrict, lookahead):
@@ -101,6 +132,7 @@ def main():
                     help="comma-separated bit masks of restricted inputs, one search each")
     ap.add_argument("--lookahead", type=int, default=int(os.environ.get("SBOX_LOOKAHEAD", "0")))
     ap.add_argument("--walk", type=float, default=0, help="seconds of local search per job")
+    ap.add_argument("--keys", type=int, default=0, help="second uses whose key masks join the walk")
     args = ap.parse_args()
     boxes = [int(b) for b in args.boxes.split(",")]
     masks = [int(m) for m in args.restrict.split(",")]
@@ -111,12 +143,16 @@ def main():
     cands = {b: [current[b]] for b in range(8) if b in current}
     if args.walk:
         with tempfile.TemporaryDirectory() as td, cf.ThreadPoolExecutor(args.jobs) as pool:
-            synth, walk = _build(td), _build(td, "sbox_walk")
+            synth = _build(td)
+            walk = [_build(td, "sbox_walk", k) for k in range(args.keys + 1)]
 
             def job(box, j):
                 seed = args.seed * 1000003 + box * 7919 + j
                 start = current.get(box) if j % 2 == 0 else None
-                return _walk(walk, box, args.walk, seed, start or _run(synth, box, 1, seed, 0, 0))
+                sets = list(itertools.combinations([e % 6 for e in SECOND_USES if e // 6 == box], args.keys))
+                keys = sets[j // 2 % len(sets)] if sets else ()
+                return _walk(walk[len(keys)], box, args.walk, seed,
+                             start or _run(synth, box, 1, seed, 0, 0), keys)
             futs = {pool.submit(job, b, j): b for j in range(args.jobs) for b in boxes}
             for fut in cf.as_completed(futs):
                 verify_network(futs[fut], fut.result())
