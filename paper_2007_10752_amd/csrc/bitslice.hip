@@ -33,13 +33,14 @@
 // where every one pairs with another wave's.  1 GiB by the operations of a round,
 // each pair on one machine: 242 (196 S-box gates) 1,083 us, 224 (176 gates) 1,028;
 // 224 1,066 us, 211 (163 gates) 1,015; 211 919, 202 (159 gates, five of the sixteen
-// second-use masks folded into them) 892.  The key masks are scalars, widened from the
-// key words by scalar instructions.  Read from a table in LDS, 17 reads a round
-// (vector operands, which were thought to pair where scalar ones do not), they cost
-// issue slots: 1 GiB 986 -> 918 us, 64 MiB 69.2 -> 64.8, CTR of 256 MiB 255 -> 239,
-// CBC decryption 264 -> 248.  Workgroups of one wave or two: the same at most sizes
-// (48 MiB: 59 us with two, 50 with one or four); of eight: 36 MiB 58 to 48.  A 6-wave
-// register budget: 64 MiB 68 to 66.
+// second-use masks folded into them) 892; 202 910, 201 (six folded) 906.
+//
+// The key masks are scalars, widened from the key words by scalar instructions.
+// Read from a table in LDS, 17 reads a round (vector operands, which were thought to
+// pair where scalar ones do not), they cost issue slots: 1 GiB 986 -> 918 us, 64 MiB
+// 69.2 -> 64.8, CTR of 256 MiB 255 -> 239, CBC decryption 264 -> 248.  Workgroups of
+// one wave or two: the same at most sizes (48 MiB: 59 us with two, 50 with one or
+// four); of eight: 36 MiB 58 to 48.  A 6-wave register budget: 64 MiB 68 to 66.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

@@ -263,28 +263,28 @@ __device__ __forceinline__ void bs_box<7>(const uint32_t *x, uint32_t *d,
     const uint32_t x1 = x[1] ^ m.e[1];
     const uint32_t x2 = x[2];
     const uint32_t x3 = x[3];
-    const uint32_t x4 = x[4] ^ m.e[2];
+    const uint32_t x4 = x[4];
     const uint32_t x5 = x[5] ^ m.e[3];
-    const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x0, x3, x5, 0xaf);
-    const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x1, x4, g6, 0xf2);
-    const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x2, x3, g7, 0xd2);
-    const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x1, x4, g8, 0xc9);
-    const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x0, x1, g8, 0x86);
-    const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x3, g9, g10, 0x4b);
-    const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x0, x1, g11, 0x93);
-    const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x4, g8, g12, 0xc9);
-    const uint32_t g14 = __builtin_amdgcn_bitop3_b32(x5, g11, g13, 0xea);
-    const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x1, x4, g14, 0xc9);
-    const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x0, g11, g14, 0x69);
-    const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x1, g15, g16, 0xb4);
-    const uint32_t g18 = __builtin_amdgcn_bitop3_b32(x5, g11, g17, 0xc6);
-    const uint32_t g19 = __builtin_amdgcn_bitop3_b32(x0, x5, g18, 0x1c);
-    const uint32_t g20 = __builtin_amdgcn_bitop3_b32(g11, g13, g19, 0x96);
-    const uint32_t g21 = __builtin_amdgcn_bitop3_b32(g6, g18, g20, 0x96);
-    const uint32_t g22 = __builtin_amdgcn_bitop3_b32(g6, g15, g16, 0x96);
-    const uint32_t g23 = __builtin_amdgcn_bitop3_b32(g16, g17, g18, 0x69);
-    d[0] = __builtin_amdgcn_bitop3_b32(d[0], g21, m.o[0], 0x69);
-    d[1] = __builtin_amdgcn_bitop3_b32(d[1], g20, m.o[1], 0x69);
-    d[2] = __builtin_amdgcn_bitop3_b32(d[2], g22, m.o[2], 0x96);
+    const uint32_t g6 = __builtin_amdgcn_bitop3_b32(x4, x1, m.e[2], 0x96);
+    const uint32_t g7 = __builtin_amdgcn_bitop3_b32(x0, x1, g6, 0x9a);
+    const uint32_t g8 = __builtin_amdgcn_bitop3_b32(x0, x1, x5, 0x9c);
+    const uint32_t g9 = __builtin_amdgcn_bitop3_b32(x3, g7, g8, 0x19);
+    const uint32_t g10 = __builtin_amdgcn_bitop3_b32(x0, x2, g9, 0xc9);
+    const uint32_t g11 = __builtin_amdgcn_bitop3_b32(x3, g7, g10, 0x87);
+    const uint32_t g12 = __builtin_amdgcn_bitop3_b32(x1, x5, g11, 0x69);
+    const uint32_t g13 = __builtin_amdgcn_bitop3_b32(x1, g8, g9, 0xcb);
+    const uint32_t g14 = __builtin_amdgcn_bitop3_b32(g6, g10, g11, 0x63);
+    const uint32_t g15 = __builtin_amdgcn_bitop3_b32(x0, g12, g14, 0x7d);
+    const uint32_t g16 = __builtin_amdgcn_bitop3_b32(x5, g12, g15, 0x93);
+    const uint32_t g17 = __builtin_amdgcn_bitop3_b32(x1, g14, g16, 0x5c);
+    const uint32_t g18 = __builtin_amdgcn_bitop3_b32(g7, g13, g17, 0x69);
+    const uint32_t g19 = __builtin_amdgcn_bitop3_b32(g8, g16, g18, 0xd2);
+    const uint32_t g20 = __builtin_amdgcn_bitop3_b32(x5, g14, g19, 0xc6);
+    const uint32_t g21 = __builtin_amdgcn_bitop3_b32(g12, g13, g20, 0x4b);
+    const uint32_t g22 = __builtin_amdgcn_bitop3_b32(g12, g13, g20, 0x2e);
+    const uint32_t g23 = __builtin_amdgcn_bitop3_b32(g20, g16, g19, 0x69);
+    d[0] = __builtin_amdgcn_bitop3_b32(d[0], g21, m.o[0], 0x96);
+    d[1] = __builtin_amdgcn_bitop3_b32(d[1], g22, m.o[1], 0x96);
+    d[2] = __builtin_amdgcn_bitop3_b32(d[2], g18, m.o[2], 0x69);
     d[3] = __builtin_amdgcn_bitop3_b32(d[3], g23, m.o[3], 0x96);
 }
