@@ -29,7 +29,7 @@
 // loaded blocks, then XORs each with the ciphertext block before it (the
 // IV before the first), re-read after the rounds.
 //
-// Bound by VALU issue: an instruction takes 2.2 clocks of its SIMD on 1 GiB, 2.0
+// Bound by VALU issue: an instruction takes 2.35 clocks of its SIMD on 1 GiB, 2.0
 // where every one pairs with another wave's.  1 GiB by the operations of a round,
 // each pair on one machine: 242 (196 S-box gates) 1,083 us, 224 (176 gates) 1,028;
 // 224 1,066 us, 211 (163 gates) 1,015; 211 919, 202 (159 gates, five of the sixteen
