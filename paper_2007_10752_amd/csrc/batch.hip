@@ -11,11 +11,10 @@
 // 256 bytes, and runs the same bitsliced core as the plain kernel.  The key
 // masks: a wave's 64 slices lie in a run of consecutive messages; where there
 // are at most KMAX of them the wave expands their masks together, one round
-// ahead, into a table in LDS (one row per message and round, in the plain
-// kernel's layout), and each lane reads its own message's row with the plain
-// kernel's piped LDS reads.  In a wave over more messages each lane widens its
-// own message's key words, one S-box ahead, and in a wave inside one message the
-// masks are scalars.
+// ahead, into a table in LDS (one row per message and round), and each lane reads
+// its own message's row two S-boxes ahead.  In a wave over more messages each lane
+// widens its own message's key words, one S-box ahead, and in a wave inside one
+// message the masks are scalars, as in the plain kernel.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -228,12 +227,11 @@ __global__ __launch_bounds__(kScanThreads) void batch_scan_kernel(const tdes_msg
 // own 48 masks per round).  The wave's lanes hold consecutive slices, so a
 // wave spans a run of consecutive messages; the table serves waves over up to
 // KMAX of them.  Table of one wave: 2 round buffers x KMAX rows x
-// kRowWords words; a row holds one message's 64 masks of one round in the
-// plain kernel's layout (box j at 8 j: output masks o[0..3], second-use
-// masks e[0..3]), padded so that the rows of different messages start on
+// kRowWords words; a row holds one message's 64 masks of one round
+// (box j at 8 j: output masks o[0..3], second-use masks e[0..3]), padded so that the rows of different messages start on
 // different banks.  Per round and message the wave writes 64 words, one per
 // lane (two VALU operations each), and every lane reads its own message's
-// row with the piped LDS reads of the plain kernel.
+// row, two S-boxes ahead.
 constexpr int kRowWords = 68;
 
 // The bit of a round's two key words (lo: output masks, hi: second uses) a
