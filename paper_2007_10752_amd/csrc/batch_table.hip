@@ -110,6 +110,7 @@ __device__ __forceinline__ uint32_t block_prefix(uint32_t v, uint32_t *sums, uin
 // SCAN: the workgroup scans the descriptors itself (n <= kTableScanMax);
 // otherwise ws holds their scan.
 // NB: blocks a lane takes in a step.
+// per: lanes of a step, with SCAN the most of them; least: see below.
 template <bool SCAN, int NB>
 __global__ __launch_bounds__(kThreads) void batch_table_kernel(const tdes_msg *__restrict__ msgs,
                                                               uint32_t n,
@@ -117,10 +118,10 @@ __global__ __launch_bounds__(kThreads) void batch_table_kernel(const tdes_msg *_
                                                               uint32_t n_sched, const uint8_t *in,
                                                               uint8_t *out, BatchBounds bb,
                                                               uint64_t *ws, uint64_t *skipped_out,
-                                                              uint32_t per) {
+                                                              uint32_t per, uint32_t least) {
     __shared__ __align__(16) uint32_t table[kTableWords];
     __shared__ uint4 rows[kRows * kRowStride];
-    // SCAN: first block of every message (entries past the last: the total).
+    // SCAN: first lane of every message (entries past the last: the total).
     // Else first slices of the 1,024 messages after the step's first one, from
     // the step's first slice on.
     __shared__ uint32_t start[SCAN ? kTableScanMax : kThreads];
@@ -129,9 +130,13 @@ __global__ __launch_bounds__(kThreads) void batch_table_kernel(const tdes_msg *_
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     uint64_t *first = ws + kWsHeader;
     uint32_t grid = gridDim.x;
-    uint64_t total;  // blocks, or the lanes of all slices
+    uint64_t total;  // lanes of all messages, or of all slices
     if (SCAN) {
         static_assert(kTableScanMax == 2 * kThreads, "two descriptors a thread");
+        // A message takes a lane per block, and no fewer than `least`, so that a
+        // step's lanes hold kRows messages at most (empty ones aside), one pass of the
+        // loop below, however unlike the messages are: a step whose first and last
+        // messages are cut has 1 + ceil((per - 1) / least) of them.
         // (batch_is_table bounds the work of so few messages, and a message is no
         // longer than that where outputs overlap: the sums fit 32 bits)
         uint32_t v[2], u[2], bad = 0;
@@ -142,6 +147,7 @@ __global__ __launch_bounds__(kThreads) void batch_table_kernel(const tdes_msg *_
             v[k] = (uint32_t)units_of(msgs[i < n ? i : n - 1], n_sched, bb, 8, &b);
             v[k] = i < n ? v[k] : 0u;
             u[k] = (v[k] + kSlice / 8 - 1) / (kSlice / 8);
+            v[k] = v[k] == 0 ? 0u : max(v[k], least);
             bad += i < n && b;
         }
         uint32_t sum;
@@ -165,6 +171,11 @@ __global__ __launch_bounds__(kThreads) void batch_table_kernel(const tdes_msg *_
         start[2 * tid] = f;
         start[2 * tid + 1] = f + v[0];
         total = sum;
+        // what there is, evenly over the workgroups: the first multiple of the lanes
+        // that NB waves' blocks fill which takes it in one step (the lanes try one each)
+        const uint32_t unit = NB * kWave;
+        const uint64_t enough = __ballot((lane + 1) * unit * grid >= sum);
+        if (enough != 0) per = min(per, (uint32_t)__builtin_ctzll(enough) * unit + unit);
         __syncthreads();
     } else {
         fill_tables(table);
@@ -174,7 +185,7 @@ __global__ __launch_bounds__(kThreads) void batch_table_kernel(const tdes_msg *_
     const uint8_t *sp = reinterpret_cast<const uint8_t *>(table);
     const uint32_t mask = in_vgpr(kIndexMask);
     for (uint64_t base = (uint64_t)blockIdx.x * per; base < total; base += (uint64_t)grid * per) {
-        const uint32_t here = (uint32_t)min((uint64_t)per, total - base);  // blocks of this step
+        const uint32_t here = (uint32_t)min((uint64_t)per, total - base);  // lanes of this step
         // this lane's blocks (tid, tid + lanes, ...): their messages, and their
         // places there
         const uint32_t lanes = NB == 1 ? kThreads : per / NB;
@@ -228,12 +239,12 @@ __global__ __launch_bounds__(kThreads) void batch_table_kernel(const tdes_msg *_
             dst[k] = nullptr;
             if (active[k]) {
                 const tdes_msg d = msgs[m[k]];
-                // (by slices, a message's last slice may be partial)
-                if (!SCAN) active[k] = at[k] < d.nbytes / 8;
-                if (active[k]) {
-                    w[k] = *reinterpret_cast<const uint2 *>(in + d.in_off + 8 * at[k]);
-                    dst[k] = out + d.out_off + 8 * at[k];
-                }
+                // (a message shorter than `least`, or its last slice, leaves lanes idle:
+                // they load its last block, so that no load waits for a branch)
+                const uint64_t nblk = d.nbytes / 8;
+                w[k] = *reinterpret_cast<const uint2 *>(in + d.in_off + 8 * min(at[k], nblk - 1));
+                dst[k] = out + d.out_off + 8 * at[k];
+                active[k] = at[k] < nblk;
             }
         }
         __syncthreads();
@@ -298,25 +309,33 @@ hipError_t launch_batch_table(const tdes_msg *msgs, size_t n_msgs, const uint32_
     // step take LDS time by the block, a step itself ~6 us of dependent loads, so
     // more blocks a lane beat more steps (300 messages: 2.1 MB 21.2 -> 20.1 us, 4
     // MiB 28.4 -> 27.1, 6 MiB 39.8 -> 37.3), and even steps beat full ones with a
-    // small last one (2.1 MB 25.5 -> 21.4).  No more than kRows messages of the
-    // batch's mean length hold: each kRows messages more cost a pass.  Where lanes
-    // go by slices, one block a lane.  Any grid is correct.
+    // small last one (2.1 MB 25.5 -> 21.4).  work_bytes only bounds the work, so a
+    // kernel that scans divides what it finds, and short messages may take more lanes
+    // than blocks there (`least`), at most n_msgs x per / (kRows - 1) more.  (Steps
+    // sized here, by the mean message and work_bytes, against these: one of 5 MB beside
+    // 2,000 of a block, all in one workgroup's step of 32 passes, 482 -> 45 us; 2,048
+    // of a block in a buffer of 6 MiB 479 -> 28, 300 of 1,000 bytes there 34 -> 18;
+    // even ones up to 2 % slower.)  Where lanes go by slices, one block a lane.  Any grid
+    // is correct.
     const bool scan = n_msgs <= kTableScanMax;
-    const uint64_t cus = device_cus();
+    // (a scanning kernel's extra workgroup has a CU too: as one more than fit it would
+    // start when another ends, 1-1.8 us later)
+    const uint64_t cus = scan && device_cus() > 1 ? device_cus() - 1 : device_cus();
     const uint64_t work = work_bytes / 8 + (scan ? 0 : n_msgs * (kSlice / 8));
-    const uint64_t fit = scan ? work * kRows / n_msgs : kThreads;
     const uint64_t cu_work = (work + cus - 1) / cus;
     const uint32_t nb = !scan || cu_work <= kThreads ? 1 : cu_work <= 2 * kThreads ? 2 : 3;
     const uint64_t steps = (cu_work + nb * kThreads - 1) / (nb * kThreads);
     uint64_t per = steps == 0 ? 1 : (cu_work + steps - 1) / steps;
+    if (scan) per += per * n_msgs / ((kRows - 1) * cus);
     const uint32_t unit = nb * kWave;
     per = (per + unit - 1) / unit * unit;
-    if (per > fit) per = fit < unit ? unit : fit / unit * unit;
-    uint64_t grid = (work + per - 1) / per;
+    if (per > (uint64_t)nb * kThreads) per = (uint64_t)nb * kThreads;
+    const uint32_t least = per <= kRows ? 1 : (uint32_t)(per + kRows - 2) / (kRows - 1);
+    uint64_t grid = scan ? (work + n_msgs * (least - 1) + unit - 1) / unit : (work + per - 1) / per;
     grid = grid < 1 ? 1 : grid > cus ? cus : grid;
     auto launch = [&](auto kernel, uint64_t g) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)g), dim3(kThreads), 0, stream, msgs, (uint32_t)n_msgs,
-                           schedules, (uint32_t)n_schedules, in, out, bb, ws, skipped_out, (uint32_t)per);
+                           schedules, (uint32_t)n_schedules, in, out, bb, ws, skipped_out, (uint32_t)per, least);
     };
     if (!scan) launch(batch_table_kernel<false, 1>, grid);
     else if (nb == 1) launch(batch_table_kernel<true, 1>, grid + 1);
