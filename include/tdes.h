@@ -54,23 +54,23 @@ typedef enum { TDES_ENCRYPT = 0, TDES_DECRYPT = 1 } tdes_dir;
 
 /* Kernel selection for tdes_ecb_crypt. */
 typedef enum {
-    TDES_KERNEL_AUTO = 0,     /* the library's choice by size: the table
-                                 kernel while its workgroups have a CU each
-                                 (2 MiB on 256 CUs; lower latency), the
-                                 bitsliced kernels above                   */
+    TDES_KERNEL_AUTO = 0,     /* the library's choice: the table kernel up
+                                 to 1.5 times the bytes one wave of its
+                                 resident workgroups covers at one block per
+                                 lane (6 MiB on 256 CUs), the bitsliced
+                                 kernel above                              */
     TDES_KERNEL_BITSLICE = 1, /* 32 blocks per lane as bit planes; S-boxes
                                  as gate networks, E/P/IP/FP as renaming   */
     TDES_KERNEL_SPBOX = 2     /* one block per lane; S-box+P tables in LDS */
 } tdes_kernel;
 
-/* Which side of the small-input limit nbytes is on, on the current device:
+/* The kernel TDES_KERNEL_AUTO runs for nbytes on the current device:
  * TDES_KERNEL_SPBOX up to 1.5 times the table kernel's one-pass size
- * (resident workgroups x 1,024 lanes x 8 bytes: 6 MiB on 256 CUs), where the
- * table kernel beats the plain bitsliced one, TDES_KERNEL_BITSLICE above.
- * (TDES_KERNEL_AUTO runs the table kernel for the lower third of the first
- * range and the bitsliced cipher, S-boxes split over waves, for the rest of
- * it, where that is faster still.)  Returns a negative tdes_status (TDES_ERR_DEVICE) without a
- * device. */
+ * (resident workgroups x 1,024 lanes x 8 bytes: 6 MiB on 256 CUs),
+ * TDES_KERNEL_BITSLICE above.  (From a third of that size on, 2 MiB, an explicit
+ * TDES_KERNEL_BITSLICE takes less time than the table kernel: 14.7 against 17.8 us
+ * for 3 MiB, 15.9 against 25.7 for 6 MiB.)  Returns a negative tdes_status
+ * (TDES_ERR_DEVICE) without a device. */
 int tdes_ecb_auto_kernel(size_t nbytes);
 
 /* Round keys of a key bundle, Sec. III-A.  k[b][i] is round key i+1 (of 16)

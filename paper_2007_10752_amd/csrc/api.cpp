@@ -79,16 +79,19 @@ tdes_status tdes::set_last_error(tdes_status st, const char *msg) {
 }
 
 int tdes::auto_kernel(size_t nbytes) {
-    // one and a half passes: up to there the table kernel's launch is shorter
-    // than the plain bitsliced kernel's (launch_auto has a third choice)
+    // One and a half passes (6 MiB on 256 CUs): the limit that tdes.h states, part of
+    // the interface.  Up to there the table kernel's launch is shorter than the plain
+    // bitsliced kernel's (5 MiB 25.4 against 29.4 us).  The split kernel's, which an
+    // explicit TDES_KERNEL_BITSLICE runs there, is shorter still from 2 MiB on (3 MiB
+    // 17.8 against 14.7, 6 MiB 25.7 against 15.9).
     return nbytes <= spbox_one_pass_bytes() / 2 * 3 ? TDES_KERNEL_SPBOX : TDES_KERNEL_BITSLICE;
 }
 
 bool tdes::auto_is_table(size_t nbytes) {
     // The table kernel as long as its workgroups have a CU each (2 MiB on 256
-    // CUs): one lane's 48 rounds on one block, 4-11 us a launch against 15 for
+    // CUs): one lane's 48 rounds on one block, 4-11 us a launch against 14 for
     // the bitsliced kernel with its S-boxes split over waves.  Two workgroups
-    // share a CU's LDS beyond: 17.8 against 15.4 us at 3 MiB.
+    // share a CU's LDS beyond: 17.8 against 14.7 us at 3 MiB.
     return nbytes <= spbox_one_pass_bytes() / 2;
 }
 
@@ -139,18 +142,17 @@ tdes_status tdes_ecb_crypt(const tdes_schedule *ks, int dir, int kernel, const v
     uint8_t *out = static_cast<uint8_t *>(d_out);
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e;
+    if (kernel == TDES_KERNEL_AUTO) kernel = tdes::auto_kernel(nbytes);
     if (kernel == TDES_KERNEL_SPBOX) {
         tdes::RoundSequence seq;
         tdes::round_sequence(*ks, dir, &seq);
         tdes::SpboxKeys k;
         tdes::spbox_keys(seq, &k);
         e = tdes::launch_spbox<tdes::kModeEcb>(k, tdes::ModeArgs{}, in, out, nbytes, s);
-    } else if (kernel == TDES_KERNEL_BITSLICE) {
+    } else {
         tdes::BitsliceKeys k;
         tdes::bitslice_keys(*ks, dir, &k);
         e = tdes::launch_bitslice(k, in, out, nbytes, s);
-    } else {
-        e = tdes::launch_ecb_auto(*ks, dir, in, out, nbytes, s);
     }
     if (e != hipSuccess) return fail(TDES_ERR_DEVICE, "kernel launch failed: %s", hipGetErrorString(e));
     return TDES_OK;

@@ -151,11 +151,13 @@ hipError_t batch_autotune(const tdes_msg *msgs, size_t n_msgs, const uint32_t *s
 // resident workgroups on the current device (4 MiB on 256 CUs).
 size_t spbox_one_pass_bytes();
 
-// tdes_ecb_auto_kernel's answer, as a tdes_kernel value.
+// The kernel TDES_KERNEL_AUTO runs for a size, as a tdes_kernel value
+// (tdes_ecb_auto_kernel's answer).
 int auto_kernel(size_t nbytes);
-// Whether TDES_KERNEL_AUTO and the other modes run the table kernel for a size
-// (the bitsliced ones otherwise), and the launch (see api.cpp).
+// Whether the other modes, the server's single requests and the chunks of
+// tdes_ecb_host run the table kernel for a size (the bitsliced ones otherwise).
 bool auto_is_table(size_t nbytes);
+// The launch by that rule.
 template <int MODE>
 hipError_t launch_auto(const tdes_schedule &ks, int dir, const ModeArgs &m, const uint8_t *in,
                        uint8_t *out, size_t nbytes, hipStream_t stream);

@@ -237,8 +237,8 @@ tdes_status launch_slot(tdes_server *s, Slot &sl) {
     hipError_t e = hipSuccess;
     if (n <= kPlainBatchMax) {
         // a batch of a few requests: plain launches with host-built key
-        // material (no copies, one launch each, the kernel tdes_ecb_crypt
-        // picks for the size) finish sooner than the copy, the descriptor
+        // material (no copies, one launch each, the size's faster kernel)
+        // finish sooner than the copy, the descriptor
         // scan and the batched kernel, whose lanes each run 32 blocks
         // through the rounds
         for (const Active &a : sl.reqs) {

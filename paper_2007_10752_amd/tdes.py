@@ -168,8 +168,8 @@ def ecb_crypt_ptr(schedule, direction, kernel, d_in, d_out, nbytes, stream=0):
 
 
 def auto_kernel(nbytes):
-    """Which side of the small-input limit nbytes is on, on the current device
-    (tdes_ecb_auto_kernel), by name ("spbox" or "bitslice")."""
+    """The kernel TDES_KERNEL_AUTO runs for nbytes on the current device, by
+    name ("spbox" or "bitslice")."""
     k = lib().tdes_ecb_auto_kernel(int(nbytes))
     if k < 0:
         raise TdesError(k, lib().tdes_last_error().decode())
