@@ -193,7 +193,14 @@ size_t tdes_batch_workspace_bytes(size_t n_msgs);
  * direction is out of range is skipped (neither read nor written), and the
  * number skipped is left in the second 64-bit word of the workspace.
  * Messages whose outputs overlap each other are not detected; their bytes
- * are then unspecified.  Errors (synchronous): TDES_ERR_ARG (NULL pointers
+ * are then unspecified.
+ * The kernel is chosen by n_msgs and out_bytes, which is all the host knows of
+ * the batch's size: up to 2,048 messages and out_bytes of 6 MiB (256 CUs), or
+ * more messages and out_bytes + 256 n_msgs of 4 MiB, a table kernel of lower
+ * latency, else the bitsliced one.  So a small batch that goes into a large
+ * buffer takes longer (300 messages of 7 KB: 20 us into their own 2.1 MB, 22
+ * into 6 MiB, 36 into 64 MiB); out_bytes may be as little as reaches the last
+ * message's end.  Errors (synchronous): TDES_ERR_ARG (NULL pointers
  * with n_msgs > 0, workspace too small, n_msgs > TDES_BATCH_MAX_MSGS,
  * n_schedules 0 or > TDES_BATCH_MAX_SCHEDULES), TDES_ERR_ALIGN,
  * TDES_ERR_DEVICE. */
