@@ -324,7 +324,10 @@ tdes_status tdes_batch_set_config(const tdes_batch_config *cfg);
  * `stream`.  The fastest is kept for every later batched call on the
  * current device (the request server's batches included), written to the
  * tuning cache under this device kind (best->saved says whether it was),
- * and returned in *best.  Synchronous.  Every trial reads the input and
+ * and returned in *best.  The configurations are the bitsliced batch
+ * kernel's: for a batch that tdes_batch_submit runs on the table kernel (see
+ * there) none differs, so the current one is kept, written and returned; tune
+ * on a batch of the size that matters.  Synchronous.  Every trial reads the input and
  * writes the output, so the input range [d_in_base, d_in_base + in_bytes)
  * must not overlap the output range (TDES_ERR_OVERLAP otherwise, in-place
  * batches included): each trial then writes the same result.  Batched

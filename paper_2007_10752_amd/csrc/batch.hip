@@ -793,8 +793,11 @@ hipError_t batch_autotune(const tdes_msg *msgs, size_t n_msgs, const uint32_t *s
     BatchConfig keep;
     hipError_t e = batch_config_current(&keep);
     if (e != hipSuccess) return e;
-    BatchConfig cands[64];
-    const int n_cands = batch_config_list(cands, 64);
+    // A batch that submits run on the table kernel has no configuration to choose: it
+    // is timed once, as it runs, and the current configuration kept, so that what is
+    // noise between its runs does not decide how later, larger batches run.
+    BatchConfig cands[64] = {keep};
+    const int n_cands = batch_is_table(n_msgs, out_bytes) ? 1 : batch_config_list(cands, 64);
     // a: start, on lane 0's stream, which the other lanes wait for; end[i]:
     // lane i's last batch, which lane 0 waits for before b
     hipEvent_t a = nullptr, b = nullptr, end[kMaxTuneLanes] = {};
@@ -805,8 +808,8 @@ hipError_t batch_autotune(const tdes_msg *msgs, size_t n_msgs, const uint32_t *s
     float best_ms = 0;
     BatchConfig best = keep;
     auto run = [&](const TuneLane &l) {
-        return launch_batch_bitslice(msgs, n_msgs, schedules, n_schedules, in, in_bytes, l.out,
-                                     out_bytes, l.ws, nullptr, l.stream);
+        return launch_batch(msgs, n_msgs, schedules, n_schedules, in, in_bytes, l.out, out_bytes,
+                            l.ws, nullptr, l.stream);
     };
     const hipStream_t s0 = lanes[0].stream;
     for (int i = 0; i < n_cands && e == hipSuccess; i++) {

@@ -487,8 +487,8 @@ class Batch:
     def autotune(self, x, out, reps=3, stream=None):
         """Time this batch in every batched-kernel configuration and keep the
         fastest for later batched launches on this device (and in the tuning
-        cache); returns it as a dict (synchronous).  x and out must not
-        overlap."""
+        cache; the current one for a batch small enough for the table kernel);
+        returns it as a dict (synchronous).  x and out must not overlap."""
         c = BatchConfig()
         _check(lib().tdes_batch_autotune(
             ctypes.c_void_p(self.msgs.data_ptr()), self.n_msgs, ctypes.c_void_p(self.sched.data_ptr()),
