@@ -565,25 +565,6 @@ void batch_bitslice_kernel(const tdes_msg *__restrict__ msgs, uint32_t n_msgs,
 // direction's masks on their own, 20 with neither, 12.8 with the fields below.
 constexpr int kExpandWaves = 4;
 
-struct PrimaryBits {  // of the expanded key: bit e at e
-    static constexpr int at(int i) { return kBsPrimaryE[i]; }
-};
-struct DupKeyBits {
-    static constexpr int at(int i) { return kBsDupE[i]; }
-};
-struct DupMaskBits {  // of the primary mask
-    static constexpr int at(int i) { return kBsESrc[kBsDupE[i]]; }
-};
-struct OutBits {
-    static constexpr int at(int i) { return kBsOutWord[i]; }
-};
-struct Pc2Lo {  // round-key bit e (0..31, 32..47) at bit e % 32
-    static constexpr int at(int i) { return pc2_at(i); }
-};
-struct Pc2Hi {
-    static constexpr int at(int i) { return pc2_at(32 + i); }
-};
-
 // The workgroups past the bundles' copy copy16 16-byte pieces from copy_src to
 // copy_dst (a server batch's descriptors and slice table, from host memory).
 __global__ __launch_bounds__(kExpandWaves * kWave) void expand_kernel(const uint8_t *keys24,
@@ -604,29 +585,18 @@ __global__ __launch_bounds__(kExpandWaves * kWave) void expand_kernel(const uint
     const size_t b = (size_t)blockIdx.x * kExpandWaves + w;
     const bool live = b < n;  // uniform per wave; every wave reaches the barrier
     if (live && lane < 48) {
-        const uint64_t r = round_halves(
+        const RoundMasks m = round_masks(
             load_key(keys24 + 24 * b + 8 * (lane / 16), ((uintptr_t)keys24 & 7u) == 0), lane % 16);
-        const uint64_t rk = (uint64_t)pick_bits<Pc2Hi, 16>(r) << 32 | pick_bits<Pc2Lo, 32>(r);
-        const uint32_t p = pick_bits<PrimaryBits, 32>(rk);
-        p_s[w][lane] = p;
-        o_s[w][lane] = pick_bits<OutBits, 32>(p);
-        d_s[w][lane] = pick_bits<DupKeyBits, 16>(rk) ^ pick_bits<DupMaskBits, 16>(p);
+        p_s[w][lane] = m.primary;
+        o_s[w][lane] = m.out;
+        d_s[w][lane] = m.dup;
     }
     __syncthreads();
     if (!live || lane >= 50) return;
     for (int dir = 0; dir < 2; dir++) {
-        auto P = [&](int t) { return p_s[w][round_key_slot(dir, t)]; };
-        uint2 out;
-        if (lane < 48) {
-            const int before = bs_mask_before(lane), after = bs_mask_after(lane);
-            out.x = (before < 0 ? 0u : o_s[w][round_key_slot(dir, before)]) ^
-                    (after < 0 ? 0u : o_s[w][round_key_slot(dir, after)]);
-            out.y = d_s[w][round_key_slot(dir, lane)];
-        } else {  // words 96, 97 and 98, 99 (bs_extra_word)
-            out.x = lane == 48 ? P(0) : P(31) ^ P(32);
-            out.y = lane == 48 ? P(15) ^ P(16) : P(47);
-        }
-        reinterpret_cast<uint2 *>(schedules + b * kDeviceScheduleWords + dir * kDirWords)[lane] = out;
+        const WordPair out = schedule_words(p_s[w], o_s[w], d_s[w], dir, lane);
+        reinterpret_cast<uint2 *>(schedules + b * kDeviceScheduleWords + dir * kDirWords)[lane] =
+            make_uint2(out.x, out.y);
     }
 }
 

@@ -61,7 +61,8 @@ TDES_HD inline void des_round_keys(const uint8_t key[8], uint64_t rk[16]) {
 
 // Round key i (0..15) of one 64-bit key on its own, without the rounds
 // before it: the halves are rotated once by the sum of the shift table
-// through round i (modulo 28, a full turn).  Equals rk[i] of des_round_keys.
+// through round i (modulo 28, a full turn).  Equals rk[i] of des_round_keys.  (The
+// plain form of what keysched_device.h computes by fields; only a test runs it.)
 TDES_HD inline uint64_t des_round_key(const uint8_t key[8], int i) {
     uint64_t k = 0;
     for (int b = 0; b < 8; b++) k = (k << 8) | key[b];

@@ -261,12 +261,6 @@ __global__ __launch_bounds__(kThreads) void tdes_spbox_multi_kernel(const SpboxM
 // and raw bundles in host memory, a wave to a message: lane t < 48 makes the table
 // kernel's keys of round t, four more copy the descriptor.  (A copy of host-built
 // keys took 8 us, and the host 1 us a message to build them.)
-struct Pc2Low {  // round-key bit e at bit 47 - e, as host code has it
-    static constexpr int at(int i) { return pc2_at(47 - i); }
-};
-struct Pc2High {
-    static constexpr int at(int i) { return pc2_at(15 - i); }
-};
 constexpr int kPrepareWaves = 4;
 
 __global__ __launch_bounds__(64 * kPrepareWaves) void tdes_spbox_prepare_kernel(
@@ -283,9 +277,7 @@ __global__ __launch_bounds__(64 * kPrepareWaves) void tdes_spbox_prepare_kernel(
         return;
     }
     const int slot = round_key_slot((int)dir, (int)lane);
-    const uint64_t r = round_halves(load_key(h_keys24 + 24 * m + 8 * (slot / 16), true), slot % 16);
-    const uint64_t rk = (uint64_t)pick_bits<Pc2High, 16>(r) << 32 | pick_bits<Pc2Low, 32>(r);
-    const SpboxRound k = spbox_round_keys(rk);
+    const SpboxRound k = table_round_keys(load_key(h_keys24 + 24 * m + 8 * (slot / 16), true), slot % 16);
     *reinterpret_cast<uint4 *>(keys[m].w[lane]) = make_uint4(k.w[0], k.w[1], k.w[2], k.w[3]);
 }
 
