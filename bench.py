@@ -27,6 +27,7 @@ import argparse
 import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -668,16 +669,35 @@ def full_output_check(args, host, out_h, key):
     return res
 
 
+def kernel_sources(kernel):
+    """The files a kernel is compiled from: its source and every file of csrc/
+    that it includes, directly or not (paths in csrc/, sorted)."""
+    csrc = os.path.join(ROOT, "paper_2007_10752_amd", "csrc")
+    todo, seen = [kernel + ".hip"], set()
+    while todo:
+        name = todo.pop()
+        if name in seen:
+            continue
+        seen.add(name)
+        with open(os.path.join(csrc, name)) as f:
+            for line in f:
+                m = re.match(r'\s*#\s*include\s+"([^"]+)"', line)
+                if not m:
+                    continue
+                for at in (os.path.join(os.path.dirname(name), m.group(1)), m.group(1)):
+                    if os.path.exists(os.path.join(csrc, at)):
+                        todo.append(at)
+                        break
+    return sorted(seen)
+
+
 def kernel_source_hash(kernel):
     """Hash of the sources a kernel is compiled from (to tell whether stored
     counter readings still describe it)."""
     import hashlib
     csrc = os.path.join(ROOT, "paper_2007_10752_amd", "csrc")
-    files = {"bitslice": ["bitslice.hip", "bitslice_core.h", "key_masks.h",
-                          "generated/bitslice_gen.h"],
-             "spbox": ["spbox.hip", "generated/spbox_gen.h"]}[kernel]
     h = hashlib.sha256()
-    for name in files:
+    for name in kernel_sources(kernel):
         with open(os.path.join(csrc, name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
