@@ -188,11 +188,14 @@ def kernel_key_bytes(schedule, direction, kernel):
 def _stream_handle(stream):
     import torch
     if stream is None:
-        if torch.cuda.is_initialized():
-            # the current device's current stream without a Stream object
-            # around it, which takes longer (2.9 us) than the rest of a call's
-            # marshalling
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        try:
+            if torch.cuda.is_initialized():
+                # the current device's current stream without a Stream object
+                # around it, which takes longer (2.9 us) than the rest of a call's
+                # marshalling
+                return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:  # not part of torch's interface
+            pass
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream)
 
