@@ -2,7 +2,7 @@
 //
 // One block per lane (spbox.hip), or two or three, interleaved; the blocks of all
 // messages in a row, `per` of them to a workgroup and step.  The lanes of the
-// bitsliced batch kernel (batch.hip) take 32 blocks each through the rounds, ~40 us
+// bitsliced batch kernel (batch.hip) take 32 blocks each through the rounds, ~36 us
 // for the smallest batch.
 //
 // A workgroup has a CU to itself: 64 KiB of tables, the round keys of up to
@@ -16,9 +16,9 @@
 //
 // Bound by the latency of its steps (descriptors, schedules, tables, one block's
 // 48 rounds), which a workgroup goes through one after the other: ~10 us for the
-// smallest batch, 150 GB/s on large ones.  Measured (us a submit, bitsliced ->
-// table): 16 messages of 4 KiB 41 -> 9.7, 300 of 6.7 KB 43 -> 16, 2,000 of 72
-// bytes 41 -> 12.
+// smallest batch, 180 GB/s on large ones.  Measured (us a submit, bitsliced ->
+// table): 16 messages of 4 KiB 40 -> 9.4, 300 of 7 KB 36 -> 19.4, 2,000 of 72
+// bytes 41 -> 11.7.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -292,10 +292,10 @@ __global__ __launch_bounds__(kThreads) void batch_table_kernel(const tdes_msg *_
 
 bool batch_is_table(size_t n_msgs, uint64_t work_bytes) {
     // us a submit, this kernel against the bitsliced one (256 CUs, one launch up
-    // to kTableScanMax messages): 300 messages in 2 MB 16 to 43, in 6 MB 37 to
-    // 40; 1,000 in 6.5 MB 49 to 45.  Three launches, lanes by slices: 4,000 in
-    // 1 MB 24 to 41, in 4 MB 48 to 41; 16,000 in 1.2 MB 39 to 42, in 4.2 MB 53
-    // to 43.
+    // to kTableScanMax messages): 300 messages in 2.1 MB 20 to 36, in 6 MB 35 to 36,
+    // in 7 MiB 52 to 38; 1,000 in 6 MB 36 to 37; 2,000 in 6 MB 37 to 41.  With the scan
+    // before it, lanes by slices: 4,000 in 1 MB 22 to 38, in 3 MB 34 to 37; 16,000 of
+    // a block 37 to 37.
     if (n_msgs <= kTableScanMax) return work_bytes <= spbox_one_pass_bytes() / 2 * 3;
     return work_bytes + kSlice * (uint64_t)n_msgs <= spbox_one_pass_bytes();
 }
@@ -310,13 +310,11 @@ hipError_t launch_batch_table(const tdes_msg *msgs, size_t n_msgs, const uint32_
     // more blocks a lane beat more steps (300 messages: 2.1 MB 21.2 -> 20.1 us, 4
     // MiB 28.4 -> 27.1, 6 MiB 39.8 -> 37.3), and even steps beat full ones with a
     // small last one (2.1 MB 25.5 -> 21.4).  work_bytes only bounds the work, so a
-    // kernel that scans divides what it finds, and short messages may take more lanes
-    // than blocks there (`least`), at most n_msgs x per / (kRows - 1) more.  (Steps
-    // sized here, by the mean message and work_bytes, against these: one of 5 MB beside
-    // 2,000 of a block, all in one workgroup's step of 32 passes, 482 -> 45 us; 2,048
-    // of a block in a buffer of 6 MiB 479 -> 28, 300 of 1,000 bytes there 34 -> 18;
-    // even ones up to 2 % slower.)  Where lanes go by slices, one block a lane.  Any grid
-    // is correct.
+    // kernel that scans divides what it finds.  (Steps sized here, by the mean message
+    // and work_bytes, against these: one of 5 MB beside 2,000 of a block, all in one
+    // workgroup's step of 32 passes, 482 -> 43 us; 2,048 of a block in a buffer of 6
+    // MiB 479 -> 27, 300 of 1,000 bytes there 34 -> 18; even ones up to 2 % slower.)
+    // Where lanes go by slices, one block a lane.  Any grid is correct.
     const bool scan = n_msgs <= kTableScanMax;
     // (a scanning kernel's extra workgroup has a CU too: as one more than fit it would
     // start when another ends, 1-1.8 us later)
@@ -326,13 +324,21 @@ hipError_t launch_batch_table(const tdes_msg *msgs, size_t n_msgs, const uint32_
     const uint32_t nb = !scan || cu_work <= kThreads ? 1 : cu_work <= 2 * kThreads ? 2 : 3;
     const uint64_t steps = (cu_work + nb * kThreads - 1) / (nb * kThreads);
     uint64_t per = steps == 0 ? 1 : (cu_work + steps - 1) / steps;
-    if (scan) per += per * n_msgs / ((kRows - 1) * cus);
     const uint32_t unit = nb * kWave;
-    per = (per + unit - 1) / unit * unit;
+    auto whole = [&](uint64_t v) { return (v + unit - 1) / unit * unit; };
+    per = whole(per);
+    // (no more workgroups than whole shares fill: one with nothing to do still holds a
+    // CU's LDS while it scans, 8-11 % of the rate of two streams)
+    uint64_t grid = (work + per - 1) / per;
+    grid = grid < 1 ? 1 : grid > cus ? cus : grid;
+    // room for the lanes that short messages leave idle, n_msgs x per / (kRows - 1) at
+    // most; a step of kRows lanes needs none
+    if (scan && per > kRows) {
+        const uint64_t room = (kRows - 1) * grid;
+        per = whole(per + (room > 2 * n_msgs ? per * n_msgs / (room - n_msgs) : per));
+    }
     if (per > (uint64_t)nb * kThreads) per = (uint64_t)nb * kThreads;
     const uint32_t least = per <= kRows ? 1 : (uint32_t)(per + kRows - 2) / (kRows - 1);
-    uint64_t grid = scan ? (work + n_msgs * (least - 1) + unit - 1) / unit : (work + per - 1) / per;
-    grid = grid < 1 ? 1 : grid > cus ? cus : grid;
     auto launch = [&](auto kernel, uint64_t g) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)g), dim3(kThreads), 0, stream, msgs, (uint32_t)n_msgs,
                            schedules, (uint32_t)n_schedules, in, out, bb, ws, skipped_out, (uint32_t)per, least);
