@@ -2,7 +2,7 @@
 // key schedule and direction, in one pass over the device.
 //
 // Work unit: a lane slice of 256 bytes (32 blocks) of one message; a
-// message of n bytes has ceil(n / 256) slices.  A single-workgroup scan
+// message of n bytes has ceil(n / 256) slices.  A scan over many workgroups
 // turns the descriptors into first-slice offsets (in the caller's
 // workspace); then a grid of twice the resident waves strides over the
 // slices, one per lane, 64 consecutive slices per wave per step.  Each lane
@@ -32,7 +32,12 @@
 // messages of a wave share the LDS mask table; WAVES waves per SIMD is
 // the occupancy the register budget is set for (KMAX 16 does not fit 4).  The first is the default
 // (with a grid of twice the resident workgroups); tdes_batch_autotune picks
-// among all of them and grids of 1..4 times the resident workgroups.
+// among all of them and grids of 1..4 times the resident workgroups.  All stay
+// because callers may set or have saved them.  us a submit, 16,384 messages of 113
+// MB / 112 of 1 MiB, grid 2: (8,4) 133 / 107, (8,3) 137 / 109, (4,3) 148 / 106, (4,4)
+// 150 / 106, (16,3) 151 / 109, (8,5) 147 / 113, (4,5) 157 / 111.  At 5 waves 62 and
+// 47 registers spill, outside the rounds; since one-message waves have scalar masks
+// the budget gains them nothing.
 #define TDES_BATCH_VARIANTS(X) X(8, 4) X(4, 4) X(8, 3) X(4, 3) X(16, 3) X(8, 5) X(4, 5)
 
 namespace tdes {

@@ -293,8 +293,13 @@ hipError_t launch_bitslice_mode(const BitsliceKeys &k, const ModeArgs &m, const 
                                 uint8_t *out, size_t nbytes, hipStream_t stream) {
     const size_t chunks = (nbytes + kChunk - 1) / kChunk;
     // Up to five chunks a CU every SIMD here would hold one wave, some two, and
-    // the split kernel is the faster (20 MiB on 256 CUs: 33.5 against 35.4 us;
-    // 24 MiB: 38.5 against 37.7).
+    // the split kernel is the faster (us on 256 CUs, split against this: 8 MiB 16.3 to
+    // 30.0, 12 MiB 21.0 to 30.2, 16 MiB 26.0 to 30.8, 20 MiB 31.9 to 34.5; CTR of 20
+    // MiB 30.5 to 34.8, CBC decryption 31.1 to 35.1).  Each chunk a CU more costs it 5
+    // us, this one 0.3 as long as the waves a SIMD are the same.  Of calls that overlap on several
+    // streams this kernel does more, which a call cannot see: us a call on two and on
+    // four streams, 8 MiB 10.7, 10.3 to 15.7, 10.3; 12 MiB 15.6, 16.0 to 16.2, 11.6; 16
+    // MiB 20.5, 21.1 to 17.1, 13.5.
     if (chunks <= 5 * device_cus()) return launch_bitslice_split<MODE>(k, m, in, out, nbytes, stream);
     const size_t blocks = (chunks + kWavesPerBlock - 1) / kWavesPerBlock;
     if (blocks > 0x7fffffffu) return hipErrorInvalidValue;

@@ -39,9 +39,9 @@ __device__ __forceinline__ uint32_t shl_paired(uint32_t b) {
 // exchange the J-bit groups where row bit J differs from column bit J.
 // Byte and half-word stages are one byte permute per word; bit stages are
 // a shift and a bitwise select (v_bitop3, which pairs with other waves'
-// instructions; v_bfi and v_perm do not).  Constants live in VGPRs: an
-// instruction with a scalar operand is never paired either.  Pairs are kept
-// in groups of four by scheduling barriers: the scheduler would otherwise
+// instructions; v_bfi and v_perm do not).  Constants live in VGPRs (as
+// scalars, which pair too, 0.2-0.6 % faster on ECB and no faster on CTR).
+// Pairs are kept in groups of four by scheduling barriers: the scheduler would otherwise
 // compute a whole stage's new words before retiring the old ones, holding
 // up to 32 more words live.
 template <int J>

@@ -17,16 +17,18 @@
 // The key masks are bits of the launch's key words, widened by scalar
 // instructions: no mask table in LDS, and nothing to build before the rounds.
 //
-// A round takes ~540 clocks, most of it the exchange, which all waves make at
-// once: 80 rows of LDS traffic (160 clocks at 128 B a clock), two LDS latencies and
-// the barrier.  From three chunks a CU on LDS bandwidth and the masks' unpaired
-// operations bound it, and the plain kernel is the faster one where its SIMDs hold
-// two waves or more.  Measured (kernel time, us, plain -> split, 176 S-box gates):
-// 1 MiB 31.3 -> 14.9, 4 MiB 31.8 -> 15.7, 8 MiB 31.3 -> 17.6, 12 MiB 32.0 -> 21.7, 16
-// MiB 32.3 -> 26.9, 20 MiB 35.4 -> 33.5, 24 MiB 37.7 -> 38.5; with 163 gates 8 MiB 17.2,
-// 12 MiB 21.5, and with the round loop unrolled four times 16.5 and 21.1.  Key words
-// picked from vector registers by v_readlane in place of scalar loads: 18.3 and 22.8.
-// Two boxes a wave (four waves, fewer rows): 19.2 at 1 MiB, 27.9 at 16 MiB.
+// With one chunk a CU a round takes ~540 clocks, most of it the exchange, which all
+// waves make at once: 80 rows of LDS traffic (160 clocks at 128 B a clock), two LDS
+// latencies and the barrier.  A second chunk fits beside it almost free; from the
+// third on LDS traffic (8,320 clocks a chunk) and issue slots (6,400, the masks'
+// operations do not pair) add up, neither of them full (0.54 of a CU's time each at
+// 12 MiB), and the plain kernel is the faster one where its SIMDs hold two waves or
+// more.  Measured (us a launch, plain -> split): 2 MiB 28.4 -> 14.2, 4 MiB 29.2 -> 14.7,
+// 8 MiB 30.0 -> 16.3, 12 MiB 30.2 -> 21.0, 16 MiB 30.8 -> 26.0, 20 MiB
+// 34.5 -> 31.9.  The round loop unrolled four times: 8 MiB 17.2 -> 16.5, 12 MiB 21.5
+// -> 21.1.  Key words picked from vector registers by v_readlane in place of scalar
+// loads: 18.3 and 22.8.  Two boxes a wave (four waves, fewer rows): 19.2 at 1 MiB,
+// 27.9 at 16 MiB.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

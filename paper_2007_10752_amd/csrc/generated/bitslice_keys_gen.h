@@ -28,7 +28,9 @@ static constexpr int kBsBoxDup[32] = {
     6, 7, -1, -1, 8, 9, -1, -1, 10, 11, -1, -1, 12, 13, 14, 15,
 };
 
-// Mask layout in LDS: round t, box j at kBsRoundMasks*t + kBsBoxMasks*j
-// (outputs 0..3, then second uses); then the four 32-word extra groups.
+// Places of the masks widened from the key words, as a table: round t, box j at
+// kBsRoundMasks*t + kBsBoxMasks*j (outputs 0..3, then second uses); then the four
+// 32-word extra groups.  The kernels use a box's kBsBoxMasks places (a row of the
+// batched kernel's table), the CPU emulation of the tests the whole.
 enum { kBsBoxMasks = 8, kBsRoundMasks = 64, kBsInitY = 3072, kBsRemask16 = 3104,
        kBsRemask32 = 3136, kBsFinalX = 3168, kBsNumMasks = 3200 };

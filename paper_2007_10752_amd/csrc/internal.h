@@ -19,8 +19,8 @@ struct RoundSequence {
 };
 
 // Kernel argument for the bitsliced kernel: the 100 key-mask words of one
-// direction (layout in keysched_core.h); the kernel expands the bits to
-// 0 / ~0 words in LDS.
+// direction (layout in keysched_core.h); scalar instructions of the kernel
+// widen the bits to 0 / ~0 operands.
 struct BitsliceKeys {
     uint32_t w[100];
 };

@@ -31,8 +31,8 @@
 //
 // The modes are those of bitslice.hip.  Inputs of a block per lane are bound by
 // one lane's chain of rounds (203 clocks each; the table fill takes ~2,100),
-// large ones by LDS and VALU issue together.  CTR and CBC decryption of 1 MiB
-// run 7.5 us a launch here, 14.8 on the split bitsliced kernel, 31 on the plain
+// large ones by LDS and VALU issue together.  CTR and CBC decryption of 2 MiB
+// run 11 us a launch here, 14 on the split bitsliced kernel, 28 on the plain
 // one.
 #include <hip/hip_runtime.h>
 #include <stdint.h>

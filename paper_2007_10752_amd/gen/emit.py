@@ -155,8 +155,8 @@ def out_word():
     return [pinv[m] for m in range(32)]
 
 
-# Layout of the per-launch key masks (0 or ~0 words) as the plain kernel
-# expands them into LDS: round t (0..47) takes 64 words at 64*t, 8 per S-box:
+# Layout of a direction's key masks (0 or ~0 words) as one table (the kernels widen
+# a round's at a time): round t (0..47) takes 64 words at 64*t, 8 per S-box:
 # box j at 64*t + 8*j holds [0..3] the masks folded into the XORs of its
 # outputs q = 0..3 into the other half, [4..7] the masks of its second-use
 # expansion inputs in input order (box_dups(j); unused slots 0); then 32
@@ -315,8 +315,10 @@ def emit_bitslice_keys():
         bd += ks + [-1] * (4 - len(ks))
     s.append("// Second-use index k of mask slot 4 + i of S-box j: kBsBoxDup[4*j + i] (-1: unused).\n")
     s.append(c_array("static constexpr int kBsBoxDup", bd))
-    s.append("\n// Mask layout in LDS: round t, box j at kBsRoundMasks*t + kBsBoxMasks*j\n"
-             "// (outputs 0..3, then second uses); then the four 32-word extra groups.\n")
+    s.append("\n// Places of the masks widened from the key words, as a table: round t, box j at\n"
+             "// kBsRoundMasks*t + kBsBoxMasks*j (outputs 0..3, then second uses); then the four\n"
+             "// 32-word extra groups.  The kernels use a box's kBsBoxMasks places (a row of the\n"
+             "// batched kernel's table), the CPU emulation of the tests the whole.\n")
     s.append("enum { kBsBoxMasks = %d, kBsRoundMasks = %d, kBsInitY = %d, kBsRemask16 = %d,\n"
              "       kBsRemask32 = %d, kBsFinalX = %d, kBsNumMasks = %d };\n"
              % (BS_BOX_MASKS, BS_ROUND_MASKS, BS_INIT_Y, BS_REMASK_16, BS_REMASK_32, BS_FINAL_X,
